@@ -786,73 +786,128 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
 // ============================================================================ split combine
 // Log-sum-exp merge of the per-split partial results (the same rescaling the paper uses to
 // merge partial attentions, Sec. 4.1.1 and App. B): each partial is stored in bf16, normalised by
-// its own sum l_s, and weighted by l_s 2^(m_s - M) / sum_s l_s 2^(m_s - M). Grid (n_rows, H), block 128.
+// its own sum l_s, and weighted by l_s 2^(m_s - M) / sum_s l_s 2^(m_s - M). Grid (n_rows, 64 heads).
+//
+// Two kernels by the number of splits ns. What bounds both is the chain of dependent round trips to
+// partials that other XCDs have just written, not their bytes. Up to kCombineRegs splits (32 rows and
+// more) one thread holds all partials of its four dims: one round trip. Beyond that (down to one row:
+// up to 256 splits) eight waves share the splits of a (row, head), each with kCombineDeep of its
+// partials in flight, and sum through LDS. One row of 73 splits: 48.8 us with one thread walking its
+// splits in turn, 4.5 us so.
 constexpr int kCombineRegs = 8;  // splits whose partials a thread holds at once
-__global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a, int H, int d_v) {
+__device__ __forceinline__ f32x4 bf16x4_f32(u32x2 v) {
+  return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
+               __uint_as_float(v.y & 0xFFFF0000u)};
+}
+__global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
+  constexpr int H = 64, d_v = 512;
   const int64_t row = blockIdx.x;
   const int head = blockIdx.y;
   const int ns = a.n_split;
   auto pidx = [&](int s) { return (row * ns + s) * H + head; };
-  if (ns <= kCombineRegs && d_v == 512) {
-    // every split's maximum, sum and four values of this thread requested together (one round trip)
-    const int d = (int)threadIdx.x * 4;
-    float ms[kCombineRegs], ls[kCombineRegs];
-    u32x2 pv[kCombineRegs];
+  // every split's maximum, sum and four values of this thread requested together (one round trip)
+  const int d = (int)threadIdx.x * 4;
+  float ms[kCombineRegs], ls[kCombineRegs];
+  u32x2 pv[kCombineRegs];
 #pragma unroll
-    for (int s = 0; s < kCombineRegs; ++s) {
-      ms[s] = -INFINITY;
-      ls[s] = 0.f;
-      pv[s] = u32x2{0u, 0u};
-      if (s < ns) {
-        const int64_t pi = pidx(s);
-        ms[s] = a.part_ml[pi * 2];
-        ls[s] = a.part_ml[pi * 2 + 1];
-        pv[s] = *reinterpret_cast<const u32x2*>(a.part_o + pi * d_v + d);
-      }
+  for (int s = 0; s < kCombineRegs; ++s) {
+    ms[s] = -INFINITY;
+    ls[s] = 0.f;
+    pv[s] = u32x2{0u, 0u};
+    if (s < ns) {
+      const int64_t pi = pidx(s);
+      ms[s] = a.part_ml[pi * 2];
+      ls[s] = a.part_ml[pi * 2 + 1];
+      pv[s] = *reinterpret_cast<const u32x2*>(a.part_o + pi * d_v + d);
     }
-    float M = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kCombineRegs; ++s) M = fmaxf(M, ms[s]);
-    float L = 0.f;
-    f32x4 acc = {};
-#pragma unroll
-    for (int s = 0; s < kCombineRegs; ++s) {
-      if (!(ls[s] > 0.f)) continue;
-      // the partial is normalised by its own sum ls: weight it back by ls 2^(m_s - M)
-      const float wgt = ls[s] * fast_exp2(ms[s] - M);
-      L += wgt;
-      acc += wgt * f32x4{__uint_as_float(pv[s].x << 16), __uint_as_float(pv[s].x & 0xFFFF0000u),
-                         __uint_as_float(pv[s].y << 16), __uint_as_float(pv[s].y & 0xFFFF0000u)};
-    }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    const u32x2 v = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
-    *reinterpret_cast<u32x2*>(a.out + (row * H + head) * d_v + d) = v;
-    if (a.lse && threadIdx.x == 0) a.lse[row * H + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
-    return;
   }
   float M = -INFINITY;
-  for (int s = 0; s < ns; ++s) M = fmaxf(M, a.part_ml[pidx(s) * 2]);
+#pragma unroll
+  for (int s = 0; s < kCombineRegs; ++s) M = fmaxf(M, ms[s]);
   float L = 0.f;
-  for (int s = 0; s < ns; ++s) {
-    const int64_t pi = pidx(s);
-    const float ms = a.part_ml[pi * 2], ls = a.part_ml[pi * 2 + 1];
-    L += ls > 0.f ? ls * fast_exp2(ms - M) : 0.f;
+  f32x4 acc = {};
+#pragma unroll
+  for (int s = 0; s < kCombineRegs; ++s) {
+    if (!(ls[s] > 0.f)) continue;
+    // the partial is normalised by its own sum ls: weight it back by ls 2^(m_s - M)
+    const float wgt = ls[s] * fast_exp2(ms[s] - M);
+    L += wgt;
+    acc += wgt * bf16x4_f32(pv[s]);
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
-  for (int d = threadIdx.x * 4; d < d_v; d += 128 * 4) {
-    f32x4 acc = {};
-    for (int s = 0; s < ns; ++s) {
-      const int64_t pi = pidx(s);
-      const float ls = a.part_ml[pi * 2 + 1];
-      if (!(ls > 0.f)) continue;
-      // the partial is normalised by its own sum ls: weight it back by ls 2^(m_s - M)
-      const float wgt = ls * fast_exp2(a.part_ml[pi * 2] - M);
-      const u32x2 pv = *reinterpret_cast<const u32x2*>(a.part_o + pi * d_v + d);
-      acc += wgt * f32x4{__uint_as_float(pv.x << 16), __uint_as_float(pv.x & 0xFFFF0000u),
-                         __uint_as_float(pv.y << 16), __uint_as_float(pv.y & 0xFFFF0000u)};
+  const u32x2 v = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
+  *reinterpret_cast<u32x2*>(a.out + (row * H + head) * d_v + d) = v;
+  if (a.lse && threadIdx.x == 0) a.lse[row * H + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
+}
+
+// More than kCombineRegs splits: wave w of eight sums splits w, w + 8, .. (lane l: dims 8 l .. + 7).
+constexpr int kCombineDeep = 8;  // partials of 16 bytes per lane a wave requests together
+__global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
+  constexpr int H = 64, d_v = 512;
+  __shared__ __attribute__((aligned(16))) float sum[8][d_v];
+  __shared__ float wl[8];
+  const int64_t row = blockIdx.x;
+  const int head = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int ns = a.n_split;
+  const int64_t p0 = row * ns * H + head;  // split s: p0 + s H
+  // the first partials are requested before their weights are known
+  u32x4 pv[kCombineDeep];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kCombineDeep; ++u) {
+      const int s = s0 + 8 * u;
+      pv[u] = s < ns ? *reinterpret_cast<const u32x4*>(a.part_o + (p0 + (int64_t)s * H) * d_v + 8 * lane) : u32x4{0, 0, 0, 0};
     }
-    const u32x2 v = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
-    *reinterpret_cast<u32x2*>(a.out + (row * H + head) * d_v + d) = v;
+  };
+  request(wv);
+  // maximum over all splits: every wave reads all of them, a lane four apart
+  float m4[4], M = -INFINITY;
+  for (int b = 0; b < ns; b += 256) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = b + 64 * u + lane;
+      m4[u] = s < ns ? a.part_ml[(p0 + (int64_t)s * H) * 2] : -INFINITY;
+    }
+    M = fmaxf(M, fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
+  }
+  M = wave_max(M);
+  float acc[8] = {}, L = 0.f;
+  for (int s0 = wv; s0 < ns; s0 += 8 * kCombineDeep) {
+    if (s0 != wv) request(s0);
+    float ms[kCombineDeep], ls[kCombineDeep];
+#pragma unroll
+    for (int u = 0; u < kCombineDeep; ++u) {
+      const int s = s0 + 8 * u;
+      const int64_t pi = p0 + (int64_t)(s < ns ? s : 0) * H;
+      ms[u] = a.part_ml[pi * 2];
+      ls[u] = s < ns ? a.part_ml[pi * 2 + 1] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kCombineDeep; ++u) {
+      if (!(ls[u] > 0.f)) continue;  // (an empty piece of the list)
+      const float wgt = ls[u] * fast_exp2(ms[u] - M);
+      L += wgt;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        acc[2 * k] += wgt * __uint_as_float(pv[u][k] << 16);
+        acc[2 * k + 1] += wgt * __uint_as_float(pv[u][k] & 0xFFFF0000u);
+      }
+    }
+  }
+  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane]) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane + 4]) = f32x4{acc[4], acc[5], acc[6], acc[7]};
+  if (lane == 0) wl[wv] = L;
+  __syncthreads();
+  L = 0.f;
+#pragma unroll
+  for (int x = 0; x < 8; ++x) L += wl[x];
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  if (threadIdx.x < d_v / 2) {
+    const int d = 2 * (int)threadIdx.x;
+    f32x2 o = {};
+#pragma unroll
+    for (int x = 0; x < 8; ++x) o += *reinterpret_cast<const f32x2*>(&sum[x][d]);
+    *reinterpret_cast<uint32_t*>(a.out + (row * H + head) * d_v + d) = pack_bf16x2(o[0] * inv, o[1] * inv);
   }
   if (a.lse && threadIdx.x == 0) a.lse[row * H + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
@@ -893,7 +948,7 @@ hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st) {
     launch_mla_kernel<true>(dim3((unsigned)a.n_rows, (unsigned)a.n_split), a, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_attn_combine(a, 64, 512, st);
+    return launch_attn_combine(a, st);
   }
   launch_mla_kernel<false>(dim3((unsigned)a.n_rows), a, st);
   return hipGetLastError();
@@ -918,8 +973,12 @@ hipError_t launch_mqa_attn(const AttnGeom& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_attn_combine(const AttnGeom& a, int H, int d_v, hipStream_t st) {
-  hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)a.n_rows, (unsigned)H), dim3(128), 0, st, a, H, d_v);
+hipError_t launch_attn_combine(const AttnGeom& a, hipStream_t st) {
+  const dim3 grid((unsigned)a.n_rows, 64u);
+  if (a.n_split <= kCombineRegs)
+    hipLaunchKernelGGL(attn_combine_kernel, grid, dim3(128), 0, st, a);
+  else
+    hipLaunchKernelGGL(attn_combine_deep_kernel, grid, dim3(512), 0, st, a);
   return hipGetLastError();
 }
 

@@ -94,7 +94,7 @@ struct AttnGeom {
 
 hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st);
 hipError_t launch_mqa_attn(const AttnGeom& a, hipStream_t st);
-hipError_t launch_attn_combine(const AttnGeom& a, int H, int d_v, hipStream_t st);
+hipError_t launch_attn_combine(const AttnGeom& a, hipStream_t st);  // MLA: 64 heads x 512
 // One part (a.part = 0 or 1) of the split attention into the partials a.part_o / a.part_ml.
 hipError_t launch_mla_attn_part(const AttnGeom& a, hipStream_t st);
 // The window part (a.part = 1) as the query-tiled kernel: two consecutive rows per workgroup

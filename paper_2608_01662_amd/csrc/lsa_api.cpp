@@ -776,7 +776,7 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
     if ((e = lsa::launch_mla_attn_window(a, hs->side)) != hipSuccess) return hip_fail(e, "split attention (window)");
     if ((e = hipEventRecord(hs->join, hs->side)) != hipSuccess) return hip_fail(e, "split attention join");
     if ((e = hipStreamWaitEvent(st, hs->join, 0)) != hipSuccess) return hip_fail(e, "split attention join");
-    if ((e = lsa::launch_attn_combine(a, 64, 512, st)) != hipSuccess) return hip_fail(e, "split attention merge");
+    if ((e = lsa::launch_attn_combine(a, st)) != hipSuccess) return hip_fail(e, "split attention merge");
   }
   return LSA_OK;
 }

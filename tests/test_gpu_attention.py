@@ -217,6 +217,33 @@ def test_long_lists_beyond_one_staging_pass():
         P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
 
 
+@pytest.mark.parametrize("n_rows,k_cap", [(1, 2308), (1, 8192), (2, 96), (3, 2600), (28, 2308), (29, 2308), (32, 2308)],
+                         ids=lambda v: str(v))
+def test_split_merge_counts(n_rows, k_cap):
+    """The merge of split lists at its edges: 73 pieces and the largest count (256, one tile each) for one
+    row, three pieces of one tile, 82 pieces, and the counts on both sides of the switch between its two
+    kernels (10, 9 and 8 pieces), with one row shorter than a piece (the others of its pieces are empty)
+    and one empty row, against the oracle."""
+    from dataclasses import replace
+    w = replace(W.SMALL_MLA, seq_len=9000)
+    n_kv = w.seq_len
+    a = _attn_inputs(w, 0, n_rows, n_kv)
+    g = np.random.default_rng(13)
+    cnt = np.full(n_rows, k_cap, np.int32)
+    cnt[-1] = k_cap - 7
+    if n_rows > 2:
+        cnt[0], cnt[1] = 5, 0
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    for i, c in enumerate(cnt):
+        idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
+    rows = list(range(n_rows))
+    o, l = _gpu_attn(w, a, rows, idx, cnt)
+    if n_rows > 2:
+        assert np.all(o[1] == 0) and np.all(np.isneginf(l[1])), "an empty list attends to nothing"
+    keep = [i for i in rows if cnt[i] > 0]
+    _check_rows(w, a, keep, idx[keep], cnt[keep], o[keep], l[keep])
+
+
 def test_many_rows_mixed_lists():
     """Calls of 256 rows or more run one pass over each row's whole list (no split into pieces):
     259 rows mixing short lists, empty lists, one exact tile and lists longer than one staging pass
