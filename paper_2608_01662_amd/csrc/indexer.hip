@@ -17,6 +17,7 @@
 // operands leaves the dot product unchanged, and this one lets every lane read one contiguous
 // run of key bytes.
 #include <atomic>
+#include <type_traits>
 
 #include "device.hpp"
 #include "launch.hpp"
@@ -65,47 +66,10 @@ __device__ __forceinline__ int64_t phys_page(const IndexGeom& g, int64_t seq, in
 }
 
 // ============================================================================ block cache (Stage 1)
-// Sub-block handled by work item `item`: item itself (whole cache), or the sub-block holding token
-// rows[item] (incremental update); -1 when that row is out of range or in the incomplete tail.
-__device__ __forceinline__ int64_t block_of_item(int64_t item, const int64_t* __restrict__ rows, int64_t n_tok, int B) {
-  if (rows == nullptr) return item;
-  const int64_t r = rows[item];
+// Sub-block holding token row r of an incremental update; -1 when r is out of range or in the
+// incomplete tail.
+__device__ __forceinline__ int64_t block_of_row(int64_t r, int64_t n_tok, int B) {
   return (r >= 0 && r < n_tok && r / B < n_tok / B) ? r / B : -1;
-}
-
-// Mean keys (Eq. 9). One thread per (work item, group of 4 dims): fp32 sum of s_i * k_i over the
-// B tokens, one multiply by 1/B (B is a power of two, exact), one round-to-nearest-even to bf16.
-template <bool FP8>
-__global__ __launch_bounds__(256) void block_means_kernel(int64_t n_items, const int64_t* __restrict__ rows, int64_t n_tok,
-                                                          int D, int B, const void* __restrict__ k,
-                                                          const float* __restrict__ ks, uint16_t* __restrict__ out) {
-  const int groups = D / 4;
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= n_items * groups) return;
-  const int64_t item = id / groups;
-  const int gq = (int)(id - item * groups);
-  const int64_t sub = block_of_item(item, rows, n_tok, B);
-  if (sub < 0) return;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i = 0; i < B; ++i) {
-    const int64_t tok = sub * B + i;
-    if (FP8) {
-      const uint32_t v = reinterpret_cast<const uint32_t*>(k)[tok * groups + gq];
-      const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(v, false);
-      const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(v, true);
-      const float s = ks[tok];
-      acc[0] += s * lo.x; acc[1] += s * lo.y; acc[2] += s * hi.x; acc[3] += s * hi.y;
-    } else {
-      const u32x2 v = reinterpret_cast<const u32x2*>(k)[tok * groups + gq];
-      acc[0] += __uint_as_float(v.x << 16); acc[1] += __uint_as_float(v.x & 0xFFFF0000u);
-      acc[2] += __uint_as_float(v.y << 16); acc[3] += __uint_as_float(v.y & 0xFFFF0000u);
-    }
-  }
-  const float inv = 1.0f / (float)B;
-  u32x2 o;
-  o.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-  o.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-  reinterpret_cast<u32x2*>(out)[sub * groups + gq] = o;
 }
 
 // bf16 bits of x rounded to nearest, ties to even, in one step from fp64: the float rounded
@@ -120,49 +84,97 @@ __device__ __forceinline__ uint32_t bf16_rne_from_f64(double x) {
   return (b >> 16) + (half & (uint32_t)(rest || lsb));
 }
 
-// Min-max extrema (Eq. 13). One thread per (work item, group of 4 dims): each dequantised key
-// s_i * k_i is formed exactly in fp64 (24-bit scale times 4-bit code), the extrema are exact, and
-// each is rounded once to bf16. Output row: [k_max (D) | k_min (D)].
-template <bool FP8>
-__global__ __launch_bounds__(256) void block_minmax_kernel(int64_t n_items, const int64_t* __restrict__ rows, int64_t n_tok,
-                                                           int D, int B, const void* __restrict__ k,
-                                                           const float* __restrict__ ks, uint16_t* __restrict__ out) {
-  const int groups = D / 4;
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= n_items * groups) return;
-  const int64_t item = id / groups;
-  const int gq = (int)(id - item * groups);
-  const int64_t sub = block_of_item(item, rows, n_tok, B);
-  if (sub < 0) return;
-  double mx[4], mn[4];
-  for (int i = 0; i < B; ++i) {
-    const int64_t tok = sub * B + i;
-    double v[4];
-    if (FP8) {
-      const uint32_t c = reinterpret_cast<const uint32_t*>(k)[tok * groups + gq];
-      const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(c, false);  // codes decode exactly
-      const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(c, true);
-      const double s = (double)ks[tok];
-      v[0] = s * (double)lo.x; v[1] = s * (double)lo.y; v[2] = s * (double)hi.x; v[3] = s * (double)hi.y;
-    } else {
-      const u32x2 c = reinterpret_cast<const u32x2*>(k)[tok * groups + gq];
-      v[0] = (double)__uint_as_float(c.x << 16); v[1] = (double)__uint_as_float(c.x & 0xFFFF0000u);
-      v[2] = (double)__uint_as_float(c.y << 16); v[3] = (double)__uint_as_float(c.y & 0xFFFF0000u);
-    }
+// The block cache. A workgroup copies kBlockTok tokens (128 / B sub-blocks, or half of one of 256) into
+// LDS with 16-byte loads that are all in flight together, then each thread takes two dims of a
+// sub-block and walks its B tokens in order.
+//   Mean keys (Eq. 9): fp32 sum of s_i * k_i in token order, one multiply by 1/B (B is a power of two,
+//   exact), one round-to-nearest-even to bf16.
+//   Min-max extrema (Eq. 13): each dequantised key s_i * k_i is formed exactly in fp64 (24-bit scale
+//   times 4-bit code), the extrema are exact, and each is rounded once to bf16. Row: [k_max | k_min].
+// Latency bounds it: a prefix of 128K tokens is 17.6 MB, 4 us at the copy rate, and an appended token's
+// sub-block a few KB. With a thread per four dims reading its B tokens one dword after the other, a 128K
+// prefix at B = 128 took 25.7 us (min-max 36.4) and the update of 64 sequences' sub-blocks (B = 64)
+// 31.3 us; here 6.1 (11.3) and 4.0 us. At 1M tokens and B = 8 bandwidth bounds both (31.4 and 27.9 us). Same order of the sums, bit-identical results.
+constexpr int kBlockTok = 128;  // tokens staged at a time
+template <bool FP8, bool MINMAX>
+__global__ __launch_bounds__(256) void block_cache_kernel(int64_t n_items, const int64_t* __restrict__ rows, int64_t n_tok,
+                                                          int D, int B, const void* __restrict__ k,
+                                                          const float* __restrict__ ks, uint16_t* __restrict__ out) {
+  constexpr int kPieces = kBlockTok * 128 * (FP8 ? 1 : 2) / 16 / 256;  // 16-byte loads per thread (D = 128)
+  __shared__ __attribute__((aligned(16))) uint8_t kl[kBlockTok * 128 * (FP8 ? 1 : 2)];
+  __shared__ float sl[FP8 ? kBlockTok : 1];
+  const int tid = threadIdx.x, RB = D * (FP8 ? 1 : 2), half_d = D / 2;
+  int64_t sub0;  // first sub-block of this workgroup
+  int nsub = 1;
+  if (rows == nullptr) {
+    const int spw = B < kBlockTok ? kBlockTok / B : 1;
+    sub0 = (int64_t)blockIdx.x * spw;
+    nsub = (int)(n_items - sub0 < spw ? n_items - sub0 : spw);
+  } else {
+    sub0 = block_of_row(rows[blockIdx.x], n_tok, B);
+    if (sub0 < 0) return;  // (uniform)
+  }
+  const int n = nsub * B;  // tokens of this workgroup (at most kBlockTok unless B = 256)
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(k) + sub0 * B * RB;
+  using acc_t = std::conditional_t<MINMAX, double, float>;
+  acc_t x0 = 0, x1 = 0, y0 = 0, y1 = 0;  // sums, or maxima (x) and minima (y)
+  for (int c0 = 0; c0 < n; c0 += kBlockTok) {
+    const int nt = n - c0 < kBlockTok ? n - c0 : kBlockTok, np = nt * RB / 16;
+    const u32x4* sp = reinterpret_cast<const u32x4*>(src + (int64_t)c0 * RB);
+    u32x4 v[kPieces];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      mx[e] = (i == 0 || v[e] > mx[e]) ? v[e] : mx[e];
-      mn[e] = (i == 0 || v[e] < mn[e]) ? v[e] : mn[e];
+    for (int u = 0; u < kPieces; ++u) v[u] = tid + 256 * u < np ? sp[tid + 256 * u] : u32x4{0u, 0u, 0u, 0u};
+    float sc = 0.f;
+    if (FP8 && tid < nt) sc = ks[sub0 * B + c0 + tid];
+    if (c0 > 0) __syncthreads();  // the previous tokens' readers are done
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u)
+      if (tid + 256 * u < np) *reinterpret_cast<u32x4*>(kl + 16 * (tid + 256 * u)) = v[u];
+    if (FP8 && tid < nt) sl[tid] = sc;
+    __syncthreads();
+    const int per = B < kBlockTok ? B : kBlockTok;  // tokens of a sub-block here
+    for (int it = tid; it < nsub * half_d; it += 256) {
+      const int s = it / half_d, dp = it - s * half_d;
+      if (c0 == 0) x0 = x1 = y0 = y1 = 0;
+      const uint8_t* kp = kl + s * B * RB + dp * (FP8 ? 2 : 4);
+#pragma unroll 8
+      for (int i = 0; i < per; ++i) {
+        f32x2 e;
+        if constexpr (FP8) {
+          e = __builtin_amdgcn_cvt_pk_f32_fp8(*reinterpret_cast<const uint16_t*>(kp + i * RB), false);
+        } else {
+          const uint32_t w = *reinterpret_cast<const uint32_t*>(kp + i * RB);
+          e = f32x2{__uint_as_float(w << 16), __uint_as_float(w & 0xFFFF0000u)};
+        }
+        if constexpr (MINMAX) {
+          const double f = FP8 ? (double)sl[s * B + i] : 1.0;
+          const double p0 = f * (double)e.x, p1 = f * (double)e.y;
+          const bool first = c0 == 0 && i == 0;
+          x0 = (first || p0 > x0) ? p0 : x0;
+          x1 = (first || p1 > x1) ? p1 : x1;
+          y0 = (first || p0 < y0) ? p0 : y0;
+          y1 = (first || p1 < y1) ? p1 : y1;
+        } else if constexpr (FP8) {
+          const float f = sl[s * B + i];
+          x0 += f * e.x;
+          x1 += f * e.y;
+        } else {
+          x0 += e.x;
+          x1 += e.y;
+        }
+      }
+      if (c0 + kBlockTok < n) continue;  // (B = 256: one item per thread, the second half follows)
+      const int64_t sub = sub0 + s;
+      if constexpr (MINMAX) {
+        uint32_t* row = reinterpret_cast<uint32_t*>(out + sub * 2 * D) + dp;
+        row[0] = bf16_rne_from_f64(x0) | (bf16_rne_from_f64(x1) << 16);
+        row[half_d] = bf16_rne_from_f64(y0) | (bf16_rne_from_f64(y1) << 16);
+      } else {
+        const float inv = 1.0f / (float)B;
+        reinterpret_cast<uint32_t*>(out + sub * D)[dp] = pack_bf16x2(x0 * inv, x1 * inv);
+      }
     }
   }
-  u32x2 hi, lo;
-  hi.x = bf16_rne_from_f64(mx[0]) | (bf16_rne_from_f64(mx[1]) << 16);
-  hi.y = bf16_rne_from_f64(mx[2]) | (bf16_rne_from_f64(mx[3]) << 16);
-  lo.x = bf16_rne_from_f64(mn[0]) | (bf16_rne_from_f64(mn[1]) << 16);
-  lo.y = bf16_rne_from_f64(mn[2]) | (bf16_rne_from_f64(mn[3]) << 16);
-  u32x2* row = reinterpret_cast<u32x2*>(out + sub * 2 * D);
-  row[gq] = hi;
-  row[groups + gq] = lo;
 }
 
 // ============================================================================ operand loads
@@ -1774,15 +1786,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KPT <= 16 ? 
 template <bool FP8, bool MINMAX>
 static hipError_t launch_bk(int64_t n_items, const int64_t* rows, int64_t n_tok, int D, int B, const void* k,
                             const float* ks, uint16_t* out, hipStream_t st) {
-  const int64_t threads = n_items * (D / 4);
-  if (threads == 0) return hipSuccess;
-  const int64_t blocks = (threads + 255) / 256;
-  if (MINMAX)
-    hipLaunchKernelGGL(block_minmax_kernel<FP8>, dim3((unsigned)blocks), dim3(256), 0, st, n_items, rows, n_tok, D, B,
-                       k, ks, out);
-  else
-    hipLaunchKernelGGL(block_means_kernel<FP8>, dim3((unsigned)blocks), dim3(256), 0, st, n_items, rows, n_tok, D, B,
-                       k, ks, out);
+  if (n_items == 0) return hipSuccess;
+  const int spw = rows == nullptr && B < kBlockTok ? kBlockTok / B : 1;  // sub-blocks per workgroup
+  hipLaunchKernelGGL((block_cache_kernel<FP8, MINMAX>), dim3((unsigned)((n_items + spw - 1) / spw)), dim3(256), 0, st,
+                     n_items, rows, n_tok, D, B, k, ks, out);
   return hipGetLastError();
 }
 

@@ -74,6 +74,36 @@ def test_block_minmax_parity(fp8, B):
 
 
 @pytest.mark.parametrize("pooling", ["mean", "minmax"])
+@pytest.mark.parametrize("head_dim,fp8,B,n", [(64, True, 256, 3 * 256 + 255), (128, False, 256, 2 * 256), (128, False, 128, 300),
+                                              (64, False, 128, 129), (128, True, 2, 128 * 3 + 7), (128, True, 32, 31),
+                                              (64, True, 16, 128 + 16)])
+def test_block_cache_staging_edges(head_dim, fp8, B, n, pooling):
+    """The block cache where its 128-token staging can go wrong: sub-blocks of two stagings (B = 256), a
+    last workgroup with one or few sub-blocks, a prefix shorter than one sub-block, both row widths; and
+    the update of single rows gives the same bits."""
+    inp = synth.indexer_inputs(8, 1, n, 8, head_dim, fp8)
+    page = max(32, B)
+    prm = lsa.IndexParams(8, head_dim, fp8, page, B, 0, 16, 4, 128, 64, pooling)
+    k = P.to_dev(inp["k"]) if fp8 else P.bf16_dev(inp["k"])
+    ks = P.to_dev(inp["k_scale"]) if fp8 else None
+    block = lsa.block_keys(prm, k, ks)
+    got = block.view(torch.int16).cpu().numpy().view(np.uint16)
+    k_hat = P.oracle_keys(inp)
+    if pooling == "minmax":
+        ref = np.concatenate([orc.f64_to_bf16_bits(x) for x in orc.sub_block_minmax_keys(k_hat, B)], axis=1)
+        assert np.array_equal(got, ref)
+    else:
+        ref = orc.f64_to_bf16_bits(orc.sub_block_mean_keys(k_hat, B))
+        # an fp32 sum of B terms is within B 2^-24 of the sum of their magnitudes: a result next to a
+        # bf16 rounding boundary may land one ulp away
+        assert got.shape == ref.shape and np.all(np.abs(got.astype(np.int32) - ref.astype(np.int32)) <= 1)
+    again = torch.full_like(block, 7.0)
+    rows = torch.arange(0, n, max(1, B // 2), dtype=torch.int64, device=k.device)
+    lsa.block_keys_update(prm, rows, k, ks, again)
+    assert torch.equal(again.view(torch.int16), block.view(torch.int16))
+
+
+@pytest.mark.parametrize("pooling", ["mean", "minmax"])
 @pytest.mark.parametrize("fp8", [True, False])
 def test_block_keys_update_after_append(pooling, fp8):
     """Decode appends tokens to a cache whose block cache already exists: updating the sub-blocks
