@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(256) void fine_kernel(IndexGeom g, int64_t n_rows, 
   }
 }
 
-// Prefill variant (contiguous keys): one wave per (group of rows, XCD), the rows taken in turn.
+// Prefill variant (contiguous keys): one wave per (one or two rows, XCD), or several per (row, XCD).
 // Workgroup b runs on XCD b mod 8, and the wave of XCD x scores only the recalled pages p with
 // p mod 8 == x, so each XCD's L2 holds one eighth of the keys instead of streaming all of them. A page's keys are one contiguous
 // block of P rows, copied into LDS 64 rows at a time by direct loads in which the 16-byte granules
@@ -1071,13 +1071,14 @@ __device__ __forceinline__ int fine_swz(int t) {
 }
 
 constexpr int kFineChunk = 64;  // key rows staged in LDS at a time
-constexpr int kFineRowsPerWave = 8;  // query rows a fine-scoring wave takes in turn
+constexpr int kFineRowsPerWave = 2;  // query rows a fine-scoring wave takes in turn (long calls)
 
 template <int D, bool FP8>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP8 || D == 64 ? 4 : 3, 8))) void fine_xcd_kernel(IndexGeom g, int64_t n_rows, const uint16_t* __restrict__ q,
                                                       const float* __restrict__ w, const void* __restrict__ k,
                                                       const float* __restrict__ kscale, const int32_t* __restrict__ pages,
-                                                      uint32_t* __restrict__ fine_keys, int64_t ldf) {
+                                                      uint32_t* __restrict__ fine_keys, int64_t ldf, int rows_per_wave,
+                                                      int parts) {
   constexpr int KS = D / 16;          // MFMA k-steps
   constexpr int RB = FP8 ? D : 2 * D;
   constexpr int GR = RB / 16;
@@ -1086,9 +1087,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP8 || D == 
   __shared__ float lsc[kFineChunk];
   const int lane = threadIdx.x, j = lane & 31, h = lane >> 5;
   const int x = (int)(blockIdx.x & 7);
-  // kFineRowsPerWave consecutive query rows, one after the other (fewer, longer-lived waves)
-  const int64_t rbeg = (int64_t)(blockIdx.x >> 3) * kFineRowsPerWave;
-  const int64_t rend = rbeg + kFineRowsPerWave < n_rows ? rbeg + kFineRowsPerWave : n_rows;
+  // rows_per_wave consecutive query rows, one after the other (fewer, longer-lived waves), or with
+  // parts > 1 (a power of two) every parts-th of the XCD's pages of one row
+  const int64_t group = (int64_t)(blockIdx.x >> 3) / parts;
+  const int part = (int)((blockIdx.x >> 3) & (unsigned)(parts - 1));
+  const int64_t rbeg = group * rows_per_wave;
+  const int64_t rend = rbeg + rows_per_wave < n_rows ? rbeg + rows_per_wave : n_rows;
   for (int64_t row = rbeg; row < rend; ++row) {
     const RowInfo ri = row_info(g, row);
     if (!ri.valid || ri.p_hi < ri.p_lo) continue;
@@ -1148,7 +1152,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP8 || D == 
       // page ids fit in 31 bits (n_kv < 2^31)
       const int page = kk < n_sel ? (flat ? (int)(ri.p_lo + kk) : pages[row * g.M + kk]) : -1;
       // this wave's pages in this block (recalled pages are always eligible; checked anyway)
-      const uint64_t mine = __ballot(page >= ri.p_lo && page <= ri.p_hi && (page & 7) == x);
+      const uint64_t mine = __ballot(page >= ri.p_lo && page <= ri.p_hi && (page & 7) == x && ((page >> 3) & (parts - 1)) == part);
       if (!mine) continue;
       // page id held by lane b, as a wave-uniform value
       auto page_of = [&](int b) { return (int64_t)__builtin_amdgcn_readlane(page, b); };
@@ -1802,6 +1806,22 @@ hipError_t launch_block_keys(int64_t n_items, const int64_t* rows, int64_t n_tok
              : launch_bk<false, false>(n_items, rows, n_tok, D, B, k, ks, out, st);
 }
 
+// Prefill calls of few rows split each row group's tiles into chunks (grid y) until the launch has
+// `fill` workgroups, of at least `least` tiles each: every chunk loads its rows' query operands
+// again, so no more of them than fill the GPU. Four-wave kernel: 512 rows of 4096 tiles (1M tokens,
+// B = 8) took 2570 us in 128 workgroups, 770 in 512, 770 to 850 in 1024 to 4096; min-max rows of 32
+// tiles lost 20% to two chunks of 16 (82 to 98 us at 2000 rows). Staged kernel, 16-tile rows: 100 rows
+// 21.4 us whole, 10.0 in chunks of 4, 7.1 in chunks of 2; 901 rows 22.5, 13.8 and 19.5, so 1024
+// workgroups suffice (4096 rows of 14 tiles: 35 us whole, 42 in halves).
+constexpr int64_t kCoarseFill = 512;
+constexpr int kCoarseMin = 64;
+constexpr int64_t kCoarseStagedFill = 1024;
+constexpr int kCoarseStagedMin = 2;
+static int coarse_chunk(int64_t groups, int64_t max_tiles, int64_t fill, int least) {
+  int64_t per = max_tiles;
+  while (per > least && groups * ((max_tiles + per - 1) / per) < fill) per = (per + 1) / 2;
+  return (int)per;
+}
 template <int D, int R, bool PAGED, bool MINMAX>
 static hipError_t launch_coarse_t(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w,
                                   const uint16_t* kmean, uint32_t* page_keys, int64_t ld, int64_t max_tiles,
@@ -1810,12 +1830,14 @@ static hipError_t launch_coarse_t(const IndexGeom& g, int64_t n_rows, const uint
   if (!PAGED && !MINMAX && max_tiles <= kCoarseStagedTiles && g.n_sub > 0 &&
       g.n_sub <= ((int64_t)1 << 32) / D / 2) {  // one wave per workgroup, all tiles of its rows
     constexpr int RS = kCoarseRowsStaged;
-    const dim3 grid((unsigned)((n_rows + RS - 1) / RS), 1u);
+    const int64_t groups = (n_rows + RS - 1) / RS;
+    const int per = coarse_chunk(groups, max_tiles, kCoarseStagedFill, kCoarseStagedMin);
+    const dim3 grid((unsigned)groups, (unsigned)((max_tiles + per - 1) / per));
     hipLaunchKernelGGL((coarse_kernel<D, RS, false, false, true>), grid, dim3(64), 0, st, g, n_rows, q, w, kmean,
-                       page_keys, ld, (int)max_tiles);
+                       page_keys, ld, per);
     return hipGetLastError();
   }
-  const int tiles_per_chunk = PAGED ? 8 : (int)max_tiles;
+  const int tiles_per_chunk = PAGED ? 8 : coarse_chunk((n_rows + R - 1) / R, max_tiles, kCoarseFill, kCoarseMin);
   const int64_t chunks = (max_tiles + tiles_per_chunk - 1) / tiles_per_chunk;
   const dim3 grid((unsigned)((n_rows + R - 1) / R), (unsigned)chunks);
   hipLaunchKernelGGL((coarse_kernel<D, R, PAGED, MINMAX>), grid, dim3(256), 0, st, g, n_rows, q, w, kmean, page_keys,
@@ -1867,14 +1889,26 @@ static hipError_t launch_fine_t(const IndexGeom& g, int64_t n_rows, const uint16
   return hipGetLastError();
 }
 
+// Waves of the fine stage. A launch of n rows has 8 n waves with one row each against 4096 that the GPU
+// holds; two rows per wave only where that still leaves several rounds of them (8192 rows: 595 us with
+// one or two, 650 with eight; 131072 rows 9.09 ms with two, 9.19 with one), and below
+// kFinePartsFill rows the pages of an (XCD, row) are dealt to 2, 4 or 8 waves. With eight rows per wave always,
+// 512 rows of 1024 recalled pages took 1742 us (now 670), 50 rows 1655 (84), 100 rows of 64 pages 150 (26),
+// 2000 rows 276 (181). More parts than that cost more query loads than they fill: 300 rows of 1024 pages
+// 411 us whole, 464 in two parts; 200 rows 309 whole, 283 in two, 312 in four.
+constexpr int64_t kFinePartsFill = 256;
+constexpr int kFineMaxParts = 8;
 template <int D, bool FP8>
 static hipError_t launch_fine_xcd_t(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w,
                                     const void* k, const float* ks, const int32_t* pages, uint32_t* fine_keys,
                                     int64_t ldf, hipStream_t st) {
   if (n_rows == 0) return hipSuccess;
-  const int64_t waves_per_xcd = (n_rows + kFineRowsPerWave - 1) / kFineRowsPerWave;
+  const int rpw = n_rows >= 8192 ? kFineRowsPerWave : 1;
+  int parts = 1;
+  while (parts < kFineMaxParts && n_rows * parts < kFinePartsFill) parts *= 2;
+  const int64_t waves_per_xcd = (n_rows + rpw - 1) / rpw * parts;
   hipLaunchKernelGGL((fine_xcd_kernel<D, FP8>), dim3((unsigned)(waves_per_xcd * 8)), dim3(64), 0, st, g, n_rows, q, w, k, ks,
-                     pages, fine_keys, ldf);
+                     pages, fine_keys, ldf, rpw, parts);
   return hipGetLastError();
 }
 
