@@ -401,7 +401,7 @@ def main():
     ap.add_argument("--attn", default="fused", choices=["fused", "runs", "split"],
                     help="sparse attention as one fused pass over S_t (lsa_sparse_attn), the same pass "
                          "reading S_t from its run encoding (lsa_sparse_attn_runs), or split into "
-                         "the listed part and the contiguous window on two streams, merged by log-sum-exp "
+                         "the listed part and the contiguous window, in one pass "
                          "(lsa_hfa_attn)")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -549,9 +549,9 @@ def main():
                                "k_sparse": w.k_sparse, "k_sink": w.k_sink, "k_swa": w.k_swa,
                                "run_align": w.run_align, "pooling": w.pooling},
                    "attention": {"kind": w.attn, "heads": H, "d_qk": dqk, "d_v": dv,
-                                 "operator": ("split (listed part + window, two streams)" if split_attn else
+                                 "operator": ("split (listed part + contiguous window, one pass)" if split_attn else
                                               "fused, list read as runs" if runs_attn else "fused")}},
-        "roofline": {"kernel": ("lsa_hfa_attn (two mla_attn_kernel parts + attn_combine_kernel)" if split_attn
+        "roofline": {"kernel": ("lsa_hfa_attn (mla_attn_kernel)" if split_attn
                                 else "mla_attn_kernel"),
                      "bound": "hbm", "achieved": attn_gbs, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": attn_gbs / HBM_PEAK_GBS,

@@ -268,20 +268,17 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
 
 /*
  * Split sparse attention of prefill (Sec. 4.1.1, the hybrid operator): the same result as
- * lsa_sparse_attn over S_t, computed as two partial attentions merged by online-softmax
- * (log-sum-exp) rescaling: the listed part of S_t without its sliding window (sink and sparse
- * positions: the first count[r] - min(k_swa, t+1) entries of the ascending list), and the window
- * [t - k_swa + 1, t] read as contiguous cache rows. The two run on two streams (the caller's and a
- * library-owned non-blocking one, default priority, joined by events before the merge), in passes
- * of 16384 rows. MLA latent cache only, contiguous cache only.
+ * lsa_sparse_attn over S_t, where only the part of S_t before its sliding window is read from the list
+ * (sink and sparse positions: the first count[r] - min(k_swa, t+1) entries of the ascending list), and
+ * the window [t - k_swa + 1, t] is taken as contiguous cache rows. One pass over both on the caller's
+ * stream (calls of few rows: in two pieces merged by online-softmax rescaling). MLA latent cache only,
+ * contiguous cache only.
  *   q_start    position t of row 0 (row r is the query at t = q_start + r); q_start + n_rows <=
  *              n_kv_rows
  *   k_swa      the indexer's window size: idx must end with the whole window of each row, as
  *              lsa_index_prefill writes it (rows shorter than the window hold [0, t])
  *   workspace  >= lsa_hfa_attn_workspace_size(p, n_rows) bytes, 256-byte aligned (the partials)
- * Other arguments as lsa_sparse_attn. Calls on one device share the side stream and its two
- * events; the library enqueues one call's whole sequence under a lock, so concurrent calls from
- * several host threads are correct (their work on the side stream runs one call after the other).
+ * Other arguments as lsa_sparse_attn.
  */
 size_t lsa_hfa_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows);
 lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv, int64_t n_kv_rows,

@@ -193,42 +193,29 @@ __device__ __forceinline__ int64_t block_prefix512(int64_t v, int64_t* wtot, int
   return base + inc - v;
 }
 
-// WIN: the window branch of the split attention as a query-tiled kernel (Sec. 4.1.1): a workgroup
-// takes two consecutive query rows t0, t0 + 1 and heads 32 blockIdx.y .. + 31, and walks the
-// contiguous cache rows of the union of their windows, [t0 - k_swa + 1, t0 + 1], once: every tile
-// is loaded once into LDS for both rows. Scorer w4 works on row t0 + (w4 >> 1), heads
-// 32 blockIdx.y .. + 31 and tokens 16 (w4 & 1) .. of every tile, value wave w4 + 4 on both rows,
-// heads 32 blockIdx.y .. + 31 and value columns 128 w4 ..; each row masks the tokens outside its
-// own window.
-// Writes the fp32 partial of split a.part.
-// (Two rows of 64 heads would hold 2 x (73.7 KB of Q operand + 131 KB of fp32 accumulators), 80%
-// of a CU's 512 KB register file, before any operand; tiling 2 rows x 32 heads keeps the 64 query
-// vectors per tile of the list kernel.)
-template <bool SPLIT, bool WIN = false>
+// WINDOWED lists (a.k_swa >= 0, the split attention of Sec. 4.1.1): a row's list is the entries before
+// its window, idx[0 .. count - w), and then the window [t - w + 1, t], w = min(k_swa, t + 1), taken as
+// contiguous positions instead of read from the list; both go through the same tiles, since a 1152-byte
+// row costs the same gathered or contiguous and one pass over them needs no partials and no merge (2048
+// rows at 32K: 680 us, against 846 for a listed and a query-tiled window kernel on two streams and
+// their merge; 37 rows at 60K: 48 against 66 us).
+template <bool SPLIT, bool WINDOWED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void mla_attn_kernel(AttnGeom a) {
-  static_assert(!WIN || SPLIT, "the window kernel writes partials");
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kMlaBufs * kMlaTile + 2 * kMlaPSlot];
-  __shared__ int32_t ids[WIN ? 1 : kMlaIdCap];
+  __shared__ int32_t ids[kMlaIdCap];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i16 = lane & 15, g = lane >> 4;
   const int w4 = wv & 3;  // scorer / value-wave pair
   const bool scorer = wv < 4;
-  // WIN: item = row pair, pair w4 on row 2 item + (w4 >> 1); the second row of a pair past n_rows
-  // (odd count) computes nothing it writes
-  const int64_t item = xcd_band(blockIdx.x, WIN ? (a.n_rows + 1) / 2 : a.n_rows);
-  const int64_t wrow = WIN ? 2 * item + (w4 >> 1) : item;
-  const bool row_ok = wrow < a.n_rows;
-  const int64_t row = row_ok ? wrow : a.n_rows - 1;
-  const int split = SPLIT ? (a.part >= 0 ? a.part : (int)blockIdx.y) : 0;
+  const int64_t row = xcd_band(blockIdx.x, a.n_rows);
+  const int split = SPLIT ? (int)blockIdx.y : 0;
   __shared__ int64_t rtot[8];
   __shared__ int32_t roff[512];   // run form: list position of each thread's first run (clamped)
   __shared__ int4 rq[kRunQueue];  // run form: (start, offset into the run, ids slot, entries)
   __shared__ int rq_n;
   int cnt;
-  if (WIN) {
-    cnt = 0;  // (unused: the window is generated)
-  } else if (a.runs) {  // the list length is the sum of the run lengths (at most k_cap entries are used)
+  if (a.runs) {  // the list length is the sum of the run lengths (at most k_cap entries are used)
     const RunBlock rb = run_block(a, row);
     int64_t mine = 0;
     for (int r0 = rb.b; r0 < rb.e; r0 += 4) {
@@ -245,35 +232,19 @@ void mla_attn_kernel(AttnGeom a) {
     cnt = a.count[row];
     cnt = cnt < 0 ? 0 : (cnt > a.k_cap ? a.k_cap : cnt);
   }
-  int s0 = SPLIT && a.part < 0 ? split * a.split_len : 0;
-  int s1 = SPLIT && a.part < 0 ? (cnt < s0 + a.split_len ? cnt : s0 + a.split_len) : cnt;
-  int64_t win0 = -1;  // first cache row of the window part (contiguous rows, no list)
-  // WIN: this wave's row window [w_lo, w_hi] (empty for a skipped row) and the pair's union
-  int64_t w_lo = 0, w_hi = -1, u_last = -1;
-  if (WIN) {
-    const int64_t t0 = a.q_pos0 + 2 * item;
-    const int64_t t1 = a.q_pos0 + (2 * item + 1 < a.n_rows ? 2 * item + 1 : 2 * item);
-    const int64_t t = a.q_pos0 + row;
-    int c = a.count[row];
-    if (row_ok && c > 0) {  // an empty list (a skipped row) has no window either
-      w_hi = t;
-      w_lo = t - a.k_swa + 1 > 0 ? t - a.k_swa + 1 : 0;
-    }
-    win0 = t0 - a.k_swa + 1 > 0 ? t0 - a.k_swa + 1 : 0;
-    u_last = t1 < a.n_kv_rows - 1 ? t1 : a.n_kv_rows - 1;
-    s0 = 0;
-    s1 = (int)(t1 - win0 + 1);
-  } else if (a.part >= 0) {
+  int n_list = cnt;   // entries read from the list; the others are the window from win0 on
+  int64_t win0 = 0;
+  if constexpr (WINDOWED) {
     const int64_t t = a.q_pos0 + row;
     const int nwin = (int)(a.k_swa < t + 1 ? a.k_swa : t + 1);
-    if (a.part == 0) {
-      s1 = cnt - nwin > 0 ? cnt - nwin : 0;
-    } else {
-      s1 = cnt > 0 ? nwin : 0;  // an empty list (a skipped row) has no window either
-      win0 = t - nwin + 1;
-    }
+    n_list = cnt - nwin > 0 ? cnt - nwin : 0;
+    win0 = t - nwin + 1;
+    cnt = cnt > 0 ? n_list + nwin : 0;  // an empty list (a skipped row) has no window either
   }
+  const int s0 = SPLIT ? split * a.split_len : 0;
+  const int s1 = SPLIT && cnt > s0 + a.split_len ? s0 + a.split_len : cnt;
   const int n = s1 > s0 ? s1 - s0 : 0;
+  const int nl = n_list - s0;  // listed entries from s0 on (n of them unless windowed)
   const int32_t* slots = a.rows ? a.rows + row * a.k_cap + s0 : nullptr;  // list form (unused with runs)
   const uint8_t* kvb = reinterpret_cast<const uint8_t*>(a.kv);
   uint8_t* const pslots = lds + kMlaBufs * kMlaTile;
@@ -283,7 +254,7 @@ void mla_attn_kernel(AttnGeom a) {
   const int pair = w4 >> 1;
   __shared__ float fin[2 * 2 * 64];           // per (token half, pair, local head): reference max and sum
 
-  constexpr int kPass = WIN ? (1 << 30) : kMlaIdCap;  // the window needs no staged list
+  constexpr int kPass = kMlaIdCap;
   // list entries [c0, c0 + nc) -> LDS, validated (-1 = skip; the last tile is padded with -1)
   auto stage = [&](int c0, int nc, int ntiles) {
     if (a.runs && threadIdx.x == 0) rq_n = 0;  // the previous pass's readers passed a barrier since
@@ -333,7 +304,14 @@ void mla_attn_kernel(AttnGeom a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = (int)threadIdx.x + 512 * u;
-        v[u] = i < nc ? (win0 >= 0 ? (int)(win0 + c0 + i) : slots[c0 + i]) : -1;
+        v[u] = i < (WINDOWED && nl - c0 < nc ? nl - c0 : nc) ? slots[c0 + i] : -1;
+      }
+      if constexpr (WINDOWED) {  // entries past the listed ones are the window
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = (int)threadIdx.x + 512 * u;
+          if (i < nc && c0 + i >= nl) v[u] = (int)(win0 + (c0 + i - nl));
+        }
       }
       if (a.page_table) {  // paged cache: position -> cache row through the sequence's page table
         const int32_t* tab = a.page_table + (row / a.rows_per_seq) * a.max_pages;
@@ -359,21 +337,13 @@ void mla_attn_kernel(AttnGeom a) {
     }
     __syncthreads();
   };
-  // cache row of token `tok` of tile `tile` (WIN: contiguous rows; positions past the union re-read
-  // its last row, masked), -1 for a skipped entry
-  auto tile_row = [&](int tile, int tok) -> int {
-    if constexpr (WIN) {
-      const int64_t p = win0 + (int64_t)tile * kMlaT + tok;
-      return (int)(p < u_last ? p : u_last);
-    } else {
-      return ids[tile * kMlaT + tok];
-    }
-  };
+  // cache row of token `tok` of tile `tile`, -1 for a skipped entry
+  auto tile_row = [&](int tile, int tok) -> int { return ids[tile * kMlaT + tok]; };
 
   if (scorer) {
     // scorer w4 takes tokens 16 th .. + 15 of every tile for the 32 heads of its pair
     const int th = w4 & 1;
-    const int hbase = WIN ? 32 * (int)blockIdx.y : 32 * pair;
+    const int hbase = 32 * pair;
     // Q^T as the B operand of S^T = K Q^T: column = head 16 nb + i16, k-step s covers dims 32s + 8g .. +7
     u32x4 qb[2][18];
 #pragma unroll
@@ -393,7 +363,7 @@ void mla_attn_kernel(AttnGeom a) {
     for (int c0 = 0; c0 < n; c0 += kPass) {
       const int nc = n - c0 < kPass ? n - c0 : kPass;
       const int ntiles = (nc + kMlaT - 1) / kMlaT;
-      if constexpr (!WIN) stage(c0, nc, ntiles);
+      stage(c0, nc, ntiles);
       __syncthreads();
       uint32_t cur_off = 0;
       for (int it = 0; it <= ntiles; ++it) {
@@ -405,8 +375,7 @@ void mla_attn_kernel(AttnGeom a) {
         // issued first, so that their LDS round trips overlap the products: this lane's list entry
         // of the tile (softmax mask) and the other token half's reference maxima of tile it - 1
         // (adopted when larger)
-        int idv = 0;
-        if constexpr (!WIN) idv = ids[it * kMlaT + lj];
+        const int idv = ids[it * kMlaT + lj];
         float mp[2] = {-INFINITY, -INFINITY};
         if (it > 0) {
           const uint8_t* pr = pslots + ((it - 1) & 1) * kMlaPSlot + 64 * kMlaPHead + (1 - th) * 256;
@@ -438,13 +407,7 @@ void mla_attn_kernel(AttnGeom a) {
           __builtin_amdgcn_sched_barrier(0);
         }
         // online softmax (base 2); lane holds tokens 16 th + 4g + r of heads 16 nb + i16
-        uint32_t vmask;
-        if constexpr (WIN) {
-          const int64_t p = win0 + (int64_t)it * kMlaT + lj;
-          vmask = (uint32_t)__ballot(p >= w_lo && p <= w_hi);
-        } else {
-          vmask = (uint32_t)__ballot(idv >= 0);
-        }
+        const uint32_t vmask = (uint32_t)__ballot(idv >= 0);
         const uint32_t hmask = (vmask >> (16 * th)) & 0xFFFFu;
         if (hmask != 0xFFFFu) {  // partial or skipped tokens: mask them
 #pragma unroll
@@ -531,7 +494,7 @@ void mla_attn_kernel(AttnGeom a) {
   for (int c0 = 0; c0 < n; c0 += kPass) {
     const int nc = n - c0 < kPass ? n - c0 : kPass;
     const int ntiles = (nc + kMlaT - 1) / kMlaT;
-    if constexpr (!WIN) stage(c0, nc, ntiles);
+    stage(c0, nc, ntiles);
     __syncthreads();
     if (ntiles > 0) issue(tile_row(0, dma_tok), 0);
     int nrow = ntiles > 1 ? tile_row(1, dma_tok) : -1;  // row of this lane's next load, read a tile ahead
@@ -611,8 +574,7 @@ void mla_attn_kernel(AttnGeom a) {
   }
   __syncthreads();  // the scorers' reference maxima and sums
   // accumulator layout: lane l, register r of block 4 hb + c holds dim 128 w4 + 32 c + 8 (r / 4) +
-  // 4 (l / 32) + r % 4 of local head 32 hb + l % 32: in the list kernel head 32 hb + l % 32 of the
-  // row, in the window kernel head 32 blockIdx.y + l % 32 of row 2 item + hb
+  // 4 (l / 32) + r % 4 of head 32 hb + l % 32
   float mfin[2], lt[2];
 #pragma unroll
   for (int hb = 0; hb < 2; ++hb) {
@@ -641,12 +603,7 @@ void mla_attn_kernel(AttnGeom a) {
       }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this wave's staging writes are done)
-  // local head hh = 32 hb + h: head hh of the row, or (WIN) head 32 blockIdx.y + h of row 2 item + hb
-  auto split_index = [&](int hb, int h, int64_t& pi) {
-    const int64_t orow = WIN ? 2 * item + hb : row;
-    pi = (orow * a.n_split + split) * 64 + (WIN ? 32 * (int)blockIdx.y : 32 * hb) + h;
-    return orow < a.n_rows;  // WIN: the second row of an odd count is not written
-  };
+  const int64_t p0 = SPLIT ? (row * a.n_split + split) * 64 : 0;  // this piece's partial of head 0
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int hh = 4 * k + (lane >> 4);
@@ -654,8 +611,7 @@ void mla_attn_kernel(AttnGeom a) {
     if (!SPLIT) {
       *reinterpret_cast<u32x4*>(a.out + (row * 64 + hh) * 512 + 128 * w4 + 8 * (lane & 15)) = v;
     } else {
-      int64_t pi;
-      if (split_index(hh >> 5, hh & 31, pi)) *reinterpret_cast<u32x4*>(a.part_o + pi * 512 + 128 * w4 + 8 * (lane & 15)) = v;
+      *reinterpret_cast<u32x4*>(a.part_o + (p0 + hh) * 512 + 128 * w4 + 8 * (lane & 15)) = v;
     }
   }
   if (w4 == 0 && lane < 32) {
@@ -664,11 +620,8 @@ void mla_attn_kernel(AttnGeom a) {
       if (!SPLIT) {
         if (a.lse) a.lse[row * 64 + 32 * hb + oj] = lt[hb] > 0.f ? (mfin[hb] + __log2f(lt[hb])) * kLn2 : -INFINITY;
       } else {
-        int64_t pi;
-        if (split_index(hb, oj, pi)) {
-          a.part_ml[pi * 2] = mfin[hb];
-          a.part_ml[pi * 2 + 1] = lt[hb];
-        }
+        a.part_ml[(p0 + 32 * hb + oj) * 2] = mfin[hb];
+        a.part_ml[(p0 + 32 * hb + oj) * 2 + 1] = lt[hb];
       }
     }
   }
@@ -939,7 +892,8 @@ __global__ __launch_bounds__(256) void translate_rows_kernel(const int32_t* __re
 // ============================================================================ host launchers
 template <bool SPLIT>
 static void launch_mla_kernel(dim3 grid, const AttnGeom& a, hipStream_t st) {
-  hipLaunchKernelGGL((mla_attn_kernel<SPLIT>), grid, dim3(512), 0, st, a);
+  if (a.k_swa >= 0) hipLaunchKernelGGL((mla_attn_kernel<SPLIT, true>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((mla_attn_kernel<SPLIT, false>), grid, dim3(512), 0, st, a);
 }
 
 hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st) {
@@ -951,19 +905,6 @@ hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st) {
     return launch_attn_combine(a, st);
   }
   launch_mla_kernel<false>(dim3((unsigned)a.n_rows), a, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_mla_attn_part(const AttnGeom& a, hipStream_t st) {
-  if (a.n_rows == 0) return hipSuccess;
-  launch_mla_kernel<true>(dim3((unsigned)a.n_rows), a, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_mla_attn_window(const AttnGeom& a, hipStream_t st) {
-  if (a.n_rows == 0) return hipSuccess;
-  hipLaunchKernelGGL((mla_attn_kernel<true, true>), dim3((unsigned)((a.n_rows + 1) / 2), 2u), dim3(512), 0,
-                     st, a);
   return hipGetLastError();
 }
 

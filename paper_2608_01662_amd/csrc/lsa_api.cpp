@@ -215,21 +215,17 @@ struct AttnPlan {
 // workgroups, 0.166 ms at 2048).
 constexpr int64_t kSplitTarget = 256;
 
-AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+// `ns` pieces per row, of 32-entry multiples (fewer where the list has fewer tiles).
+AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, int64_t ns) {
   AttnPlan pl{};
   pl.n_split = 1;
   pl.split_len = k_cap;
   const bool mla = p->latent != 0;
-  if (mla && n_rows > 0 && n_rows < kSplitTarget) {
-    // too few rows to fill 256 CUs: split every row's list into 32-token-aligned pieces
-    int64_t want = cdiv(kSplitTarget, n_rows);
-    int64_t max_split = cdiv(k_cap, 32);
-    int64_t ns = want < max_split ? want : max_split;
-    if (ns > 1) {
-      int64_t len = round_up((size_t)cdiv(k_cap, ns), 32);
-      pl.split_len = (int)len;
-      pl.n_split = (int)cdiv(k_cap, len);
-    }
+  if (ns > cdiv(k_cap, 32)) ns = cdiv(k_cap, 32);
+  if (ns > 1) {
+    const int64_t len = (int64_t)round_up((size_t)cdiv(k_cap, ns), 32);
+    pl.split_len = (int)len;
+    pl.n_split = (int)cdiv(k_cap, len);
   }
   size_t off = 0;
   pl.off_rows = off;  // translated cache rows (paged MQA; the MLA kernel translates as it stages)
@@ -240,6 +236,12 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int3
   if (pl.n_split > 1) off += round_up((size_t)n_rows * pl.n_split * p->n_heads * 2 * 4, 256);
   pl.total = off;
   return pl;
+}
+
+AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+  // too few rows to fill 256 CUs: split every row's list into 32-token-aligned pieces
+  const bool few = p->latent != 0 && n_rows > 0 && n_rows < kSplitTarget;
+  return plan_pieces(p, n_rows, k_cap, paged, few ? cdiv(kSplitTarget, n_rows) : 1);
 }
 
 lsa_status check_attn_params(const lsa_attn_params* p) {
@@ -557,7 +559,7 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   a.n_split = pl.n_split;
   a.split_len = pl.split_len;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
-  a.part = -1;  // the whole index list
+  a.k_swa = -1;  // plain lists
   if (paged && mla) {  // the MLA kernel translates positions while it stages each list
     a.page_table = page_table;
     a.max_pages = max_pages;
@@ -649,7 +651,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
   a.n_split = pl.n_split;
   a.split_len = pl.split_len;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
-  a.part = -1;
+  a.k_swa = -1;  // plain lists
   if (pl.n_split > 1) {
     a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
     a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
@@ -660,52 +662,15 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
 }
 
 // ---------------------------------------------------------------- split attention (HFA)
-// Rows per pass of lsa_hfa_attn: the two partials of a row (bf16 values, fp32 maximum and sum per
-// head) take 2 * 64 * (512 * 2 + 2 * 4) bytes.
-constexpr int64_t kHfaRowsPerPass = 16384;
-
-static int64_t hfa_rows_per_pass(int64_t n_rows) { return n_rows < kHfaRowsPerPass ? n_rows : kHfaRowsPerPass; }
+// Rows that the workspace of lsa_hfa_attn covers with two partials each (bf16 values, fp32 maximum and
+// sum per head).
+constexpr int64_t kHfaRows = 16384;
 
 size_t lsa_hfa_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || p->latent == 0) return 0;
-  const size_t r = (size_t)hfa_rows_per_pass(n_rows);
+  const size_t r = (size_t)(n_rows < kHfaRows ? n_rows : kHfaRows);
   return round_up(r * 2 * 64 * 512 * 2, 256) + round_up(r * 2 * 64 * 2 * 4, 256);
 }
-
-namespace {
-// The second stream of the split attention and the two events that fork and join it, one set
-// per device, created on first use (default priority, non-blocking).
-struct HfaStreams {
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-};
-std::mutex g_hfa_mu;       // creation of the per-device streams and events
-std::mutex g_hfa_call_mu;  // one call's enqueue sequence at a time
-HfaStreams g_hfa[64];
-
-hipError_t hfa_streams(HfaStreams** out) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lk(g_hfa_mu);
-  HfaStreams& h = g_hfa[dev];
-  if (h.side == nullptr) {  // all three objects, or none (a failed call leaves nothing half-made)
-    HfaStreams n;
-    if ((e = hipStreamCreateWithFlags(&n.side, hipStreamNonBlocking)) == hipSuccess &&
-        (e = hipEventCreateWithFlags(&n.fork, hipEventDisableTiming)) == hipSuccess &&
-        (e = hipEventCreateWithFlags(&n.join, hipEventDisableTiming)) == hipSuccess) {
-      h = n;
-    } else {
-      if (n.fork) (void)hipEventDestroy(n.fork);
-      if (n.side) (void)hipStreamDestroy(n.side);
-      return e;
-    }
-  }
-  *out = &h;
-  return hipSuccess;
-}
-}  // namespace
 
 lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv, int64_t n_kv_rows,
                         const int32_t* idx, const int32_t* count, int32_t k_cap, int64_t q_start, int32_t k_swa,
@@ -734,50 +699,32 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
 
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  HfaStreams* hs = nullptr;
-  hipError_t e = hfa_streams(&hs);
-  if (e != hipSuccess) return hip_fail(e, "split attention streams");
-  // the side stream and the fork/join events are shared by every call on this device: enqueue a
-  // whole call's record / wait / launch sequence under the lock, so that the side stream never
-  // interleaves the parts of two calls and each part waits on its own call's fork
-  std::lock_guard<std::mutex> call_lock(g_hfa_call_mu);
-  const int64_t rpp = hfa_rows_per_pass(n_rows);
+  // the lists with their windows as contiguous rows, in as many pieces as the workspace has partials
+  const int32_t cap = k_cap > k_swa ? k_cap : k_swa;  // entries a row can have
+  AttnPlan pl = plan_attn(p, n_rows, cap, 0);
+  if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 2);  // (two per row always fit)
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  uint16_t* part_o = reinterpret_cast<uint16_t*>(ws);
-  float* part_ml = reinterpret_cast<float*>(ws + round_up((size_t)rpp * 2 * 64 * 512 * 2, 256));
-  for (int64_t r0 = 0; r0 < n_rows; r0 += rpp) {
-    const int64_t nr = n_rows - r0 < rpp ? n_rows - r0 : rpp;
-    lsa::AttnGeom a{};
-    a.q = static_cast<const uint16_t*>(q) + r0 * 64 * 576;
-    a.kv = static_cast<const uint16_t*>(kv);
-    a.n_kv_rows = n_kv_rows;
-    a.rows = idx + r0 * k_cap;
-    a.count = count + r0;
-    a.k_cap = k_cap;
-    a.out = static_cast<uint16_t*>(out) + r0 * 64 * 512;
-    a.lse = lse ? lse + r0 * 64 : nullptr;
-    a.part_o = part_o;
-    a.part_ml = part_ml;
-    a.n_rows = nr;
-    a.n_split = 2;
-    a.split_len = k_cap;
-    a.scale_log2 = p->sm_scale * 1.4426950408889634f;
-    a.k_swa = k_swa;
-    a.q_pos0 = q_start + r0;
-    // the listed non-window part on the caller's stream, the window on the side stream, then the
-    // log-sum-exp merge once both partials exist (each pass reuses the partial buffers, which the
-    // stream order of the merge and the next pass's first kernel protects)
-    if ((e = hipEventRecord(hs->fork, st)) != hipSuccess) return hip_fail(e, "split attention fork");
-    if ((e = hipStreamWaitEvent(hs->side, hs->fork, 0)) != hipSuccess) return hip_fail(e, "split attention fork");
-    a.part = 0;
-    if ((e = lsa::launch_mla_attn_part(a, st)) != hipSuccess) return hip_fail(e, "split attention (listed part)");
-    a.part = 1;
-    if ((e = lsa::launch_mla_attn_window(a, hs->side)) != hipSuccess) return hip_fail(e, "split attention (window)");
-    if ((e = hipEventRecord(hs->join, hs->side)) != hipSuccess) return hip_fail(e, "split attention join");
-    if ((e = hipStreamWaitEvent(st, hs->join, 0)) != hipSuccess) return hip_fail(e, "split attention join");
-    if ((e = lsa::launch_attn_combine(a, st)) != hipSuccess) return hip_fail(e, "split attention merge");
+  lsa::AttnGeom a{};
+  a.q = static_cast<const uint16_t*>(q);
+  a.kv = static_cast<const uint16_t*>(kv);
+  a.n_kv_rows = n_kv_rows;
+  a.rows = idx;
+  a.count = count;
+  a.k_cap = k_cap;
+  a.out = static_cast<uint16_t*>(out);
+  a.lse = lse;
+  a.n_rows = n_rows;
+  a.n_split = pl.n_split;
+  a.split_len = pl.split_len;
+  a.scale_log2 = p->sm_scale * 1.4426950408889634f;
+  a.k_swa = k_swa;
+  a.q_pos0 = q_start;
+  if (pl.n_split > 1) {
+    a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
+    a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
   }
+  const hipError_t e = lsa::launch_mla_attn(a, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail(e, "split attention");
   return LSA_OK;
 }
 

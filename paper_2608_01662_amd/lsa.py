@@ -454,13 +454,15 @@ def hfa_workspace_size(prm: AttnParams, n_rows: int) -> int:
 def hfa_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, idx: torch.Tensor, count: torch.Tensor,
              q_start: int, k_swa: int, out: torch.Tensor | None = None, lse: torch.Tensor | bool | None = True,
              workspace: torch.Tensor | None = None):
-    """Split attention (lsa_hfa_attn): listed non-window part and contiguous window on two streams,
-    merged by log-sum-exp rescaling. Returns (out, lse or None) as sparse_attn."""
+    """Split attention (lsa_hfa_attn): the listed non-window part and the contiguous window in one pass.
+    Returns (out, lse or None) as sparse_attn."""
     n_rows, n_kv_rows, out, lse = _attn_io(prm, q, kv, out, lse, False)
     _need("idx", idx, _I32, (n_rows, None), q.device)
     k_cap = idx.shape[1]
     _need("count", count, _I32, (n_rows,), q.device)
-    ws, wsb = _workspace(hfa_workspace_size(prm, n_rows), q.device, workspace)
+    # (with the list form's workspace a call of few rows is split over the GPU as that one is)
+    ws, wsb = _workspace(max(hfa_workspace_size(prm, n_rows), attn_workspace_size(prm, n_rows, max(k_cap, k_swa), False)),
+                         q.device, workspace)
     _check(lib().lsa_hfa_attn(ctypes.byref(prm.c()), n_rows, _p(q), _p(kv), n_kv_rows, _p(idx), _p(count), k_cap,
                               q_start, k_swa, _p(out), _p(lse), _p(ws), wsb, _stream(q.device)), "lsa_hfa_attn")
     return out, lse

@@ -559,6 +559,32 @@ def test_split_attention_parity(w, q0, n_q):
     print(w.name, q0, n_q, "worst vs oracle", worst, "max |hfa - fused|", float(np.max(np.abs(o[keep] - of[keep]))))
 
 
+@pytest.mark.parametrize("q0,n_q,ws_rows", [(0, 1, 1), (900, 1, 1), (0, 40, 40), (501, 5, 5), (501, 5, None), (130, 129, None), (100, 257, 257)])
+def test_split_attention_few_rows(q0, n_q, ws_rows):
+    """Split attention of few rows: whole lists and lists cut into pieces (two with the smallest workspace,
+    more with the list form's), pieces that start inside the window, rows shorter than the window, and a
+    row whose count is smaller than its window (nothing is listed, the window is attended whole), every
+    row against the oracle."""
+    w = W.SMALL_MLA
+    rows = list(range(q0, q0 + n_q))
+    idx, cnt = _oracle_index(w, rows, w.seq_len)
+    a = _attn_inputs(w, 0, w.seq_len, w.seq_len)
+    cut = cnt.copy()
+    if n_q > 4:
+        cut[3] = 3
+    ws = None
+    if ws_rows is not None:
+        ws = torch.empty(lsa.hfa_workspace_size(w.attn_params(), ws_rows), dtype=torch.uint8, device="cuda")
+    o, l = lsa.hfa_attn(w.attn_params(), P.bf16_dev(a["q"][rows]), P.bf16_dev(a["kv"]), P.to_dev(idx), P.to_dev(cut), q0,
+                        w.k_swa, workspace=ws)
+    o, l = o.float().cpu().numpy(), l.cpu().numpy()
+    if n_q > 4:
+        t = rows[3]
+        win = np.arange(max(0, t - w.k_swa + 1), t + 1, dtype=np.int32)
+        idx[3, :win.size], cnt[3] = win, win.size
+    _check_rows(w, a, rows, idx, cnt, o, l)
+
+
 def test_binding_rejects_mismatched_tensors():
     """The C ABI sees bare pointers, so the binding checks every tensor against the sizes it passes
     (dtype, device, contiguity, shape) and raises before anything is launched."""
