@@ -216,7 +216,9 @@ typedef struct lsa_attn_params {
   float sm_scale;  /* softmax scale applied to q . k                                           */
 } lsa_attn_params;
 
-/* Workspace bytes for lsa_sparse_attn (non-zero only for split calls and paged MQA calls). */
+/* Workspace bytes for lsa_sparse_attn: non-zero for paged MQA calls and for MLA calls whose rows do not
+ * fill the GPU's 256 CUs evenly, where rows are cut into pieces. (A call of 256 rows or more that brings
+ * less takes every row whole.) */
 size_t lsa_sparse_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap,
                                       int32_t paged);
 

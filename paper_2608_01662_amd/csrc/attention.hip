@@ -15,6 +15,9 @@
 #include "device.hpp"
 #include "launch.hpp"
 
+// (The list staging unrolls loops with uniform early exits, which the unroller then reports.)
+#pragma clang diagnostic ignored "-Wpass-failed"
+
 namespace lsa {
 
 constexpr float kLn2 = 0.69314718055994530942f;
@@ -208,8 +211,17 @@ void mla_attn_kernel(AttnGeom a) {
   const int i16 = lane & 15, g = lane >> 4;
   const int w4 = wv & 3;  // scorer / value-wave pair
   const bool scorer = wv < 4;
-  const int64_t row = xcd_band(blockIdx.x, a.n_rows);
-  const int split = SPLIT ? (int)blockIdx.y : 0;
+  // SPLIT: the first n_whole workgroups take whole rows, the others one piece of a row's list each
+  const bool whole = !SPLIT || blockIdx.x < a.n_whole;
+  int64_t row;
+  int split = 0;
+  if (whole) {
+    row = xcd_band(blockIdx.x, SPLIT ? a.n_whole : a.n_rows);
+  } else {
+    const uint32_t pb = blockIdx.x - (uint32_t)a.n_whole, rem = (uint32_t)(a.n_rows - a.n_whole);
+    split = (int)(pb / rem);
+    row = a.n_whole + xcd_band(pb % rem, rem);
+  }
   __shared__ int64_t rtot[8];
   __shared__ int32_t roff[512];   // run form: list position of each thread's first run (clamped)
   __shared__ int4 rq[kRunQueue];  // run form: (start, offset into the run, ids slot, entries)
@@ -242,8 +254,8 @@ void mla_attn_kernel(AttnGeom a) {
     cnt = cnt > 0 ? n_list + nwin : 0;  // an empty list (a skipped row) has no window either
   }
   const int s0 = SPLIT ? split * a.split_len : 0;
-  const int s1 = SPLIT && cnt > s0 + a.split_len ? s0 + a.split_len : cnt;
-  const int n = s1 > s0 ? s1 - s0 : 0;
+  const int s1 = !whole && cnt - s0 > a.split_len ? s0 + a.split_len : cnt;
+  const int n = __builtin_amdgcn_readfirstlane(s1 > s0 ? s1 - s0 : 0);
   const int nl = n_list - s0;  // listed entries from s0 on (n of them unless windowed)
   const int32_t* slots = a.rows ? a.rows + row * a.k_cap + s0 : nullptr;  // list form (unused with runs)
   const uint8_t* kvb = reinterpret_cast<const uint8_t*>(a.kv);
@@ -299,19 +311,22 @@ void mla_attn_kernel(AttnGeom a) {
         }
       }
     } else {
+      // 512 entries per step; steps past the list are skipped by the whole block (the breaks: with
+      // predicated steps instead, or eight steps per pass, the call of 8192 rows takes 0.5 to 0.8%
+      // longer), lanes past it re-read its last entry, so the loads issue back to back
       constexpr int U = kMlaIdCap / 512;
       int v[U];
+      const int nlc = WINDOWED ? (nl - c0 < nc ? nl - c0 : nc) : nc;  // listed entries of this chunk
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = (int)threadIdx.x + 512 * u;
-        v[u] = i < (WINDOWED && nl - c0 < nc ? nl - c0 : nc) ? slots[c0 + i] : -1;
+        v[u] = -1;
+        if (512 * u < nlc) v[u] = slots[c0 + (i < nlc ? i : nlc - 1)];
       }
-      if constexpr (WINDOWED) {  // entries past the listed ones are the window
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = (int)threadIdx.x + 512 * u;
-          if (i < nc && c0 + i >= nl) v[u] = (int)(win0 + (c0 + i - nl));
-        }
+      for (int u = 0; u < U; ++u) {
+        const int i = (int)threadIdx.x + 512 * u;
+        if (i >= nlc) v[u] = WINDOWED && i < nc ? (int)(win0 + (c0 + i - nl)) : -1;  // the window, or padding
       }
       if (a.page_table) {  // paged cache: position -> cache row through the sequence's page table
         const int32_t* tab = a.page_table + (row / a.rows_per_seq) * a.max_pages;
@@ -320,6 +335,7 @@ void mla_attn_kernel(AttnGeom a) {
         const int lg = __ffs(kvp) - 1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+          if (512 * u >= nc) break;
           const int pos = v[u];
           if (pos >= 0) {
             const int pg = p2 ? pos >> lg : pos / kvp;
@@ -332,6 +348,7 @@ void mla_attn_kernel(AttnGeom a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = (int)threadIdx.x + 512 * u;
+        if (512 * u >= ntiles * kMlaT) break;
         if (i < ntiles * kMlaT) ids[i] = (v[u] >= 0 && (int64_t)v[u] < a.n_kv_rows) ? v[u] : -1;
       }
     }
@@ -584,6 +601,34 @@ void mla_attn_kernel(AttnGeom a) {
     mfin[hb] = fmaxf(ma, mb);
     lt[hb] = (ma == mfin[hb] ? la : la * fast_exp2(ma - mfin[hb])) + (mb == mfin[hb] ? lb : lb * fast_exp2(mb - mfin[hb]));
   }
+  const int64_t p0 = SPLIT ? ((row - a.n_whole) * a.n_split + split) * 64 : 0;  // this piece's partial of head 0
+  if (w4 == 0 && lane < 32) {
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      if (whole) {
+        if (a.lse) a.lse[row * 64 + 32 * hb + oj] = lt[hb] > 0.f ? (mfin[hb] + __log2f(lt[hb])) * kLn2 : -INFINITY;
+      } else {
+        a.part_ml[(p0 + 32 * hb + oj) * 2] = mfin[hb];
+        a.part_ml[(p0 + 32 * hb + oj) * 2 + 1] = lt[hb];
+      }
+    }
+  }
+  if (SPLIT && !whole && a.part_f32) {  // fp32 partials straight from the accumulators
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      const float inv = lt[hb] > 0.f ? 1.f / lt[hb] : 0.f;
+      float* dst = a.part_f32 + (p0 + 32 * hb + oj) * 512 + 128 * w4 + 4 * (lane >> 5);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& ob = o[4 * hb + c];
+          *reinterpret_cast<f32x4*>(dst + 32 * c + 8 * q) =
+              f32x4{ob[4 * q] * inv, ob[4 * q + 1] * inv, ob[4 * q + 2] * inv, ob[4 * q + 3] * inv};
+        }
+    }
+    return;
+  }
   // The normalised O of this wave (64 heads x 128 value columns, bf16) is staged head-major in the
   // tile buffers, idle since the barrier above (272 bytes per head: 256 + 16 of padding), and
   // written as 256-byte pieces of the head rows, four per store instruction: to the output, or
@@ -603,26 +648,14 @@ void mla_attn_kernel(AttnGeom a) {
       }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this wave's staging writes are done)
-  const int64_t p0 = SPLIT ? (row * a.n_split + split) * 64 : 0;  // this piece's partial of head 0
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int hh = 4 * k + (lane >> 4);
     const u32x4 v = *reinterpret_cast<const u32x4*>(ost + hh * 272 + 16 * (lane & 15));
-    if (!SPLIT) {
+    if (whole) {
       *reinterpret_cast<u32x4*>(a.out + (row * 64 + hh) * 512 + 128 * w4 + 8 * (lane & 15)) = v;
     } else {
       *reinterpret_cast<u32x4*>(a.part_o + (p0 + hh) * 512 + 128 * w4 + 8 * (lane & 15)) = v;
-    }
-  }
-  if (w4 == 0 && lane < 32) {
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      if (!SPLIT) {
-        if (a.lse) a.lse[row * 64 + 32 * hb + oj] = lt[hb] > 0.f ? (mfin[hb] + __log2f(lt[hb])) * kLn2 : -INFINITY;
-      } else {
-        a.part_ml[(p0 + 32 * hb + oj) * 2] = mfin[hb];
-        a.part_ml[(p0 + 32 * hb + oj) * 2 + 1] = lt[hb];
-      }
     }
   }
 }
@@ -738,8 +771,8 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
 
 // ============================================================================ split combine
 // Log-sum-exp merge of the per-split partial results (the same rescaling the paper uses to
-// merge partial attentions, Sec. 4.1.1 and App. B): each partial is stored in bf16, normalised by
-// its own sum l_s, and weighted by l_s 2^(m_s - M) / sum_s l_s 2^(m_s - M). Grid (n_rows, 64 heads).
+// merge partial attentions, Sec. 4.1.1 and App. B): each partial is stored in bf16 or fp32, normalised by
+// its own sum l_s, and weighted by l_s 2^(m_s - M) / sum_s l_s 2^(m_s - M). Grid (rows cut into pieces, 64 heads).
 //
 // Two kernels by the number of splits ns. What bounds both is the chain of dependent round trips to
 // partials that other XCDs have just written, not their bytes. Up to kCombineRegs splits (32 rows and
@@ -752,6 +785,22 @@ __device__ __forceinline__ f32x4 bf16x4_f32(u32x2 v) {
   return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                __uint_as_float(v.y & 0xFFFF0000u)};
 }
+// Four values of a partial, bf16 or (F32) fp32.
+template <bool F32>
+struct Part4;
+template <>
+struct Part4<false> {
+  u32x2 v = {0u, 0u};
+  __device__ void load(const AttnGeom& a, int64_t i) { v = *reinterpret_cast<const u32x2*>(a.part_o + i); }
+  __device__ f32x4 f32() const { return bf16x4_f32(v); }
+};
+template <>
+struct Part4<true> {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  __device__ void load(const AttnGeom& a, int64_t i) { v = *reinterpret_cast<const f32x4*>(a.part_f32 + i); }
+  __device__ f32x4 f32() const { return v; }
+};
+template <bool F32>
 __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
   constexpr int H = 64, d_v = 512;
   const int64_t row = blockIdx.x;
@@ -761,17 +810,16 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
   // every split's maximum, sum and four values of this thread requested together (one round trip)
   const int d = (int)threadIdx.x * 4;
   float ms[kCombineRegs], ls[kCombineRegs];
-  u32x2 pv[kCombineRegs];
+  Part4<F32> pv[kCombineRegs];
 #pragma unroll
   for (int s = 0; s < kCombineRegs; ++s) {
     ms[s] = -INFINITY;
     ls[s] = 0.f;
-    pv[s] = u32x2{0u, 0u};
     if (s < ns) {
       const int64_t pi = pidx(s);
       ms[s] = a.part_ml[pi * 2];
       ls[s] = a.part_ml[pi * 2 + 1];
-      pv[s] = *reinterpret_cast<const u32x2*>(a.part_o + pi * d_v + d);
+      pv[s].load(a, pi * d_v + d);
     }
   }
   float M = -INFINITY;
@@ -785,16 +833,18 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
     // the partial is normalised by its own sum ls: weight it back by ls 2^(m_s - M)
     const float wgt = ls[s] * fast_exp2(ms[s] - M);
     L += wgt;
-    acc += wgt * bf16x4_f32(pv[s]);
+    acc += wgt * pv[s].f32();
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
   const u32x2 v = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
-  *reinterpret_cast<u32x2*>(a.out + (row * H + head) * d_v + d) = v;
-  if (a.lse && threadIdx.x == 0) a.lse[row * H + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
+  const int64_t orow = (a.n_whole + row) * H + head;
+  *reinterpret_cast<u32x2*>(a.out + orow * d_v + d) = v;
+  if (a.lse && threadIdx.x == 0) a.lse[orow] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
 
 // More than kCombineRegs splits: wave w of eight sums splits w, w + 8, .. (lane l: dims 8 l .. + 7).
 constexpr int kCombineDeep = 8;  // partials of 16 bytes per lane a wave requests together
+template <bool F32>
 __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
   constexpr int H = 64, d_v = 512;
   __shared__ __attribute__((aligned(16))) float sum[8][d_v];
@@ -804,12 +854,16 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
   const int ns = a.n_split;
   const int64_t p0 = row * ns * H + head;  // split s: p0 + s H
   // the first partials are requested before their weights are known
-  u32x4 pv[kCombineDeep];
+  Part4<F32> pv[kCombineDeep][2];
   auto request = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < kCombineDeep; ++u) {
       const int s = s0 + 8 * u;
-      pv[u] = s < ns ? *reinterpret_cast<const u32x4*>(a.part_o + (p0 + (int64_t)s * H) * d_v + 8 * lane) : u32x4{0, 0, 0, 0};
+      const int64_t i = (p0 + (int64_t)s * H) * d_v + 8 * lane;
+      if (s < ns) {  // (a later round's stale values past ns have weight 0)
+        pv[u][0].load(a, i);
+        pv[u][1].load(a, i + 4);
+      }
     }
   };
   request(wv);
@@ -824,7 +878,8 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
     M = fmaxf(M, fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
   }
   M = wave_max(M);
-  float acc[8] = {}, L = 0.f;
+  f32x4 acc[2] = {};
+  float L = 0.f;
   for (int s0 = wv; s0 < ns; s0 += 8 * kCombineDeep) {
     if (s0 != wv) request(s0);
     float ms[kCombineDeep], ls[kCombineDeep];
@@ -840,29 +895,27 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
       if (!(ls[u] > 0.f)) continue;  // (an empty piece of the list)
       const float wgt = ls[u] * fast_exp2(ms[u] - M);
       L += wgt;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[2 * k] += wgt * __uint_as_float(pv[u][k] << 16);
-        acc[2 * k + 1] += wgt * __uint_as_float(pv[u][k] & 0xFFFF0000u);
-      }
+      acc[0] += wgt * pv[u][0].f32();
+      acc[1] += wgt * pv[u][1].f32();
     }
   }
-  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane]) = f32x4{acc[0], acc[1], acc[2], acc[3]};
-  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane + 4]) = f32x4{acc[4], acc[5], acc[6], acc[7]};
+  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane]) = acc[0];
+  *reinterpret_cast<f32x4*>(&sum[wv][8 * lane + 4]) = acc[1];
   if (lane == 0) wl[wv] = L;
   __syncthreads();
   L = 0.f;
 #pragma unroll
   for (int x = 0; x < 8; ++x) L += wl[x];
   const float inv = L > 0.f ? 1.f / L : 0.f;
+  const int64_t orow = (a.n_whole + row) * H + head;
   if (threadIdx.x < d_v / 2) {
     const int d = 2 * (int)threadIdx.x;
     f32x2 o = {};
 #pragma unroll
     for (int x = 0; x < 8; ++x) o += *reinterpret_cast<const f32x2*>(&sum[x][d]);
-    *reinterpret_cast<uint32_t*>(a.out + (row * H + head) * d_v + d) = pack_bf16x2(o[0] * inv, o[1] * inv);
+    *reinterpret_cast<uint32_t*>(a.out + orow * d_v + d) = pack_bf16x2(o[0] * inv, o[1] * inv);
   }
-  if (a.lse && threadIdx.x == 0) a.lse[row * H + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
+  if (a.lse && threadIdx.x == 0) a.lse[orow] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
 
 // ============================================================================ paged position -> cache row
@@ -899,7 +952,7 @@ static void launch_mla_kernel(dim3 grid, const AttnGeom& a, hipStream_t st) {
 hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st) {
   if (a.n_rows == 0) return hipSuccess;
   if (a.n_split > 1) {
-    launch_mla_kernel<true>(dim3((unsigned)a.n_rows, (unsigned)a.n_split), a, st);
+    launch_mla_kernel<true>(dim3((unsigned)(a.n_whole + (a.n_rows - a.n_whole) * a.n_split)), a, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_attn_combine(a, st);
@@ -915,11 +968,11 @@ hipError_t launch_mqa_attn(const AttnGeom& a, hipStream_t st) {
 }
 
 hipError_t launch_attn_combine(const AttnGeom& a, hipStream_t st) {
-  const dim3 grid((unsigned)a.n_rows, 64u);
-  if (a.n_split <= kCombineRegs)
-    hipLaunchKernelGGL(attn_combine_kernel, grid, dim3(128), 0, st, a);
-  else
-    hipLaunchKernelGGL(attn_combine_deep_kernel, grid, dim3(512), 0, st, a);
+  const dim3 grid((unsigned)(a.n_rows - a.n_whole), 64u);
+  const bool deep = a.n_split > kCombineRegs;
+  auto kernel = a.part_f32 ? (deep ? attn_combine_deep_kernel<true> : attn_combine_kernel<true>)
+                           : (deep ? attn_combine_deep_kernel<false> : attn_combine_kernel<false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(deep ? 512 : 128), 0, st, a);
   return hipGetLastError();
 }
 

@@ -70,10 +70,12 @@ struct AttnGeom {
   int k_cap;
   uint16_t* out;           // [n_rows, H, d_v]
   float* lse;              // [n_rows, H] or nullptr
-  uint16_t* part_o;        // split partials, each normalised by its own sum, bf16 [n_rows, n_split, H, d_v]
-  float* part_ml;          // [n_rows, n_split, H, 2]
+  uint16_t* part_o;        // split partials, each normalised by its own sum, bf16 [n_rows - n_whole, n_split, H, d_v]
+  float* part_f32;         // the same in fp32 (then part_o is unused), or nullptr
+  float* part_ml;          // [n_rows - n_whole, n_split, H, 2]
   int64_t n_rows;
-  int n_split, split_len;  // slots per split (multiple of the tile)
+  int64_t n_whole;         // with n_split > 1: rows taken whole; the later ones are cut into pieces
+  int n_split, split_len;  // pieces per row, list entries per piece (multiple of the tile)
   float scale_log2;        // sm_scale * log2(e)
   // Windowed lists (MLA list form; k_swa < 0: plain lists): row r's list is its entries before the
   // window and then the contiguous positions [t - w + 1, t], t = q_pos0 + r, w = min(k_swa, t + 1).

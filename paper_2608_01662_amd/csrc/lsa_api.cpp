@@ -205,18 +205,18 @@ lsa_status run_index(const lsa_index_params* p, const lsa::IndexGeom& g, int64_t
 
 // ---------------------------------------------------------------- attention planning
 struct AttnPlan {
+  int64_t n_whole;  // rows taken whole (with n_split > 1; the later ones are cut into n_split pieces)
   int n_split, split_len;
+  bool f32;         // partials in fp32
   size_t off_rows, off_po, off_ml, total;
 };
 
-// Workgroups a split attention call aims for: one per CU (the MLA kernel's LDS admits one per CU).
-// Every split re-loads its row's 73 KB of Q and writes 128 KB of fp32 partials, so more, shorter
-// splits cost more than they add in parallelism (64-sequence decode: 0.067 ms per layer at 256
-// workgroups, 0.166 ms at 2048).
-constexpr int64_t kSplitTarget = 256;
+// Workgroups the GPU runs at once: one per CU (the MLA kernel's LDS admits one per CU).
+constexpr int64_t kCus = 256;
 
-// `ns` pieces per row, of 32-entry multiples (fewer where the list has fewer tiles).
-AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, int64_t ns) {
+// Rows from n_whole on in `ns` pieces each, of 32-entry multiples (fewer where the list has fewer tiles).
+AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, int64_t n_whole,
+                     int64_t ns, bool f32) {
   AttnPlan pl{};
   pl.n_split = 1;
   pl.split_len = k_cap;
@@ -227,21 +227,79 @@ AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, in
     pl.split_len = (int)len;
     pl.n_split = (int)cdiv(k_cap, len);
   }
+  pl.n_whole = pl.n_split > 1 ? n_whole : 0;
+  pl.f32 = f32;
   size_t off = 0;
   pl.off_rows = off;  // translated cache rows (paged MQA; the MLA kernel translates as it stages)
   if (paged && !mla) off += round_up((size_t)n_rows * k_cap * 4, 256);
+  const size_t pieces = pl.n_split > 1 ? (size_t)(n_rows - pl.n_whole) * pl.n_split : 0;
   pl.off_po = off;
-  if (pl.n_split > 1) off += round_up((size_t)n_rows * pl.n_split * p->n_heads * p->d_v * 2, 256);
+  off += round_up(pieces * p->n_heads * p->d_v * (pl.f32 ? 4 : 2), 256);
   pl.off_ml = off;
-  if (pl.n_split > 1) off += round_up((size_t)n_rows * pl.n_split * p->n_heads * 2 * 4, 256);
+  off += round_up(pieces * p->n_heads * 2 * 4, 256);
   pl.total = off;
   return pl;
 }
 
+// The plan whose workspace every call must bring: one piece per CU for calls of fewer rows than CUs.
+AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+  const bool few = p->latent != 0 && n_rows > 0 && n_rows < kCus;
+  return plan_pieces(p, n_rows, k_cap, paged, 0, few ? cdiv(kCus, n_rows) : 1, false);
+}
+
+// The plan used when the workspace has room for it. Rounds of kCus whole rows, and the n_rows mod kCus
+// rows that are left cut into the number of pieces that finishes first by this count, in units of one
+// 32-entry tile (about 1 us per workgroup): rounds * (tiles per piece + 9), the 9 for a piece's fixed
+// cost (73 KB of Q, list staging, pipeline fill, 64 KB of output), plus 5 for the merge and 0.03 (fp32:
+// 0.06) per piece for the partials it reads. Measured at 73 to 81 tiles, whole rows (and below 256 rows one piece
+// per CU whatever the rounds) before, this plan now: 4 rows 41.5 and 23.2 us, 24 rows 43.9 and 38.6 (264
+// pieces in two rounds, 240 in one), 100 rows 72 and 62, 170 rows 110 and 92.5, 257 rows 149 and 113, 333
+// rows 150 and 136, 513 rows 224 and 195. Cut only where the count promises 5%: 400 rows took 165 us in
+// pieces and 161 whole. The error against 64 bits stays or falls (100 rows 2.50e-3 to 2.06e-3).
+constexpr int64_t kMaxPieces = 512;  // bounds the partials (33 MB, 67 in fp32)
 AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
-  // too few rows to fill 256 CUs: split every row's list into 32-token-aligned pieces
-  const bool few = p->latent != 0 && n_rows > 0 && n_rows < kSplitTarget;
-  return plan_pieces(p, n_rows, k_cap, paged, few ? cdiv(kSplitTarget, n_rows) : 1);
+  const int64_t rem = n_rows % kCus, tiles = cdiv(k_cap, 32);
+  int64_t best = 1;
+  if (p->latent != 0 && rem > 0) {
+    double least = 0.95 * (tiles + 9);
+    for (int64_t ns = 2; ns <= tiles && rem * ns <= kMaxPieces; ++ns) {
+      const double cost = cdiv(rem * ns, kCus) * (cdiv(tiles, ns) + 9) + 5 + (n_rows < kCus ? 0.03 : 0.06) * rem * ns;
+      if (cost < least) {
+        least = cost;
+        best = ns;
+      }
+    }
+  }
+  // Partials in bf16 (half the merge's traffic: 46 against 51 us at 64 rows) round every piece once more,
+  // which averages out over a row's pieces: rows in fewer pieces than plan_least's keep fp32 ones.
+  const AttnPlan pl = plan_pieces(p, n_rows, k_cap, paged, n_rows - rem, best, false);
+  const bool f32 = pl.n_whole > 0 || pl.n_split < plan_least(p, n_rows, k_cap, paged).n_split;
+  return f32 ? plan_pieces(p, n_rows, k_cap, paged, n_rows - rem, best, true) : pl;
+}
+
+// The plan of a call with this workspace (which covers plan_least's).
+AttnPlan plan_call(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, const void* ws,
+                   size_t ws_bytes) {
+  const AttnPlan pl = plan_attn(p, n_rows, k_cap, paged);
+  const bool fits = pl.total == 0 || (ws != nullptr && aligned(ws, 256) && ws_bytes >= pl.total);
+  return fits ? pl : plan_least(p, n_rows, k_cap, paged);
+}
+
+// The plan's pieces and, when there are several, its partials in the workspace.
+void set_plan(lsa::AttnGeom& a, const AttnPlan& pl, uint8_t* ws) {
+  a.n_whole = pl.n_whole;
+  a.n_split = pl.n_split;
+  a.split_len = pl.split_len;
+  if (pl.n_split > 1) {
+    if (pl.f32) a.part_f32 = reinterpret_cast<float*>(ws + pl.off_po);
+    else a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
+    a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
+  }
+}
+
+size_t attn_ws_bytes(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+  const size_t a = plan_attn(p, n_rows, k_cap, paged).total, b = plan_least(p, n_rows, k_cap, paged).total;
+  return a > b ? a : b;
 }
 
 lsa_status check_attn_params(const lsa_attn_params* p) {
@@ -511,7 +569,7 @@ lsa_status lsa_index_decode_static(const lsa_index_params* p, int32_t batch, con
 
 size_t lsa_sparse_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || k_cap < 1) return 0;
-  return plan_attn(p, n_rows, k_cap, paged).total;
+  return attn_ws_bytes(p, n_rows, k_cap, paged);
 }
 
 lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv, const void* v,
@@ -537,11 +595,11 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   if (paged)
     LSA_REQUIRE(max_pages >= 1 && kv_page_size >= 1 && rows_per_seq >= 1, LSA_ERR_INVALID_ARG,
                 "paged cache needs max_pages, kv_page_size and rows_per_seq >= 1");
-  const AttnPlan pl = plan_attn(p, n_rows, k_cap, paged);
-  LSA_REQUIRE(pl.total == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
+  const size_t need = plan_least(p, n_rows, k_cap, paged).total;
+  LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
-  LSA_REQUIRE(ws_bytes >= pl.total, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, pl.total);
-  if (n_rows == 0) return LSA_OK;
+  LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, paged, workspace, ws_bytes);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
@@ -556,8 +614,6 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   a.out = static_cast<uint16_t*>(out);
   a.lse = lse;
   a.n_rows = n_rows;
-  a.n_split = pl.n_split;
-  a.split_len = pl.split_len;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
   a.k_swa = -1;  // plain lists
   if (paged && mla) {  // the MLA kernel translates positions while it stages each list
@@ -572,10 +628,7 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
     if (e != hipSuccess) return hip_fail(e, "page-table translation");
     a.rows = rows;
   }
-  if (pl.n_split > 1) {
-    a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
-    a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
-  }
+  set_plan(a, pl, ws);
   hipError_t e = mla ? lsa::launch_mla_attn(a, st) : lsa::launch_mqa_attn(a, st);
   if (e != hipSuccess) return hip_fail(e, "sparse attention");
   return LSA_OK;
@@ -592,7 +645,7 @@ static size_t runs_list_bytes(int64_t n_rows, int32_t k_cap) {
 
 size_t lsa_sparse_attn_runs_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || k_cap < 1) return 0;
-  const size_t attn = plan_attn(p, n_rows, k_cap, paged).total;
+  const size_t attn = attn_ws_bytes(p, n_rows, k_cap, paged);
   return runs_fused(p, paged != 0) ? attn : runs_list_bytes(n_rows, k_cap) + attn;
 }
 
@@ -620,7 +673,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
   if (paged)
     LSA_REQUIRE(max_pages >= 1 && kv_page_size >= 1 && rows_per_seq >= 1, LSA_ERR_INVALID_ARG,
                 "paged cache needs max_pages, kv_page_size and rows_per_seq >= 1");
-  const size_t need = lsa_sparse_attn_runs_workspace_size(p, n_rows, k_cap, paged);
+  const size_t need = (runs_fused(p, paged) ? 0 : runs_list_bytes(n_rows, k_cap)) + plan_least(p, n_rows, k_cap, paged).total;
   LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
@@ -637,7 +690,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
     return lsa_sparse_attn(p, n_rows, q, kv, v, n_kv_rows, idx, count, k_cap, page_table, max_pages, kv_page_size,
                            rows_per_seq, out, lse, ws + head, ws_bytes - head, stream);
   }
-  const AttnPlan pl = plan_attn(p, n_rows, k_cap, 0);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, 0, workspace, ws_bytes);
   lsa::AttnGeom a{};
   a.q = static_cast<const uint16_t*>(q);
   a.kv = static_cast<const uint16_t*>(kv);
@@ -648,14 +701,9 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
   a.out = static_cast<uint16_t*>(out);
   a.lse = lse;
   a.n_rows = n_rows;
-  a.n_split = pl.n_split;
-  a.split_len = pl.split_len;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
   a.k_swa = -1;  // plain lists
-  if (pl.n_split > 1) {
-    a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
-    a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
-  }
+  set_plan(a, pl, ws);
   const hipError_t e = lsa::launch_mla_attn(a, st);
   if (e != hipSuccess) return hip_fail(e, "sparse attention (run form)");
   return LSA_OK;
@@ -702,7 +750,7 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
   // the lists with their windows as contiguous rows, in as many pieces as the workspace has partials
   const int32_t cap = k_cap > k_swa ? k_cap : k_swa;  // entries a row can have
   AttnPlan pl = plan_attn(p, n_rows, cap, 0);
-  if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 2);  // (two per row always fit)
+  if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 0, n_rows < kCus ? 2 : 1, false);  // (two per row always fit)
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   lsa::AttnGeom a{};
   a.q = static_cast<const uint16_t*>(q);
@@ -714,15 +762,10 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
   a.out = static_cast<uint16_t*>(out);
   a.lse = lse;
   a.n_rows = n_rows;
-  a.n_split = pl.n_split;
-  a.split_len = pl.split_len;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
   a.k_swa = k_swa;
   a.q_pos0 = q_start;
-  if (pl.n_split > 1) {
-    a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
-    a.part_ml = reinterpret_cast<float*>(ws + pl.off_ml);
-  }
+  set_plan(a, pl, ws);
   const hipError_t e = lsa::launch_mla_attn(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "split attention");
   return LSA_OK;

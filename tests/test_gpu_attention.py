@@ -273,6 +273,38 @@ def test_many_rows_mixed_lists():
         P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
 
 
+@pytest.mark.parametrize("n_rows,k_cap", [(257, 400), (333, 2308), (300, 33), (511, 700), (600, 1500)])
+def test_rows_left_over_a_round(n_rows, k_cap):
+    """Calls of 256 rows or more whose last rows do not fill the CUs cut those rows' lists into pieces: one
+    row of 13 tiles, 77 in three pieces, 44 of two tiles, 255 (kept whole) and 88 after two rounds, with an
+    empty row and a short one among them; against the oracle, and with a workspace that holds no partials
+    (every row whole, as before), within two roundings of each other."""
+    from dataclasses import replace
+    w = replace(W.SMALL_MLA, seq_len=6000)
+    n_kv = w.seq_len
+    a = _attn_inputs(w, 0, n_rows, n_kv)
+    g = np.random.default_rng(17)
+    cnt = np.full(n_rows, k_cap, np.int32)
+    cnt[::7] = g.integers(1, k_cap + 1, cnt[::7].size)
+    if n_rows % 256 > 3:
+        cnt[-2], cnt[-3] = 0, 1
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    for i, c in enumerate(cnt):
+        idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
+    rows = list(range(n_rows))
+    o, l = _gpu_attn(w, a, rows, idx, cnt)
+    tiny = torch.empty(256, dtype=torch.uint8, device="cuda")
+    ow, lw = lsa.sparse_attn(w.attn_params(), P.bf16_dev(a["q"][rows]), P.bf16_dev(a["kv"]), None, P.to_dev(idx), P.to_dev(cnt),
+                             workspace=tiny)
+    ow, lw = ow.float().cpu().numpy(), lw.cpu().numpy()
+    sel = [i for i in list(range(0, 250, 50)) + list(range(256, n_rows, 11)) + [n_rows - 1] if cnt[i] > 0]
+    for i in np.nonzero(cnt == 0)[0]:
+        assert np.all(o[i] == 0) and np.all(np.isneginf(l[i]))
+    _check_rows(w, a, sel, idx[sel], cnt[sel], o[sel], l[sel])
+    full = cnt > 0
+    assert np.max(np.abs(o[full] - ow[full])) <= 2e-2 and np.max(np.abs(l[full] - lw[full])) <= 2e-3
+
+
 def test_mqa_long_lists():
     """MQA (16 x 128, separate K and V) over lists far longer than the L = 2048 workload's (1, 31,
     32, 33, 4097 and 9000 entries, the last tile partial), against the oracle."""
