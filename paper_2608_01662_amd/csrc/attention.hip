@@ -661,15 +661,26 @@ void mla_attn_kernel(AttnGeom a) {
 }
 
 // ============================================================================ MQA 16 x 128
-// One wave per query row. K and V tiles (32 rows each) are staged through VGPRs into LDS;
-// the configuration is small, so simplicity wins over the direct-load pipeline.
-constexpr int kMqaKStride = 272;  // 256 + 16: K rows start 4 banks apart
-constexpr int kMqaVStride = 288;  // 256 + 32: transposed V reads hit distinct banks
+// W waves per query row, wave w taking 32-entry tiles w, w + W, .. of its list; their maxima, sums and
+// fp32 accumulators are merged through LDS at the end. A call of few rows is bound by latency (list entry,
+// then rows, per tile, against 16 small matrix products), so list entries are read three tiles ahead,
+// paged positions translated two ahead, and a tile's rows are requested as soon as the previous tile's are
+// in LDS. A call of many rows is bound by the gather (every load takes four whole 256-byte rows: requesting
+// K in the operand layout, 16 rows x 64 bytes per load and no LDS for it, took 141 us at 8192 rows against
+// 120; without the prefetch 127).
+constexpr int kMqaKStride = 272;  // bytes per K row, 256 + 16: K rows start 4 banks apart
+constexpr int kMqaVStride = 288;  // bytes per V row, 256 + 32: transposed V reads hit distinct banks
+constexpr int kMqaOStride = 132;  // floats per head of a merged partial
+static_assert(16 * kMqaOStride * 4 <= 32 * kMqaVStride, "the partial reuses the wave's V rows");
 
-__global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
-  __shared__ __attribute__((aligned(16))) uint8_t lk[32 * kMqaKStride];
-  __shared__ __attribute__((aligned(16))) uint8_t lv[32 * kMqaVStride];
-  const int lane = threadIdx.x, g = lane >> 4, i16 = lane & 15, j = lane & 31;
+template <int W>
+__global__ __launch_bounds__(64 * W) void mqa_attn_kernel(AttnGeom a) {
+  __shared__ __attribute__((aligned(16))) uint8_t lks[W][32 * kMqaKStride];
+  __shared__ __attribute__((aligned(16))) uint8_t lvs[W][32 * kMqaVStride];
+  __shared__ float pm[W][16], pl[W][16];
+  const int lane = threadIdx.x & 63, g = lane >> 4, i16 = lane & 15, j = lane & 31;
+  const int wv = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  uint8_t *const lk = lks[wv], *const lv = lvs[wv];
   const int64_t row = xcd_band(blockIdx.x, a.n_rows);
   int cnt = a.count[row];
   cnt = cnt < 0 ? 0 : (cnt > a.k_cap ? a.k_cap : cnt);
@@ -677,6 +688,9 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
   const int32_t* slots = a.rows + row * a.k_cap;
   const u32x4* kg = reinterpret_cast<const u32x4*>(a.kv);
   const u32x4* vg = reinterpret_cast<const u32x4*>(a.v);
+  const int32_t* tab = a.page_table ? a.page_table + (row / a.rows_per_seq) * a.max_pages : nullptr;
+  const int kvp = a.kv_page, lg = __ffs(kvp) - 1;
+  const bool p2 = (kvp & (kvp - 1)) == 0;
 
   // Q^T as the B operand: column = head i16, k-step s covers dims 32s + 8g .. +7
   u32x4 qb[4];
@@ -685,34 +699,51 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) qb[s] = qp[4 * s];
   }
+  // list entry of token j of tile `it` (-1 past the list), and its cache row (-1: skipped)
+  auto entry = [&](int it) { return it * 32 + j < n ? slots[it * 32 + j] : -1; };
+  auto cache_row = [&](int pos) -> int {
+    if (tab && pos >= 0) {
+      const int pg = p2 ? pos >> lg : pos / kvp;
+      const int64_t ph = pg < a.max_pages ? tab[pg] : -1;
+      const int64_t cr = ph * kvp + (pos - pg * kvp);
+      return (ph >= 0 && cr < a.n_kv_rows) ? (int)cr : -1;
+    }
+    return (pos >= 0 && (int64_t)pos < a.n_kv_rows) ? pos : -1;
+  };
+  // load k takes tokens 4 k .. + 3, lane 16 g + i16 the 16 bytes i16 of token 4 k + g
+  u32x4 kr[8], vr[8];
+  auto request = [&](int pr) {  // (skipped entries re-read row 0, masked)
+    pr = pr >= 0 ? pr : 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t at = (int64_t)__shfl(pr, 4 * k + g) * 16 + i16;
+      kr[k] = kg[at];
+      vr[k] = vg[at];
+    }
+  };
   f32x4 o[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) o[c] = f32x4{};
   float m = -INFINITY, l = 0.f;
 
-  for (int it = 0; it < ntiles; ++it) {
-    const int sl = it * 32 + j;
-    int pr = sl < n ? slots[sl] : -1;
-    pr = (pr >= 0 && (int64_t)pr < a.n_kv_rows) ? pr : -1;
-    // stage K and V rows: 512 chunks of 16 bytes each, 8 per lane
-    u32x4 kr[8], vr[8];
+  const int e0 = entry(wv), e1 = entry(wv + W);
+  int e2 = entry(wv + 2 * W);        // list entry of the tile two ahead
+  int pr = cache_row(e0);            // cache rows of the current tile (mask)
+  int pr1 = cache_row(e1);           // and of the next
+  if (wv < ntiles) request(pr);
+  for (int it = wv; it < ntiles; it += W) {
+    __builtin_amdgcn_wave_barrier();  // (the wave's own LDS rows: written after the last tile's reads)
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const int u = k * 64 + lane, tok = u >> 4, ch = u & 15;
-      const int r = __shfl(pr, tok);
-      const int64_t base = (int64_t)(r >= 0 ? r : 0) * 16 + ch;
-      kr[k] = kg[base];
-      vr[k] = vg[base];
+      *reinterpret_cast<u32x4*>(lk + (4 * k + g) * kMqaKStride + i16 * 16) = kr[k];
+      *reinterpret_cast<u32x4*>(lv + (4 * k + g) * kMqaVStride + i16 * 16) = vr[k];
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int u = k * 64 + lane, tok = u >> 4, ch = u & 15;
-      *reinterpret_cast<u32x4*>(lk + tok * kMqaKStride + ch * 16) = kr[k];
-      *reinterpret_cast<u32x4*>(lv + tok * kMqaVStride + ch * 16) = vr[k];
-    }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
     const uint32_t vmask = (uint32_t)__ballot(pr >= 0);
+    pr = pr1;
+    if (it + W < ntiles) request(pr);
+    pr1 = cache_row(e2);
+    e2 = entry(it + 3 * W);
     // ---- S^T = K Q^T, two 16-token M tiles; lane holds tokens 16mt + 4g + r of head i16
     f32x4 sacc[2] = {f32x4{}, f32x4{}};
 #pragma unroll
@@ -732,8 +763,7 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
         z[4 * mt + r] = ((vmask >> tk) & 1u) ? sacc[mt][r] * a.scale_log2 : -INFINITY;
         mx = fmaxf(mx, z[4 * mt + r]);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = max4_xor16_32(mx);
     const bool need = mx > m + kLazy;
     if (__ballot(need)) {
       const float alpha = need ? fast_exp2(m - mx) : 1.f;
@@ -757,16 +787,46 @@ __global__ __launch_bounds__(64) void mqa_attn_kernel(AttnGeom a) {
       o[c] = mfma16(tr16_pair(p0, p0 + 16 * kMqaVStride), pb, o[c]);
     }
   }
-  float lt = l + __shfl_xor(l, 16);
-  lt += __shfl_xor(lt, 32);
-  const float inv = lt > 0.f ? 1.f / lt : 0.f;
-  uint16_t* orow = a.out + (row * 16 + i16) * 128 + 4 * g;
+  const float lt = sum4_xor16_32(l);
+  if constexpr (W == 1) {
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    uint16_t* orow = a.out + (row * 16 + i16) * 128 + 4 * g;
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const u32x2 v = {pack_bf16x2(o[c][0] * inv, o[c][1] * inv), pack_bf16x2(o[c][2] * inv, o[c][3] * inv)};
-    *reinterpret_cast<u32x2*>(orow + 16 * c) = v;
+    for (int c = 0; c < 8; ++c) {
+      const u32x2 v = {pack_bf16x2(o[c][0] * inv, o[c][1] * inv), pack_bf16x2(o[c][2] * inv, o[c][3] * inv)};
+      *reinterpret_cast<u32x2*>(orow + 16 * c) = v;
+    }
+    if (a.lse && g == 0) a.lse[row * 16 + i16] = lt > 0.f ? (m + __log2f(lt)) * kLn2 : -INFINITY;
+  } else {
+    // merge of the waves' partials, weighted by 2^(m_w - M)
+    float* const po = reinterpret_cast<float*>(lv);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) *reinterpret_cast<f32x4*>(po + i16 * kMqaOStride + 16 * c + 4 * g) = o[c];
+    if (g == 0) {
+      pm[wv][i16] = m;
+      pl[wv][i16] = lt;
+    }
+    __syncthreads();
+    for (int u = (int)threadIdx.x; u < 512; u += 64 * W) {  // head u / 32, dims 4 (u % 32) ..
+      const int head = u >> 5, d = 4 * (u & 31);
+      float M = -INFINITY;
+#pragma unroll
+      for (int x = 0; x < W; ++x) M = fmaxf(M, pm[x][head]);
+      float L = 0.f;
+      f32x4 acc = {};
+#pragma unroll
+      for (int x = 0; x < W; ++x) {
+        if (!(pl[x][head] > 0.f)) continue;  // (a wave without tiles)
+        const float wgt = fast_exp2(pm[x][head] - M);
+        L += pl[x][head] * wgt;
+        acc += wgt * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(lvs[x]) + head * kMqaOStride + d);
+      }
+      const float inv = L > 0.f ? 1.f / L : 0.f;
+      *reinterpret_cast<u32x2*>(a.out + (row * 16 + head) * 128 + d) =
+          u32x2{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
+      if (a.lse && d == 0) a.lse[row * 16 + head] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
+    }
   }
-  if (a.lse && g == 0) a.lse[row * 16 + i16] = lt > 0.f ? (m + __log2f(lt)) * kLn2 : -INFINITY;
 }
 
 // ============================================================================ split combine
@@ -918,30 +978,6 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
   if (a.lse && threadIdx.x == 0) a.lse[orow] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
 
-// ============================================================================ paged position -> cache row
-__global__ __launch_bounds__(256) void translate_rows_kernel(const int32_t* __restrict__ idx, const int32_t* __restrict__ count,
-                                                             int64_t n_rows, int k_cap, const int32_t* __restrict__ table,
-                                                             int max_pages, int kv_page, int rows_per_seq, int64_t n_kv_rows,
-                                                             int32_t* __restrict__ out) {
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= n_rows * k_cap) return;
-  const int64_t row = id / k_cap;
-  const int i = (int)(id - row * k_cap);
-  int c = count[row];
-  c = c < 0 ? 0 : (c > k_cap ? k_cap : c);
-  int32_t r = -1;
-  if (i < c) {
-    const int32_t s = idx[id];
-    const int64_t pg = s >= 0 ? s / kv_page : -1;
-    if (pg >= 0 && pg < max_pages) {
-      const int64_t ph = table[(row / rows_per_seq) * max_pages + pg];
-      const int64_t cr = ph * kv_page + s % kv_page;
-      if (ph >= 0 && cr < n_kv_rows) r = (int32_t)cr;
-    }
-  }
-  out[id] = r;
-}
-
 // ============================================================================ host launchers
 template <bool SPLIT>
 static void launch_mla_kernel(dim3 grid, const AttnGeom& a, hipStream_t st) {
@@ -961,9 +997,17 @@ hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Waves per row: up to 8, while that does not pass kMqaFill waves (four per CU) or the list's tiles. At
+// 13 tiles, one wave per row took 18.7 us for 16 rows or for 100 (and a decode call of 24 rows 20.9, after
+// a translation kernel of 3.2), eight 8.2 and 8.5 (8.8); 600 rows 21.8 with one, 19 with two or four, 21.3
+// with eight; 1100 rows 27.1 with one, 27.9 with two, 28.5 with four.
+constexpr int64_t kMqaFill = 1024;
 hipError_t launch_mqa_attn(const AttnGeom& a, hipStream_t st) {
   if (a.n_rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(mqa_attn_kernel, dim3((unsigned)a.n_rows), dim3(64), 0, st, a);
+  int w = 1;
+  while (w < 8 && a.n_rows * w < kMqaFill && 32 * w < a.k_cap) w *= 2;
+  auto kernel = w == 1 ? mqa_attn_kernel<1> : w == 2 ? mqa_attn_kernel<2> : w == 4 ? mqa_attn_kernel<4> : mqa_attn_kernel<8>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)a.n_rows), dim3((unsigned)(64 * w)), 0, st, a);
   return hipGetLastError();
 }
 
@@ -973,16 +1017,6 @@ hipError_t launch_attn_combine(const AttnGeom& a, hipStream_t st) {
   auto kernel = a.part_f32 ? (deep ? attn_combine_deep_kernel<true> : attn_combine_kernel<true>)
                            : (deep ? attn_combine_deep_kernel<false> : attn_combine_kernel<false>);
   hipLaunchKernelGGL(kernel, grid, dim3(deep ? 512 : 128), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_translate_rows(const int32_t* idx, const int32_t* count, int64_t n_rows, int k_cap,
-                                 const int32_t* page_table, int max_pages, int kv_page, int rows_per_seq,
-                                 int64_t n_kv_rows, int32_t* out_rows, hipStream_t st) {
-  const int64_t n = n_rows * k_cap;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(translate_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, idx, count, n_rows, k_cap,
-                     page_table, max_pages, kv_page, rows_per_seq, n_kv_rows, out_rows);
   return hipGetLastError();
 }
 

@@ -85,7 +85,7 @@ struct AttnGeom {
   // of the runs (start, length) runs[r, 0..run_count[r]), int32 pairs with row stride k_cap.
   const int32_t* runs;
   const int32_t* run_count;
-  // Paged cache (MLA list form; nullptr = rows are cache rows): rows holds positions, and position
+  // Paged cache (list form; nullptr = rows are cache rows): rows holds positions, and position
   // s of query row r is cache row page_table[(r / rows_per_seq) * max_pages + s / kv_page] *
   // kv_page + s % kv_page, translated while the list is staged.
   const int32_t* page_table;
@@ -95,8 +95,5 @@ struct AttnGeom {
 hipError_t launch_mla_attn(const AttnGeom& a, hipStream_t st);
 hipError_t launch_mqa_attn(const AttnGeom& a, hipStream_t st);
 hipError_t launch_attn_combine(const AttnGeom& a, hipStream_t st);  // MLA: 64 heads x 512
-hipError_t launch_translate_rows(const int32_t* idx, const int32_t* count, int64_t n_rows, int k_cap,
-                                 const int32_t* page_table, int max_pages, int kv_page, int rows_per_seq,
-                                 int64_t n_kv_rows, int32_t* out_rows, hipStream_t st);
 
 }  // namespace lsa

@@ -208,7 +208,7 @@ struct AttnPlan {
   int64_t n_whole;  // rows taken whole (with n_split > 1; the later ones are cut into n_split pieces)
   int n_split, split_len;
   bool f32;         // partials in fp32
-  size_t off_rows, off_po, off_ml, total;
+  size_t off_po, off_ml, total;
 };
 
 // Workgroups the GPU runs at once: one per CU (the MLA kernel's LDS admits one per CU).
@@ -230,7 +230,7 @@ AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, in
   pl.n_whole = pl.n_split > 1 ? n_whole : 0;
   pl.f32 = f32;
   size_t off = 0;
-  pl.off_rows = off;  // translated cache rows (paged MQA; the MLA kernel translates as it stages)
+  // (paged MQA calls bring room for a translated list, as they had to when a kernel of its own made it)
   if (paged && !mla) off += round_up((size_t)n_rows * k_cap * 4, 256);
   const size_t pieces = pl.n_split > 1 ? (size_t)(n_rows - pl.n_whole) * pl.n_split : 0;
   pl.off_po = off;
@@ -616,17 +616,11 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   a.n_rows = n_rows;
   a.scale_log2 = p->sm_scale * 1.4426950408889634f;
   a.k_swa = -1;  // plain lists
-  if (paged && mla) {  // the MLA kernel translates positions while it stages each list
+  if (paged) {  // the kernels translate positions as they read the lists
     a.page_table = page_table;
     a.max_pages = max_pages;
     a.kv_page = kv_page_size;
     a.rows_per_seq = rows_per_seq;
-  } else if (paged) {
-    int32_t* rows = reinterpret_cast<int32_t*>(ws + pl.off_rows);
-    hipError_t e = lsa::launch_translate_rows(idx, count, n_rows, k_cap, page_table, max_pages, kv_page_size,
-                                              rows_per_seq, n_kv_rows, rows, st);
-    if (e != hipSuccess) return hip_fail(e, "page-table translation");
-    a.rows = rows;
   }
   set_plan(a, pl, ws);
   hipError_t e = mla ? lsa::launch_mla_attn(a, st) : lsa::launch_mqa_attn(a, st);

@@ -326,6 +326,50 @@ def test_mqa_long_lists():
         P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
 
 
+@pytest.mark.parametrize("n_rows,k_cap,paged", [(1, 400, False), (5, 32, False), (5, 33, True), (129, 100, False), (129, 100, True),
+                                                (257, 65, True), (513, 388, False), (1025, 97, True)])
+def test_mqa_waves_per_row(n_rows, k_cap, paged):
+    """MQA with eight, four, two and one waves per row (fewer rows, or lists of fewer tiles), contiguous and
+    paged (pages of 48 tokens, with unmapped pages and positions outside the cache among the entries): lists
+    shorter than the waves' first tiles, empty rows, and a wave's last tile partial, against the oracle."""
+    w = W.L2K_MQA
+    n_kv, page = 1536, 48
+    H, dqk, dv = w.attn_dims
+    a = _attn_inputs(w, 0, n_rows, n_kv)
+    g = np.random.default_rng(19)
+    cnt = g.integers(0, k_cap + 1, n_rows).astype(np.int32)
+    cnt[0], cnt[-1] = k_cap, max(0, k_cap - 1)
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    for i, c in enumerate(cnt):
+        idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
+    q, kv, v = P.bf16_dev(a["q"]), P.bf16_dev(a["kv"]), P.bf16_dev(a["v"])
+    if paged:
+        table = g.permutation(n_kv // page).astype(np.int32)
+        table[7] = -1                                 # an unmapped page: its positions are skipped
+        tab2 = np.stack([table, table[::-1]])         # two sequences, rows split between them
+        rps = -(-n_rows // 2)
+        idx[0, 0] = n_kv + 5                          # a position past the table
+        o, l = lsa.sparse_attn(w.attn_params(), q, kv.view(-1, page, dqk), v.view(-1, page, dv), P.to_dev(idx), P.to_dev(cnt),
+                               page_table=P.to_dev(np.ascontiguousarray(tab2)), kv_page_size=page, rows_per_seq=rps)
+        rows = np.full_like(idx, -1)
+        for i in range(n_rows):
+            pg = idx[i] // page
+            ph = np.where((idx[i] >= 0) & (pg < len(table)), tab2[i // rps][np.clip(pg, 0, len(table) - 1)], -1)
+            rows[i] = np.where(ph >= 0, ph * page + idx[i] % page, -1)
+        idx = rows
+    else:
+        o, l = lsa.sparse_attn(w.attn_params(), q, kv, v, P.to_dev(idx), P.to_dev(cnt))
+    o, l = o.float().cpu().numpy(), l.cpu().numpy()
+    for i in list(range(0, n_rows, 1 + n_rows // 60)) + [n_rows - 1]:
+        S = idx[i, :cnt[i]]
+        S = S[S >= 0]
+        if S.size == 0:
+            assert np.all(o[i] == 0) and np.all(np.isneginf(l[i])), f"row {i}"
+            continue
+        oref, lref = orc.attention_for_set(a["q"][i], a["kv"], a["v"], S, dv, w.sm_scale)
+        P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
+
+
 @pytest.mark.parametrize("n_rows", [None, 8], ids=["all_rows", "split_8_rows"])
 def test_run_form_equals_list_form(n_rows):
     """Attention over the indexer's run encoding equals attention over its index lists, bit for bit
