@@ -1864,16 +1864,19 @@ hipError_t launch_coarse(const IndexGeom& g, int64_t n_rows, const uint16_t* q, 
                   : launch_coarse_d<64, false>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, st);
 }
 
+// Threads per row of the page selection: its time is the chain of barriers and scans, shorter with fewer
+// waves, against the keys per thread. Few rows (us, 64 / 256 / 1024 threads): 256 pages 6.7 / 5.3 / 6.3, 1015
+// pages - / 8.8 / 7.8. Many rows: 32 to 78 pages 5.6 against 6.4 with 256 threads (2048 rows) and 7.2
+// against 12.0 (5000), 512 pages 14.8 against 17.2 (4096 rows).
+constexpr int64_t kPageSelectSmall = 512;
 hipError_t launch_page_select(const IndexGeom& g, int64_t n_rows, const uint32_t* page_keys, int64_t ld,
                               int32_t* pages, int32_t* phys, int64_t max_elig, hipStream_t st) {
   if (n_rows == 0) return hipSuccess;
   const size_t lds = page_select_lds_bytes(max_elig, phys != nullptr);
-  if (n_rows <= kSelectFewRows)  // few rows (decode): more threads per row
-    hipLaunchKernelGGL(page_select_kernel<1024>, dim3((unsigned)n_rows), dim3(1024), lds, st, g, n_rows, page_keys, ld,
-                       pages, phys);
-  else
-    hipLaunchKernelGGL(page_select_kernel<256>, dim3((unsigned)n_rows), dim3(256), lds, st, g, n_rows, page_keys, ld,
-                       pages, phys);
+  const bool few = n_rows <= kSelectFewRows, small = max_elig <= kPageSelectSmall;
+  const int nt = few ? (small ? 256 : 1024) : (small ? 64 : 256);
+  auto kernel = nt == 64 ? page_select_kernel<64> : nt == 256 ? page_select_kernel<256> : page_select_kernel<1024>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)n_rows), dim3((unsigned)nt), lds, st, g, n_rows, page_keys, ld, pages, phys);
   return hipGetLastError();
 }
 
@@ -1974,7 +1977,16 @@ hipError_t launch_token_select(const IndexGeom& g, int64_t n_rows, const uint32_
   const int k_cap = g.k_sink + g.k_swa + g.k_sparse;
   const size_t lds = token_select_lds_bytes(slots_cap, k_cap, g.M);
   const dim3 grid((unsigned)n_rows), block(512);
-  if (slots_cap <= 1024 * 8 && n_rows <= kSelectFewRows)   // few rows (decode): more threads per row
+  // Short rows take fewer threads (a chain of barriers, and waves without keys, is what they cost): 1024
+  // slots 28.4 us with 512 threads of 16 keys, 11.5 with 128 of 8 and 12.6 with 256 of 4 (2048 rows; 24 rows
+  // 9.8 with 1024 threads, 7.9 with 128); up to 2000 slots, flat, 21.1 and 15.9 us (3001 rows).
+  if (slots_cap <= 128 * 8)
+    hipLaunchKernelGGL((token_select_reg_kernel<128, 8>), grid, dim3(128), lds, st, g, n_rows, fine_keys, ldf, pages,
+                       idx, count, runs, run_count);
+  else if (slots_cap <= 256 * 16 && n_rows > kSelectFewRows)
+    hipLaunchKernelGGL((token_select_reg_kernel<256, 16>), grid, dim3(256), lds, st, g, n_rows, fine_keys, ldf, pages,
+                       idx, count, runs, run_count);
+  else if (slots_cap <= 1024 * 8 && n_rows <= kSelectFewRows)   // few rows (decode): more threads per row
     hipLaunchKernelGGL((token_select_reg_kernel<1024, 8>), grid, dim3(1024), lds, st, g, n_rows, fine_keys, ldf, pages,
                        idx, count, runs, run_count);
   else if (slots_cap <= 512 * 16)
@@ -2101,7 +2113,8 @@ hipError_t prepare_index_kernels() {
   const int lim = (int)kSelectLdsLimit;
   const void* sel[] = {(const void*)token_select_kernel<512, false>, (const void*)token_select_kernel<1024, true>,
                        (const void*)token_select_reg_kernel<512, 16>, (const void*)token_select_reg_kernel<512, 32>,
-                       (const void*)token_select_reg_kernel<512, 64>, (const void*)token_select_reg_kernel<1024, 8>};
+                       (const void*)token_select_reg_kernel<512, 64>, (const void*)token_select_reg_kernel<1024, 8>,
+                       (const void*)token_select_reg_kernel<128, 8>, (const void*)token_select_reg_kernel<256, 16>};
   for (const void* f : sel) {  // (static LDS: under 4 KB in the first two, under 20 KB in the others)
     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (f == sel[0] || f == sel[1]) ? lim : lim - 16 * 1024);
@@ -2109,6 +2122,8 @@ hipError_t prepare_index_kernels() {
   }
   // the page selection's static LDS (range histograms) is under 8 KB
   e = hipFuncSetAttribute((const void*)page_select_kernel<256>, hipFuncAttributeMaxDynamicSharedMemorySize, lim - 4096);
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute((const void*)page_select_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, lim - 4096);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)page_select_kernel<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, lim - 4096);
   if (e != hipSuccess) return e;

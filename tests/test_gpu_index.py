@@ -469,6 +469,22 @@ def test_few_rows_equal_single_call(w):
         P.assert_same_index_outputs(part, whole, slice(q0, q0 + nq))
 
 
+@pytest.mark.parametrize("keep_pages,n_q", [(32, 1100), (33, 1100), (128, 1100), (129, 1100), (33, 40)])
+def test_selection_thread_counts(keep_pages, n_q):
+    """Token selection on both sides of each change of its threads per row: 1024 and 1056 candidate slots, 4096
+    and 4128 (many rows), and 1056 for few rows; page selection with one wave (few pages, many rows) and
+    256 threads (few rows). Sampled rows against the oracle, stage-wise, with their runs."""
+    w = replace(W.SMALL_MLA, name=f"d64_P32_M{keep_pages}", head_dim=64, page=32, sub_block=32, keep_pages=keep_pages, seq_len=6000,
+                k_sparse=300, run_align=32)
+    inp = P.prefill_inputs(w)
+    q0 = w.seq_len - n_q
+    out, _ = _run_prefill(w, inp, q_start=q0, n_q=n_q)
+    rows = sorted({0, 1, n_q // 3, n_q // 2, n_q - 2, n_q - 1} | set(range(7, n_q, 97)))
+    res = _oracle_rows(w, inp, [q0 + r for r in rows])
+    P.check_index_rows(w, [q0 + r for r in rows], out["idx"][rows], out["count"][rows], out["pages"][rows], res)
+    P.check_runs(out["runs"][rows], out["run_count"][rows], out["idx"][rows], out["count"][rows], w.run_align)
+
+
 def test_chunked_parity_sampled():
     w = W.SMALL_CHUNKED
     inp = P.prefill_inputs(w)
