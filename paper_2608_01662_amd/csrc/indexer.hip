@@ -16,6 +16,7 @@
 // half h supply dims (d_I/2)*h + 8*s .. +7 of both operands. Any permutation applied to both
 // operands leaves the dot product unchanged, and this one lets every lane read one contiguous
 // run of key bytes.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -1612,6 +1613,196 @@ __device__ int global_compact(const uint32_t* keys, int n, uint32_t T, int take_
   return total;
 }
 
+// Selection of the k largest of the n keys of a row in global memory as a bit mask in LDS (rows of up to
+// kMaskKeys), in two passes over the keys where the threshold, gather and ordered compaction above take
+// four. (1) A histogram of the non-zero keys over kMaskBins bins: bin 0 below and the last one above the
+// range [lo, hi] of 4 NT sampled keys, the others splitting it evenly, so that the counts spread over the
+// bins (by their leading 11 bits the scores of a row fall into few bins, and their LDS atomics
+// serialize). (2) Keys in bins above the one that holds the k-th largest set their bit, the keys of that bin
+// are gathered with their positions, ranked against each other by (key descending, position ascending),
+// and the first ones set their bits. More than kMaskCand in the bin: both passes again over the exact
+// range of its keys, which shrinks by a factor of kMaskBins each time, until they fit or are all equal; then
+// T and take_eq are set as radix_threshold's and false is returned (the caller compacts by them).
+// Bandwidth of the L2 and the LDS bounds it: a row of 131072 candidates (512 rows: 498 us before, 150 now; 64 rows 262 and 60).
+constexpr int kMaskBins = 2048, kMaskCand = 1024;
+constexpr int64_t kMaskKeys = 262144;
+struct MaskLds {
+  uint32_t *mask, *hist, *ckey;
+  int* cpos;
+};
+// LDS words of a row of n keys
+__host__ __device__ constexpr int64_t mask_words(int64_t n) { return (n + 31) / 32 + kMaskBins + 2 * kMaskCand; }
+
+template <int NT>
+__device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s, int* wsum, uint32_t& T, int& take_eq) {
+  __shared__ uint32_t range[2], wlo[NT / 64], whi[NT / 64];
+  __shared__ int found[3], n_cand;  // boundary bin, keys in the bins above it; gathered keys
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  auto lowest = [](uint32_t p, uint32_t q) { return p < q ? p : q; };
+  auto highest = [](uint32_t p, uint32_t q) { return p > q ? p : q; };
+  for (int i = threadIdx.x; i < (n + 31) / 32; i += NT) s.mask[i] = 0u;
+  uint32_t lo = ~0u, hi = 0u;
+  {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(keys + (int)((int64_t)threadIdx.x * n / NT & ~3));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (v[c] != 0u) lo = lowest(lo, v[c]);
+      hi = highest(hi, v[c]);
+    }
+    lo = wave_reduce_u32(lo, lowest);
+    hi = wave_reduce_u32(hi, highest);
+    if (lane == 0) {
+      wlo[wv] = lo;
+      whi[wv] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NT / 64; ++x) {
+      lo = lowest(lo, wlo[x]);
+      hi = highest(hi, whi[x]);
+    }
+    if (hi == 0u) lo = hi = 1u;  // (no candidate among the samples)
+  }
+  int rem = k;
+  for (bool first = true;; first = false) {
+    for (int i = threadIdx.x; i < kMaskBins; i += NT) s.hist[i] = 0u;
+    if (threadIdx.x == 0) {
+      n_cand = 0;
+      range[0] = ~0u;
+      range[1] = 0u;
+    }
+    __syncthreads();
+    const uint32_t span = hi - lo;
+    constexpr uint32_t kInner = kMaskBins - 2;
+    const bool direct = span < kInner;  // one value per bin
+    const uint32_t scale = direct ? 0u : (uint32_t)floor(4294967296.0 * kInner / ((double)span + 1.0)) - 1u;
+    // bin of a key in play: every non-zero key at first, then those of the previous boundary bin
+    auto in_play = [&](uint32_t key) { return first ? key != 0u : key - lo <= span; };
+    auto bin_of = [&](uint32_t key) {
+      const uint32_t d = key - lo;
+      const uint32_t b = 1u + (direct ? d : __umulhi(d, scale));
+      return key < lo ? 0u : key > hi ? (uint32_t)kMaskBins - 1u : b;
+    };
+    int nz = 0;
+    stream_row<NT>(keys, n, [&](int, const u32x4& v, bool ok) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (ok && in_play(v[c])) {
+          atomicAdd(&s.hist[bin_of(v[c])], 1u);
+          ++nz;
+        }
+    });
+    if (first) {
+      nz = wave_sum(nz);
+      if (lane == 0) wsum[wv] = nz;
+    }
+    __syncthreads();
+    if (first) {
+      int n_valid = 0;
+#pragma unroll
+      for (int x = 0; x < NT / 64; ++x) n_valid += wsum[x];
+      if (n_valid <= k) {  // (uniform) every candidate
+        stream_row<NT>(keys, n, [&](int i, const u32x4& v, bool ok) {
+          const uint32_t nib = (v.x != 0u) | (v.y != 0u) << 1 | (v.z != 0u) << 2 | (v.w != 0u) << 3;
+          if (ok && nib) atomicOr(&s.mask[i >> 5], nib << (i & 31));
+        });
+        __syncthreads();
+        return true;
+      }
+    }
+    if (wv == 0) {  // lane l: bins 32 l .. + 31
+      constexpr int PER = kMaskBins / 64;
+      uint32_t tot = 0;
+#pragma unroll 8
+      for (int b = 0; b < PER; ++b) tot += s.hist[PER * lane + ((b + lane) & (PER - 1))];
+      uint32_t suf = tot;  // totals of lanes >= l
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_down(suf, o);
+        if (lane + o < 64) suf += x;
+      }
+      uint32_t above = suf - tot;
+      if (above < (uint32_t)rem && suf >= (uint32_t)rem)
+        for (int b = PER - 1; b >= 0; --b) {
+          const uint32_t c = s.hist[PER * lane + b];
+          if (above + c >= (uint32_t)rem) {
+            found[0] = PER * lane + b;
+            found[1] = (int)above;
+            break;
+          }
+          above += c;
+        }
+    }
+    __syncthreads();
+    const uint32_t bstar = (uint32_t)found[0];
+    rem -= found[1];
+    uint32_t mn = ~0u, mx = 0u;
+    stream_row<NT>(keys, n, [&](int i, const u32x4& v, bool ok) {
+      uint32_t nib = 0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (ok && in_play(v[c])) {
+          const uint32_t b = bin_of(v[c]);
+          nib |= (b > bstar ? 1u : 0u) << c;
+          if (b == bstar) {
+            const int at = atomicAdd(&n_cand, 1);
+            if (at < kMaskCand) {
+              s.ckey[at] = v[c];
+              s.cpos[at] = i + c;
+            }
+            mn = lowest(mn, v[c]);
+            mx = highest(mx, v[c]);
+          }
+        }
+      if (nib) atomicOr(&s.mask[i >> 5], nib << (i & 31));
+    });
+    mn = wave_reduce_u32(mn, lowest);
+    mx = wave_reduce_u32(mx, highest);
+    if (lane == 0) {
+      atomicMin(&range[0], mn);
+      atomicMax(&range[1], mx);
+    }
+    __syncthreads();
+    const int nc = n_cand;
+    if (nc <= kMaskCand) {
+      for (int x = threadIdx.x; x < nc; x += NT) {
+        const uint32_t key = s.ckey[x];
+        const int pos = s.cpos[x];
+        int rank = 0;
+        for (int y = 0; y < nc; ++y) rank += s.ckey[y] > key || (s.ckey[y] == key && s.cpos[y] < pos);
+        if (rank < rem) atomicOr(&s.mask[pos >> 5], 1u << (pos & 31));
+      }
+      __syncthreads();
+      return true;
+    }
+    lo = range[0];
+    hi = range[1];
+    if (lo == hi) {
+      T = lo;
+      take_eq = rem;
+      __syncthreads();
+      return false;
+    }
+    __syncthreads();  // (range and n_cand are rewritten)
+  }
+}
+
+// Calls emit(rank, i) for every bit i of a mask of n bits, in order; returns their number.
+template <int NT, typename F>
+__device__ int mask_emit(const uint32_t* mask, int n, int* wsum, F&& emit) {
+  const int nw = (n + 31) / 32, per = (nw + NT - 1) / NT;
+  const int b = (int)threadIdx.x * per < nw ? (int)threadIdx.x * per : nw, e = b + per < nw ? b + per : nw;
+  int mine = 0;
+  for (int i = b; i < e; ++i) mine += __popc(mask[i]);
+  int rank = block_excl_prefix<NT>(mine, wsum);
+  for (int i = b; i < e; ++i)
+    for (uint32_t m = mask[i]; m != 0u; m &= m - 1u) emit(rank++, 32 * i + __ffs(m) - 1);
+  int total = 0;
+#pragma unroll
+  for (int x = 0; x < NT / 64; ++x) total += wsum[x];
+  return total;
+}
+
 // Eq. (12) / Eq. (7) then Eq. (6): S_t = sink ++ (top K_sparse candidates, ascending) ++ window;
 // idx padded with -1; runs re-encode idx, cut at gaps and at multiples of C. General version:
 // the candidate keys are staged in LDS (any number that fits), or with GK (rows too long for
@@ -1627,8 +1818,8 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
   __shared__ int wsum[2 * NT / 64 + 2];
   const int k_cap = g.k_sink + g.k_swa + g.k_sparse;
   // LDS: keys [max(slots_cap, k_cap)] (not with GK), lidx [k_cap], lpages [M], and with GK the
-  // run-start scratch [k_cap] (otherwise the keys area serves for it), the 11-bit histogram, the
-  // gathered boundary-bin keys and their counter
+  // run-start scratch [k_cap] (otherwise the keys area serves for it), which rows of up to kMaskKeys share
+  // with the mask selection's areas, or the 11-bit histogram, the gathered boundary-bin keys and their counter
   const int key_words = GK ? 0 : (slots_cap > k_cap ? slots_cap : k_cap);
   int32_t* lidx = reinterpret_cast<int32_t*>(smem + key_words);
   int32_t* lpages = lidx + k_cap;
@@ -1661,7 +1852,13 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
     __syncthreads();
     uint32_t T = 0;
     int take = 0;
-    if (GK) {
+    bool masked = false;
+    uint32_t* const area = reinterpret_cast<uint32_t*>(rstart);  // 16-byte aligned offsets are not needed
+    const int nw = (slots_cap + 31) / 32;
+    if (GK && slots_cap <= kMaskKeys) {
+      const MaskLds ml = {area, area + nw, area + nw + kMaskBins, reinterpret_cast<int*>(area + nw + kMaskBins + kMaskCand)};
+      masked = mask_select<NT>(keys, n, g.k_sparse, ml, wsum, T, take);
+    } else if (GK) {
       global_threshold<NT>(keys, n, g.k_sparse, h11, gsub, gcnt, hist, wsum, T, take);
     } else {
       const int n_valid = block_count_nonzero(keys, n, wsum);
@@ -1678,7 +1875,8 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
       lidx[ks + rank] = (int32_t)(page * P + (i - pi * P));
     };
     int n_sp;
-    if constexpr (GK) n_sp = global_compact<NT>(keys, n, T, take, wsum, emit);
+    if (GK && masked) n_sp = mask_emit<NT>(area, n, wsum, emit);
+    else if constexpr (GK) n_sp = global_compact<NT>(keys, n, T, take, wsum, emit);
     else n_sp = select_compact<NT>(keys, n, T, take, wsum, emit);
     for (int i = threadIdx.x; i < g.k_sink; i += NT) lidx[i] = i;
     for (int i = threadIdx.x; i < g.k_swa; i += NT) lidx[g.k_sink + n_sp + i] = (int32_t)(ri.t - g.k_swa + 1 + i);
@@ -1867,14 +2065,16 @@ hipError_t launch_coarse(const IndexGeom& g, int64_t n_rows, const uint16_t* q, 
 // Threads per row of the page selection: its time is the chain of barriers and scans, shorter with fewer
 // waves, against the keys per thread. Few rows (us, 64 / 256 / 1024 threads): 256 pages 6.7 / 5.3 / 6.3, 1015
 // pages - / 8.8 / 7.8. Many rows: 32 to 78 pages 5.6 against 6.4 with 256 threads (2048 rows) and 7.2
-// against 12.0 (5000), 512 pages 14.8 against 17.2 (4096 rows).
+// against 12.0 (5000), 512 pages 14.8 against 17.2 (4096 rows); 2042 pages 16.6 with 256 and 28.3 with 1024
+// (1400 rows), 3900 pages 37.4 and 35.0 (1500), 8192 pages 162 and 73 (2048).
 constexpr int64_t kPageSelectSmall = 512;
+constexpr int64_t kPageSelectLong = 4096;
 hipError_t launch_page_select(const IndexGeom& g, int64_t n_rows, const uint32_t* page_keys, int64_t ld,
                               int32_t* pages, int32_t* phys, int64_t max_elig, hipStream_t st) {
   if (n_rows == 0) return hipSuccess;
   const size_t lds = page_select_lds_bytes(max_elig, phys != nullptr);
   const bool few = n_rows <= kSelectFewRows, small = max_elig <= kPageSelectSmall;
-  const int nt = few ? (small ? 256 : 1024) : (small ? 64 : 256);
+  const int nt = few ? (small ? 256 : 1024) : (small ? 64 : max_elig > kPageSelectLong ? 1024 : 256);
   auto kernel = nt == 64 ? page_select_kernel<64> : nt == 256 ? page_select_kernel<256> : page_select_kernel<1024>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)n_rows), dim3((unsigned)nt), lds, st, g, n_rows, page_keys, ld, pages, phys);
   return hipGetLastError();
@@ -1966,7 +2166,9 @@ size_t token_select_lds_bytes(int64_t slots_cap, int k_cap, int M) {
   switch (select_mode(slots_cap, k_cap, M)) {
     case SelectMode::kRegisters: return (2 * (size_t)k_cap + m) * 4;
     case SelectMode::kLds: return ((size_t)(slots_cap > k_cap ? slots_cap : k_cap) + k_cap + m) * 4;
-    default: return (2 * (size_t)k_cap + m + (1u << kSelHistBits) + kSelGatherCap + 1) * 4;
+    default:
+      if (slots_cap > kMaskKeys) return (2 * (size_t)k_cap + m + (1u << kSelHistBits) + kSelGatherCap + 1) * 4;
+      return ((size_t)k_cap + m + std::max((size_t)k_cap, (size_t)mask_words(slots_cap))) * 4;
   }
 }
 

@@ -408,6 +408,43 @@ def test_selection_clustered_scores(mode):
     print(mode, stats)
 
 
+@pytest.mark.parametrize("mode", ["all_equal", "two_values_outliers", "dense_cluster_outliers", "few_non_zero", "last_bin"])
+def test_mask_selection_clustered_scores(mode):
+    """Designed scores (component 0 of the keys, as in the test above) for the bit-mask selection of rows
+    that are read from global memory (flat, 45056 tokens): all equal (every key in one bin, ties by
+    position), two values or 128 values of many ties beside outliers (the bin overflows, narrowed passes),
+    zero for all but 40 tokens, and more outliers above the sampled range than are selected. Rows at the end
+    of the cache and rows with few or fewer candidates than K_sparse, against the oracle."""
+    w = replace(W.L2K_MQA, name=f"mask_{mode}", keep_pages=0, seq_len=45056, k_sparse=1500)
+    n, H, d = w.seq_len, w.n_heads, w.head_dim
+    q = np.zeros((n, H, d), np.float32)
+    q[:, :, 0] = 1.0
+    kb = np.zeros((n, d), np.uint16)
+    s = np.arange(n)
+    g = np.random.default_rng(23)
+    if mode == "all_equal":
+        kb[:, 0] = 0x3F80
+    elif mode == "two_values_outliers":
+        kb[:, 0] = 0x3F80 + (s % 2)
+        kb[s % 61 == 5, 0] = 0x4700
+    elif mode == "dense_cluster_outliers":
+        kb[:, 0] = 0x3F80 + (s % 128)
+        kb[s % 61 == 5, 0] = 0x4700
+    elif mode == "few_non_zero":
+        kb[g.choice(n, 40, replace=False), 0] = 0x3F80
+    else:
+        kb[:, 0] = 0x3F80
+        kb[g.choice(n, 1600, replace=False), 0] = 0x4000 + g.integers(0, 200, 1600)
+    inp = dict(q=synth.to_bf16_bits(q), w=np.ones((n, H), np.float32), k=kb, k_scale=None)
+    for q0, nq in ((n - 12, 12), (150, 8), (1700, 8)):
+        out, _ = _run_prefill(w, inp, q_start=q0, n_q=nq, pages=False)
+        rows = list(range(q0, q0 + nq))
+        res = _oracle_rows(w, inp, rows)
+        stats = P.check_index_rows(w, rows, out["idx"], out["count"], None, res)
+        P.check_runs(out["runs"], out["run_count"], out["idx"], out["count"], w.run_align)
+        assert stats["exact"] == stats["rows"], (q0, stats)
+
+
 def test_fine_scoring_orders_every_fp8_code():
     """The fine stage widens fp8 keys to bf16 on the GPU. Designed case: each eligible token carries
     one distinct e4m3fn code in component 0 (all 254 non-NaN codes, in seeded random positions),
