@@ -347,81 +347,116 @@ __device__ __forceinline__ void lds_dma(const void* base, uint32_t off, uint32_t
 __device__ __forceinline__ void lds_read_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // ============================================================================ Stage 1: coarse page scores
-// Eq. (9), or Eq. (13) with MINMAX. Grid: (ceil(n_rows / R), chunks). Each wave takes tiles of 32
-// block keys of the chunk; R query rows share each loaded tile (prefill). Output: order keys of
-// the page scores, page_keys[row * ld + p] for eligible pages p.
-// STAGED (prefill mean keys, rows of at most kCoarseStagedTiles tiles; the tile's 32 block keys are
-// consecutive rows of the cache): one wave per workgroup takes every tile of its R rows, the rows
-// with the most eligible pages first so that the long workgroups do not form the tail of the
-// launch; it copies its next tile into its own LDS buffer by direct loads while it scores the
-// current one, whole key rows per 16 (or 8) consecutive lanes, so that a load touches 4 (or 8)
-// rows instead of one row per lane; granule c of row t sits at slot c ^ coarse_swz(t) of the row,
-// which keeps the operand reads (16 rows, one granule) free of bank conflicts. Otherwise four waves
-// share the tiles of R rows and read the keys straight into the operand layout (long rows: the
-// block keys no longer fit the L2, and four rows per tile read them fewer times).
-constexpr int kCoarseRowsStaged = 3;   // query rows of a staged workgroup (register budget)
-constexpr int kCoarseStagedTiles = 64; // longest row (in 32-key tiles) taken by the staged kernel
-template <int GR>  // 16-byte granules per key row: 16 (d = 128) or 8 (d = 64)
-__device__ __forceinline__ int coarse_swz(int t) { return GR == 16 ? (t & 15) : ((t >> 1) & 7); }
+// Sub-blocks of a page: 1 to 32 of them, consecutive block keys (a 32-bit shift where their number is a
+// power of two: n_kv < 2^31).
+struct SubBlocks {
+  int n, lg;  // sub-blocks per page; log2 or -1
+  __device__ __forceinline__ explicit SubBlocks(const IndexGeom& g) : n(g.P / g.B) { lg = (n & (n - 1)) == 0 ? __ffs(n) - 1 : -1; }
+  __device__ __forceinline__ void split(uint32_t sb, int& page, int& sub) const {
+    page = lg >= 0 ? (int)(sb >> lg) : (int)(sb / (uint32_t)n);
+    sub = (int)sb - page * n;
+  }
+  // sum over a page's lanes (aligned groups of n, the butterfly over lanes ^1, ^2, .., ^16), by register
+  // exchanges: quads and the mirrors of half rows and rows, whose lanes hold equal sums by then, then
+  // the row swap. (An LDS permute per step made four dependent round trips per row and tile at n = 16.)
+  __device__ __forceinline__ float sum(float v) const {
+    auto dpp = [](float x, auto ctrl) {
+      return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    if (n > 1) v += dpp(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+    if (n > 2) v += dpp(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+    if (n > 4) v += dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    if (n > 8) v += dpp(v, std::integral_constant<int, 0x140>{});  // row_mirror
+    if (n > 16) {
+      const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+      v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    }
+    return v;
+  }
+};
 
-template <int D, int R, bool PAGED, bool MINMAX, bool STAGED = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void coarse_kernel(IndexGeom g, int64_t n_rows, const uint16_t* __restrict__ q,
-                                                     const float* __restrict__ w, const uint16_t* __restrict__ kmean,
-                                                     uint32_t* __restrict__ page_keys, int64_t ld, int tiles_per_chunk) {
+// Eq. (9), or Eq. (13) with MINMAX, paged cache (decode). Grid: (rows, chunks of 8 tiles of 32 block keys).
+// Output: order keys of the page scores, page_keys[row * ld + p] for eligible pages p.
+template <int D, bool MINMAX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void coarse_paged_kernel(
+    IndexGeom g, const uint16_t* __restrict__ q, const float* __restrict__ w, const uint16_t* __restrict__ kmean,
+    uint32_t* __restrict__ page_keys, int64_t ld, int tiles_per_chunk) {
   constexpr int DK = MINMAX ? 2 * D : D;  // width of a block key and of the dot product
   constexpr int KS = DK / 16;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, j = lane & 31;
-  static_assert(!STAGED || (!PAGED && !MINMAX), "staged tiles are consecutive mean keys");
-  const int64_t row0 = (int64_t)(STAGED ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * R;
-  const int nsub = g.P / g.B;
-
-  if constexpr (PAGED) {
-    // Decode: one row, chunks of 8 tiles, wave wv scoring tiles wv and wv + 4 of its chunk. The
-    // page-table entries of both tiles and the query are requested before the context length is
-    // known (any page below max_pages lies inside the sequence's table row), and both tiles' block
-    // keys together, so the scores wait for two round trips instead of four. Pages past the
-    // row's eligible range are scored but not stored.
-    static_assert(R == 1 && !STAGED, "paged scoring takes one row per workgroup");
-    const int64_t row = row0, p_base = g.k_sink / g.P;  // first eligible page (k_sink only)
-    const int64_t tile_beg = (int64_t)blockIdx.y * tiles_per_chunk;
-    int64_t pp[2], ph[2];
-    int sub[2];
+  const SubBlocks subs(g);
+  const int nsub = subs.n;
+  // Decode: one row, chunks of 8 tiles, wave wv scoring tiles wv and wv + 4 of its chunk. The
+  // page-table entries of both tiles and the query are requested before the context length is
+  // known (any page below max_pages lies inside the sequence's table row), and both tiles' block
+  // keys together, so the scores wait for two round trips instead of four. Pages past the
+  // row's eligible range are scored but not stored.
+  const int64_t row = blockIdx.x, p_base = g.k_sink / g.P;  // first eligible page (k_sink only)
+  const int64_t tile_beg = (int64_t)blockIdx.y * tiles_per_chunk;
+  int64_t pp[2], ph[2];
+  int sub[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t sb = (tile_beg + wv + 4 * u) * 32 + j;  // sub-block counted from the first eligible page
-      pp[u] = p_base + sb / nsub;
-      sub[u] = (int)(sb % nsub);
-      ph[u] = phys_page(g, row, pp[u]);
-    }
-    u32x4 a[KS];
-    float wr[16];
-    if constexpr (MINMAX) load_query_minmax<D>(q, g.H, row, lane, a);
-    else load_query_operand<D>(q, g.H, row, lane, a);
-    load_head_weights(w, g.H, row, lane, wr);
-    const RowInfo ri = row_info(g, row);
-    if (!ri.valid || ri.p_hi < ri.p_lo) return;
-    const int64_t n_tiles = ((ri.p_hi - ri.p_lo + 1) * nsub + 31) / 32;
-    u32x4 b[2][KS];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t mrow = ph[u] >= 0 ? ph[u] * nsub + sub[u] : 0;
-      const u32x4* pk = reinterpret_cast<const u32x4*>(kmean + mrow * DK + (DK / 2) * (lane >> 5));
-#pragma unroll
-      for (int s = 0; s < KS; ++s) b[u][s] = pk[s];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t tile = tile_beg + wv + 4 * u;
-      if (4 * u + wv >= tiles_per_chunk || tile >= n_tiles) break;  // (wave-uniform)
-      f32x16 acc = {};
-#pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma32(a[s], b[u][s], acc);
-      float v = head_reduce(acc, wr);
-      for (int o = 1; o < nsub; o <<= 1) v += __shfl_xor(v, o);  // sum the sub-blocks of a page
-      if (lane < 32 && sub[u] == 0 && pp[u] <= ri.p_hi) page_keys[row * ld + pp[u]] = ph[u] >= 0 ? score_key(v) : 0u;
-    }
-    return;
+  for (int u = 0; u < 2; ++u) {
+    int page;
+    subs.split((uint32_t)(tile_beg + wv + 4 * u) * 32 + j, page, sub[u]);  // sub-block counted from the first eligible page
+    pp[u] = p_base + page;
+    ph[u] = phys_page(g, row, pp[u]);
   }
+  u32x4 a[KS];
+  float wr[16];
+  if constexpr (MINMAX) load_query_minmax<D>(q, g.H, row, lane, a);
+  else load_query_operand<D>(q, g.H, row, lane, a);
+  load_head_weights(w, g.H, row, lane, wr);
+  const RowInfo ri = row_info(g, row);
+  if (!ri.valid || ri.p_hi < ri.p_lo) return;
+  const int64_t n_tiles = ((ri.p_hi - ri.p_lo + 1) * nsub + 31) / 32;
+  u32x4 b[2][KS];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int64_t mrow = ph[u] >= 0 ? ph[u] * nsub + sub[u] : 0;
+    const u32x4* pk = reinterpret_cast<const u32x4*>(kmean + mrow * DK + (DK / 2) * (lane >> 5));
+#pragma unroll
+    for (int s = 0; s < KS; ++s) b[u][s] = pk[s];
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int64_t tile = tile_beg + wv + 4 * u;
+    if (4 * u + wv >= tiles_per_chunk || tile >= n_tiles) break;  // (wave-uniform)
+    f32x16 acc = {};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc = mfma32(a[s], b[u][s], acc);
+    const float v = subs.sum(head_reduce(acc, wr));
+    if (lane < 32 && sub[u] == 0 && pp[u] <= ri.p_hi) page_keys[row * ld + pp[u]] = ph[u] >= 0 ? score_key(v) : 0u;
+  }
+}
+
+// The same for prefill. Grid: (groups of R query rows, chunks of tiles), NW waves per workgroup taking
+// the chunk's 32-key tiles in turn for all R rows; the last rows (the most eligible pages) first, so that
+// the long workgroups do not form the tail of the launch. Each wave copies its next tile (consecutive rows of
+// the cache) into its own LDS buffer by direct loads while it scores the current one: whole key rows per
+// consecutive lanes, so that a load touches 2 to 8 rows instead of one row per lane; granule c of row t sits
+// at slot c ^ coarse_swz(t) of the row, which keeps the operand reads (16 rows, one granule) free of bank
+// conflicts. With NBUF = 1 the next tile is requested once the current one is in registers.
+template <int GR>  // 16-byte granules per key row: 32, 16 or 8
+__device__ __forceinline__ int coarse_swz(int t) { return GR >= 16 ? (t & 15) : ((t >> 1) & 7); }
+
+template <int D, int R, bool MINMAX, int NW, int NBUF>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void coarse_kernel(
+    IndexGeom g, int64_t n_rows, const uint16_t* __restrict__ q, const float* __restrict__ w,
+    const uint16_t* __restrict__ kmean, uint32_t* __restrict__ page_keys, int64_t ld, int tiles_per_chunk) {
+  constexpr int DK = MINMAX ? 2 * D : D;  // width of a block key and of the dot product
+  constexpr int KS = DK / 16;
+  constexpr int RB = DK * 2, GR = RB / 16;  // key row bytes, granules
+  constexpr int NDMA = 32 * RB / 1024;      // direct loads per tile (1 KB each)
+  constexpr int RPL = 1024 / RB;            // key rows per load
+  // one buffer per wave: the head weights are read from LDS for every product instead of held in registers
+  constexpr bool WLDS = NBUF == 1;
+  __shared__ __attribute__((aligned(16))) uint8_t csm[NW][NBUF][32 * RB];
+  __shared__ __attribute__((aligned(16))) float wsm[WLDS ? NW : 1][R][32];
+  const int lane = threadIdx.x & 63, j = lane & 31;
+  const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int64_t row0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * R;
+  const SubBlocks subs(g);
 
   RowInfo ri[R];
   int64_t max_tiles = 0;
@@ -430,105 +465,115 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     const int64_t row = row0 + r;
     ri[r] = row < n_rows ? row_info(g, row) : RowInfo{0, 0, 1, 0, 0, -1};
     if (ri[r].valid && ri[r].p_hi >= ri[r].p_lo) {
-      const int64_t nt = ((ri[r].p_hi - ri[r].p_lo + 1) * nsub + 31) / 32;
+      const int64_t nt = ((ri[r].p_hi - ri[r].p_lo + 1) * subs.n + 31) / 32;
       max_tiles = nt > max_tiles ? nt : max_tiles;
     }
   }
-  const int64_t tile_beg = (int64_t)blockIdx.y * tiles_per_chunk;
-  const int64_t tile_end = tile_beg + tiles_per_chunk < max_tiles ? tile_beg + tiles_per_chunk : max_tiles;
-  if (tile_beg >= tile_end) return;
+  const int tile_beg = (int)blockIdx.y * tiles_per_chunk + wv;
+  const int chunk_end = ((int)blockIdx.y + 1) * tiles_per_chunk;
+  const int tile_end = chunk_end < max_tiles ? chunk_end : (int)max_tiles;
+  if (tile_beg >= tile_end) return;  // (no barrier below)
 
   u32x4 a[R][KS];
-  float wr[R][16];
+  float wr[WLDS ? 1 : R][16];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t row = row0 + r < n_rows ? row0 + r : n_rows - 1;
     if constexpr (MINMAX) load_query_minmax<D>(q, g.H, row, lane, a[r]);
     else load_query_operand<D>(q, g.H, row, lane, a[r]);
-    load_head_weights(w, g.H, row, lane, wr[r]);
+    if constexpr (!WLDS) load_head_weights(w, g.H, row, lane, wr[r]);
+    else if (lane < 32) wsm[wv][r][lane] = lane < g.H ? w[row * g.H + lane] : 0.f;  // (this wave's own copy)
   }
-  const int64_t p_base = ri[0].p_lo;  // identical for every row (depends on k_sink only)
+  const int p_base = (int)(g.k_sink / g.P);  // first eligible page of every row
 
-  if constexpr (STAGED) {  // (the launcher checks 0 < n_sub and n_sub * row bytes < 2^32)
-    constexpr int RB = DK * 2, GR = RB / 16;  // key row bytes, granules
-    constexpr int NDMA = 32 * RB / 1024;      // direct loads per tile (1 KB each)
-    constexpr int RPL = 1024 / RB;            // key rows per load
-    __shared__ __attribute__((aligned(16))) uint8_t csm[2][32 * RB];
-    const int64_t row_lim = g.n_sub - 1;      // (rows past the cache are loaded clamped, scored as 0)
-    // load slot: lane -> key row RPL m + lane / GR of the tile, granule (lane % GR) ^ swz(row)
-    const int tl = lane / GR, cl = lane % GR;
-    const uint8_t* base = reinterpret_cast<const uint8_t*>(kmean);  // byte offsets fit 32 bits (host check)
-    auto issue = [&](int64_t tile, int buf) {
-      const int64_t r0 = p_base * nsub + tile * 32;
-      const uint32_t lds = lds_addr(&csm[buf][0]);
+  // load m: lane -> key row RPL m + lane / GR of the tile, granule (lane % GR) ^ swz(row); rows past the
+  // cache are loaded clamped and scored as 0
+  const int tl = lane / GR, cl = lane % GR;
+  const uint32_t v0 = (uint32_t)(tl * RB + 16 * (cl ^ coarse_swz<GR>(tl)));  // load 0; load m: XOR of swz(RPL m)
+  auto issue = [&](int tile, int buf) {
+    const int64_t r0 = (int64_t)p_base * subs.n + (int64_t)tile * 32;
+    const uint32_t lds = lds_addr(&csm[wv][buf][0]);
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(kmean);
+    if (r0 + 32 <= g.n_sub) {
+      base += r0 * RB;
+      uint32_t v = v0;
+      asm volatile("" : "+v"(v));  // (one register, not one per load)
 #pragma unroll
+      for (int m = 0; m < NDMA; ++m)
+        lds_dma<16>(base + 1024 * m, v ^ (uint32_t)(16 * coarse_swz<GR>(RPL * m)), lds + 1024 * m);
+    } else {
+      const int64_t rb = r0 < g.n_sub ? r0 : g.n_sub - 1;
+      const int lim = (int)(g.n_sub - 1 - rb);
+      base += rb * RB;
       for (int m = 0; m < NDMA; ++m) {
         const int t = RPL * m + tl;
-        const int64_t rr = r0 + t < row_lim ? r0 + t : row_lim;
-        const uint32_t off = (uint32_t)(rr * RB + 16 * (cl ^ coarse_swz<GR>(t)));
-        lds_dma<16>(base, off, lds + 1024 * m);
+        lds_dma<16>(base, (uint32_t)((t < lim ? t : lim) * RB + 16 * (cl ^ coarse_swz<GR>(t))), lds + 1024 * m);
       }
-    };
-    // operand read: lane (j, h) at k-step s takes granule (GR / 2) h + s of key row j
-    const uint32_t rd = (uint32_t)(j * RB);
-    const int swz_j = coarse_swz<GR>(j), h = lane >> 5;
-    int buf = 0;
-    issue(tile_beg, 0);
-    for (int64_t tile = tile_beg; tile < tile_end; ++tile) {
-      const bool more = tile + 1 < tile_end;
-      if (more) issue(tile + 1, buf ^ 1);
-      if (more) vm_wait<NDMA>();  // this tile's loads (and earlier stores) are done
-      else vm_wait<0>();
-      const uint8_t* tb = &csm[buf][0];
-      u32x4 b[KS];
+    }
+  };
+  // operand read: lane (j, h) at k-step s takes granule (GR / 2) h + s of key row j
+  const uint32_t rd = (uint32_t)(j * RB);
+  const int swz_j = coarse_swz<GR>(j), h = lane >> 5;
+  int buf = 0;
+  issue(tile_beg, 0);
+  for (int tile = tile_beg; tile < tile_end; tile += NW) {
+    const bool more = tile + NW < tile_end;
+    if (NBUF == 2 && more) {
+      issue(tile + NW, buf ^ 1);
+      vm_wait<NDMA>();  // this tile's loads (and earlier stores) are done
+    } else {
+      vm_wait<0>();
+    }
+    const uint8_t* tb = &csm[wv][buf][0];
+    // key operands, KB k-steps at a time (min-max at D = 128: in two halves, for the registers)
+    constexpr int KB = KS > 8 ? KS / 2 : KS;
+    u32x4 b[KB];
+    auto read_b = [&](int s0) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s)
-        b[s] = *reinterpret_cast<const u32x4*>(tb + rd + 16 * ((((GR / 2) * h) + s) ^ swz_j));
-      const int64_t sb = tile * 32 + j;
-      const int64_t p = p_base + sb / nsub;
-      const int sub_in_page = (int)(sb % nsub);
-      const bool okp = p * nsub + sub_in_page < g.n_sub;
+      for (int s = 0; s < KB; ++s)
+        b[s] = *reinterpret_cast<const u32x4*>(tb + rd + 16 * ((((GR / 2) * h) + s0 + s) ^ swz_j));
+    };
+    read_b(0);
+    f32x16 half[KB < KS ? R : 1];
+    if constexpr (KB < KS) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        f32x16 acc = {};
+        half[r] = f32x16{};
 #pragma unroll
-        for (int s = 0; s < KS; ++s) acc = mfma32(a[r][s], b[s], acc);
-        float v = head_reduce(acc, wr[r]);
-        for (int o = 1; o < nsub; o <<= 1) v += __shfl_xor(v, o);  // sum the sub-blocks of a page
-        const int64_t row = row0 + r;
-        if (lane < 32 && sub_in_page == 0 && row < n_rows && ri[r].valid && p <= ri[r].p_hi)
-          page_keys[row * ld + p] = okp ? score_key(v) : 0u;
+        for (int s = 0; s < KB; ++s) half[r] = mfma32(a[r][s], b[s], half[r]);
       }
-      lds_read_wait();  // the operand reads of this buffer are done before it is refilled
-      buf ^= 1;
+      read_b(KB);
     }
-    return;
-  }
-
-  for (int64_t tile = tile_beg + wv; tile < tile_end; tile += 4) {
-    const int64_t sb = tile * 32 + j;            // sub-block counted from the first eligible page
-    const int64_t p = p_base + sb / nsub;
-    const int sub_in_page = (int)(sb % nsub);
-    int64_t mrow = 0;
-    bool okp = true;
-    okp = p * nsub + sub_in_page < g.n_sub;
-    mrow = okp ? p * nsub + sub_in_page : 0;
-    u32x4 b[KS];
-    {
-      const u32x4* pk = reinterpret_cast<const u32x4*>(kmean + mrow * DK + (DK / 2) * (lane >> 5));
-#pragma unroll
-      for (int s = 0; s < KS; ++s) b[s] = pk[s];
+    if (NBUF == 1) {
+      lds_read_wait();  // the operand reads are done before the buffer is refilled
+      if (more) issue(tile + NW, 0);
     }
+    int page, sub_in_page;
+    subs.split((uint32_t)tile * 32 + j, page, sub_in_page);
+    const int p = p_base + page;
+    const bool okp = (int64_t)p * subs.n + sub_in_page < g.n_sub;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       f32x16 acc = {};
+      if constexpr (KB < KS) acc = half[r];
 #pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma32(a[r][s], b[s], acc);
-      float v = head_reduce(acc, wr[r]);
-      for (int o = 1; o < nsub; o <<= 1) v += __shfl_xor(v, o);  // sum the sub-blocks of a page
+      for (int s = KS - KB; s < KS; ++s) acc = mfma32(a[r][s], b[s - (KS - KB)], acc);
+      if constexpr (WLDS) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const f32x4 h4 = *reinterpret_cast<const f32x4*>(&wsm[wv][r][8 * x + 4 * h]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) wr[0][4 * x + e] = h4[e];
+        }
+      }
+      const float v = subs.sum(head_reduce(acc, wr[WLDS ? 0 : r]));
       const int64_t row = row0 + r;
       if (lane < 32 && sub_in_page == 0 && row < n_rows && ri[r].valid && p <= ri[r].p_hi)
         page_keys[row * ld + p] = okp ? score_key(v) : 0u;
+    }
+    if (NBUF == 2) {
+      lds_read_wait();
+      buf ^= 1;
     }
   }
 }
@@ -2006,51 +2051,54 @@ hipError_t launch_block_keys(int64_t n_items, const int64_t* rows, int64_t n_tok
 
 // Prefill calls of few rows split each row group's tiles into chunks (grid y) until the launch has
 // `fill` workgroups, of at least `least` tiles each: every chunk loads its rows' query operands
-// again, so no more of them than fill the GPU. Four-wave kernel: 512 rows of 4096 tiles (1M tokens,
-// B = 8) took 2570 us in 128 workgroups, 770 in 512, 770 to 850 in 1024 to 4096; min-max rows of 32
-// tiles lost 20% to two chunks of 16 (82 to 98 us at 2000 rows). Staged kernel, 16-tile rows: 100 rows
-// 21.4 us whole, 10.0 in chunks of 4, 7.1 in chunks of 2; 901 rows 22.5, 13.8 and 19.5, so 1024
-// workgroups suffice (4096 rows of 14 tiles: 35 us whole, 42 in halves).
+// again, so no more of them than fill the GPU. Long rows (four waves, one LDS buffer): 512 rows of 4096
+// tiles (1M tokens, B = 8) 639 us in 512 workgroups, 634 in 1024, and 64 rows 48 in chunks of 64 tiles, 65 of
+// 128. Short rows (one wave, two buffers), 16 tiles: 100 rows 21.4 us whole, 10.0 in chunks of 4, 7.1 in
+// chunks of 2; 901 rows 22.5, 13.8 and 19.5, so 1024 workgroups suffice (4096 rows of 14 tiles: 35 us whole,
+// 42 in halves). Min-max, 32 tiles: 2000 rows 57.6 whole, 42.8 in halves, 49.9 in quarters; 200 rows 12.8 in
+// chunks of 4, 11.1 of 2. Reading the keys straight into the operand layout (one key row per lane and load,
+// each wave waiting for its own loads), with a 64-bit division per tile and an LDS permute per step of the
+// page sums, long rows took 770 us (512 rows) and 3070 (2048 rows, now 2195), min-max 82 (2000 rows, now 43)
+// and 307 (8192 rows, now 150).
+constexpr int kCoarseShortTiles = 64;
 constexpr int64_t kCoarseFill = 512;
 constexpr int kCoarseMin = 64;
 constexpr int64_t kCoarseStagedFill = 1024;
 constexpr int kCoarseStagedMin = 2;
+constexpr int64_t kCoarseMinmaxFill = 1024;
+constexpr int kCoarseMinmaxMin = 2;
 static int coarse_chunk(int64_t groups, int64_t max_tiles, int64_t fill, int least) {
   int64_t per = max_tiles;
   while (per > least && groups * ((max_tiles + per - 1) / per) < fill) per = (per + 1) / 2;
   return (int)per;
 }
-template <int D, int R, bool PAGED, bool MINMAX>
-static hipError_t launch_coarse_t(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w,
-                                  const uint16_t* kmean, uint32_t* page_keys, int64_t ld, int64_t max_tiles,
-                                  hipStream_t st) {
-  if (max_tiles <= 0 || n_rows == 0) return hipSuccess;
-  if (!PAGED && !MINMAX && max_tiles <= kCoarseStagedTiles && g.n_sub > 0 &&
-      g.n_sub <= ((int64_t)1 << 32) / D / 2) {  // one wave per workgroup, all tiles of its rows
-    constexpr int RS = kCoarseRowsStaged;
-    const int64_t groups = (n_rows + RS - 1) / RS;
-    const int per = coarse_chunk(groups, max_tiles, kCoarseStagedFill, kCoarseStagedMin);
-    const dim3 grid((unsigned)groups, (unsigned)((max_tiles + per - 1) / per));
-    hipLaunchKernelGGL((coarse_kernel<D, RS, false, false, true>), grid, dim3(64), 0, st, g, n_rows, q, w, kmean,
-                       page_keys, ld, per);
-    return hipGetLastError();
-  }
-  const int tiles_per_chunk = PAGED ? 8 : coarse_chunk((n_rows + R - 1) / R, max_tiles, kCoarseFill, kCoarseMin);
-  const int64_t chunks = (max_tiles + tiles_per_chunk - 1) / tiles_per_chunk;
-  const dim3 grid((unsigned)((n_rows + R - 1) / R), (unsigned)chunks);
-  hipLaunchKernelGGL((coarse_kernel<D, R, PAGED, MINMAX>), grid, dim3(256), 0, st, g, n_rows, q, w, kmean, page_keys,
-                     ld, tiles_per_chunk);
-  return hipGetLastError();
+template <int D, int R, bool MINMAX, int NW, int NBUF>
+static void launch_coarse_t(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w, const uint16_t* kmean,
+                            uint32_t* page_keys, int64_t ld, int64_t max_tiles, int64_t fill, int least, hipStream_t st) {
+  const int64_t groups = (n_rows + R - 1) / R;
+  const int per = coarse_chunk(groups, max_tiles, fill, least);
+  const dim3 grid((unsigned)groups, (unsigned)((max_tiles + per - 1) / per));
+  hipLaunchKernelGGL((coarse_kernel<D, R, MINMAX, NW, NBUF>), grid, dim3(64 * NW), 0, st, g, n_rows, q, w, kmean, page_keys,
+                     ld, per);
 }
 
 template <int D, bool MINMAX>
 static hipError_t launch_coarse_d(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w,
                                   const uint16_t* kmean, uint32_t* page_keys, int64_t ld, int64_t max_tiles,
                                   hipStream_t st) {
-  // min-max doubles the operands' width: fewer query rows share a tile (register budget)
-  constexpr int R = MINMAX ? 2 : 4;
-  return g.ctx_len != nullptr ? launch_coarse_t<D, 1, true, MINMAX>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, st)
-                              : launch_coarse_t<D, R, false, MINMAX>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, st);
+  if (max_tiles <= 0 || n_rows == 0) return hipSuccess;
+  if (g.ctx_len != nullptr) {
+    const int per = 8;  // tiles per workgroup
+    hipLaunchKernelGGL((coarse_paged_kernel<D, MINMAX>), dim3((unsigned)n_rows, (unsigned)((max_tiles + per - 1) / per)), dim3(256),
+                       0, st, g, q, w, kmean, page_keys, ld, per);
+  } else if constexpr (MINMAX) {  // operands of twice the width: two query rows (registers), one LDS buffer
+    launch_coarse_t<D, 2, true, 1, 1>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, kCoarseMinmaxFill, kCoarseMinmaxMin, st);
+  } else if (max_tiles <= kCoarseShortTiles) {
+    launch_coarse_t<D, 3, false, 1, 2>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, kCoarseStagedFill, kCoarseStagedMin, st);
+  } else {  // long rows: four query rows read the block keys fewer times
+    launch_coarse_t<D, 4, false, 4, 1>(g, n_rows, q, w, kmean, page_keys, ld, max_tiles, kCoarseFill, kCoarseMin, st);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_coarse(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w, const uint16_t* kmean,
