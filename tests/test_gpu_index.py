@@ -491,18 +491,18 @@ def test_chunked_equals_single_call():
         P.assert_same_index_outputs(part, whole, slice(q0, q0 + nq))
 
 
-@pytest.mark.parametrize("w", [W.SMALL_CHUNKED, W.SMALL_MINMAX_B8, replace(W.SMALL_MLA, name="d64_B2", head_dim=64, sub_block=2, seq_len=8192)],
-                         ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [W.SMALL_CHUNKED, W.SMALL_MINMAX_B8, replace(W.SMALL_MLA, name="d64_B2", head_dim=64, sub_block=2, seq_len=8192),
+                               replace(W.SMALL_MLA, name="flat", keep_pages=0, seq_len=8300)], ids=lambda w: w.name)
 def test_few_rows_equal_single_call(w):
     """Calls of few rows split a row's coarse tiles over several workgroups and its recalled pages over
     several waves per XCD: the counts on both sides of each switch (1 to 257 rows: eight waves down to one;
     one and two rows per wave at 8192 rows in the whole call), staged, four-wave and min-max coarse kernels,
-    equal the same rows of one call over the whole sequence."""
+    and flat scoring's key chunks, equal the same rows of one call over the whole sequence."""
     inp = P.prefill_inputs(w)
-    whole, _ = _run_prefill(w, inp)
+    whole, _ = _run_prefill(w, inp, pages=w.keep_pages > 0)
     for nq in (1, 3, 31, 33, 63, 65, 127, 129, 255, 257):
         q0 = w.seq_len - nq - 5
-        part, _ = _run_prefill(w, inp, q_start=q0, n_q=nq)
+        part, _ = _run_prefill(w, inp, q_start=q0, n_q=nq, pages=w.keep_pages > 0)
         P.assert_same_index_outputs(part, whole, slice(q0, q0 + nq))
 
 
