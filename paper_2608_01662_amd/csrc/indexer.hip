@@ -973,39 +973,58 @@ __global__ __launch_bounds__(NT) void page_select_kernel(IndexGeom g, int64_t n_
 }
 
 // ============================================================================ Stage 2: fine token scores
+// Staged key chunks of both fine kernels: a page's keys are one contiguous block of P rows, copied into LDS
+// up to kFineChunk rows at a time by direct loads in which the 16-byte granules of one key row go to
+// consecutive lanes (a few cache lines per load instead of one line per lane); granule c of row t is
+// stored at slot c ^ swz(t) so that the operand reads are conflict-free.
+template <int D, bool FP8>
+__device__ __forceinline__ int fine_swz(int t) {
+  constexpr int RB = FP8 ? D : 2 * D;  // key row bytes
+  constexpr int GR = RB / 16;          // 16-byte granules per row
+  return RB >= 128 ? (t & 7) : ((t >> (7 - __builtin_ctz(RB))) & (GR - 1));
+}
+
+constexpr int kFineChunk = 64;  // key rows staged in LDS at a time
+
 // Eq. (11) over the recalled pages (Eq. 1 over E_t in flat mode), decode variant (paged cache).
-// Grid: (n_rows, chunks of pages_per_wg pages); each wave scores whole pages in 32-token MFMA
-// tiles. Output: fine_keys[row * ldf + k * P + offset] = order key of the score of position
-// page_k * P + offset, or 0 for positions outside E_t.
+// Grid: (n_rows, chunks of kFinePagesPerWg pages); each wave scores whole pages, every fourth of the chunk, in
+// 64-key chunks of two 32-key tiles. Output: fine_keys[row * ldf + k * P + offset] = order key of the score of
+// position page_k * P + offset, or 0 for positions outside E_t.
 // Hierarchical mode reads the k-th recalled page from pages[row * M + k] and its physical page
 // from phys[row * ldp + k] (written by the page selection); flat mode (phys == nullptr) takes the
 // eligible pages in order and looks their physical pages up in the page table. The page ids, the
 // physical pages and the query are requested before the row's context length is known (every
-// such read stays inside its array), so that the first key tile waits for one round trip after
-// them, not for a chain of context length, page, page-table entry and keys.
+// such read stays inside its array), so that the first keys wait for one round trip after
+// them, not for a chain of context length, page, page-table entry and keys; the first chunk is on its way while
+// the query is split into its fp8 terms, and the next chunk while one is scored. Whole key rows per eight
+// lanes: with one row per lane and load, 1 sequence took 8.3 us (now 6.6), 64 of 16K to 128K 17.8 (17.2), 96 of 2K
+// to 9K 23.9 (20.8), 16 with bf16 keys 9.7 (8.2).
+constexpr int kFinePagesPerWave = 2;
+constexpr int kFinePagesPerWg = 4 * kFinePagesPerWave;
 template <int D, bool FP8>
-__global__ __launch_bounds__(256) void fine_kernel(IndexGeom g, int64_t n_rows, const uint16_t* __restrict__ q,
-                                                   const float* __restrict__ w, const void* __restrict__ k,
-                                                   const float* __restrict__ kscale, const int32_t* __restrict__ pages,
-                                                   const int32_t* __restrict__ phys, int64_t ldp,
-                                                   uint32_t* __restrict__ fine_keys, int64_t ldf, int pages_per_wg) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP8 || D == 64 ? 4 : 2, 8))) void fine_kernel(IndexGeom g, const uint16_t* __restrict__ q, const float* __restrict__ w,
+                                                   const void* __restrict__ k, const float* __restrict__ kscale,
+                                                   const int32_t* __restrict__ pages, const int32_t* __restrict__ phys,
+                                                   int64_t ldp, uint32_t* __restrict__ fine_keys, int64_t ldf) {
   constexpr int KS = D / 16;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, j = lane & 31;
+  constexpr int RB = FP8 ? D : 2 * D;        // key row bytes
+  constexpr int GR = RB / 16;                // 16-byte granules per row
+  constexpr int LG = FP8 ? D / 32 : D / 16;  // 16-byte granules per lane per tile
+  __shared__ __attribute__((aligned(16))) uint8_t fsm[4][kFineChunk * RB];
+  __shared__ float lsc[4][kFineChunk];
+  const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row = blockIdx.x;
   const bool flat = g.M <= 0;
-  const int64_t k0 = (int64_t)blockIdx.y * pages_per_wg;
-  // this wave's first two pages (every fourth of the chunk, two at a time; see below): ids and
-  // physical pages requested up front (slots below min(M, ldp) are inside the row's arrays)
-  int32_t pg_pre[2] = {-1, -1}, ph_pre[2] = {-1, -1};
-  if (!flat) {
-    const int64_t lim = g.M < ldp ? g.M : ldp;
+  const int k0 = (int)blockIdx.y * kFinePagesPerWg + wv;
+  int pg[kFinePagesPerWave], ph[kFinePagesPerWave];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t kk = k0 + wv + 4 * u;
-      if (kk < lim) {
-        pg_pre[u] = pages[row * g.M + kk];
-        ph_pre[u] = phys[row * ldp + kk];
-      }
+  for (int u = 0; u < kFinePagesPerWave; ++u) {
+    const int kk = k0 + 4 * u;
+    pg[u] = ph[u] = -1;
+    if (!flat && kk < (g.M < ldp ? g.M : ldp)) {  // (slots inside the row's arrays)
+      pg[u] = pages[row * g.M + kk];
+      ph[u] = phys[row * ldp + kk];
     }
   }
   u32x4 a[KS];
@@ -1016,87 +1035,87 @@ __global__ __launch_bounds__(256) void fine_kernel(IndexGeom g, int64_t n_rows, 
   const RowInfo ri = row_info(g, row);
   if (!ri.valid || ri.p_hi < ri.p_lo) return;
   const int64_t n_elig = ri.p_hi - ri.p_lo + 1;
-  const int64_t n_sel = flat ? n_elig : (n_elig < g.M ? n_elig : g.M);
-  const int64_t k1 = k0 + pages_per_wg < n_sel ? k0 + pages_per_wg : n_sel;
-  if (k0 >= k1) return;
+  const int n_sel = (int)(flat ? n_elig : (n_elig < g.M ? n_elig : g.M));
+  if (k0 >= n_sel) return;  // (no barrier below)
+#pragma unroll
+  for (int u = 0; u < kFinePagesPerWave; ++u) {
+    const int kk = k0 + 4 * u;
+    if (kk >= n_sel) {
+      ph[u] = -1;
+    } else if (flat) {
+      pg[u] = (int)ri.p_lo + kk;
+      ph[u] = (int)phys_page(g, row, pg[u]);
+    } else if (pg[u] < ri.p_lo || pg[u] > ri.p_hi) {
+      ph[u] = -1;
+    }
+    pg[u] = __builtin_amdgcn_readfirstlane(pg[u]);
+    ph[u] = __builtin_amdgcn_readfirstlane(ph[u]);
+  }
 
+  const int P = g.P, n_pages = k0 + 4 < n_sel ? 2 : 1;
+  auto tiles_of = [&](int c0) { return P - c0 < kFineChunk ? (P - c0) / 32 : kFineChunk / 32; };  // 1 or 2
+  // load m fills slots 64 m + lane; the source offsets repeat with period 128 slots (see the prefill kernel)
+  auto src_off = [](int s) { const int t = s / GR; return t * RB + 16 * ((s % GR) ^ fine_swz<D, FP8>(t)); };
+  const uint32_t voff0 = (uint32_t)src_off(lane), voff1 = (uint32_t)src_off(64 + lane);
+  const uint32_t rd0 = (uint32_t)(j * RB + 16 * ((LG * h) ^ fine_swz<D, FP8>(j)));
+  const uint8_t* const buf = fsm[wv];
+  const uint32_t lds0 = lds_addr(fsm[wv]), lsc0 = lds_addr(lsc[wv]);
+  // rows c0 .. of physical page p -> this wave's buffer (a mapped page lies in the pool whole)
+  auto issue = [&](int p, int c0) {
+    if (p < 0) return;  // (unmapped: its scores are masked)
+    const int64_t r0 = (int64_t)p * g.kv_page + c0;
+    const uint8_t* sb = reinterpret_cast<const uint8_t*>(k) + r0 * RB;
+    const int nt = tiles_of(c0);
+#pragma unroll
+    for (int m = 0; m < GR; ++m)
+      if (m < GR / 2 || nt == 2) lds_dma<16>(sb + 2048 * (m / 2), (m & 1) ? voff1 : voff0, lds0 + 1024 * m);
+    if (FP8 && lane < 32 * nt) lds_dma<4>(kscale + r0, 4u * lane, lsc0);
+  };
+  issue(ph[0], 0);
   i32x8 qh[D / 64], ql[D / 64];
   if constexpr (FP8) query_fp8<D>(a, lane, qh, ql, wr);
-
-  constexpr int RAWN = FP8 ? D / 32 : D / 16;  // 16-byte loads per lane per tile
-  auto fetch = [&](int64_t kr, u32x4 (&r)[RAWN], float& scl) {
-    const u32x4* pp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(k) + kr * (FP8 ? D : 2 * D) +
-                                                    (FP8 ? D / 2 : D) * (lane >> 5));
 #pragma unroll
-    for (int v = 0; v < RAWN; ++v) r[v] = pp[v];
-    scl = FP8 ? kscale[kr] : 1.f;
-  };
-  const int tpp = g.P / 32;  // 32-token tiles per page
-  // the wave's pages (every fourth of the chunk) two at a time: both pages' first key rows are
-  // resolved before any key is loaded, then their (page, tile) items are scored in turn with the
-  // next item's keys in flight, so the second page's lookups overlap the first page's scoring
-  for (int64_t kk0 = k0 + wv; kk0 < k1; kk0 += 8) {
-    int64_t pg[2], kb[2];
+  for (int u = 0; u < kFinePagesPerWave; ++u) {
+    if (u >= n_pages) break;
+    const int page = pg[u];
+    uint32_t* const dst = fine_keys + row * ldf + (int64_t)(k0 + 4 * u) * P;
+    for (int c0 = 0; c0 < P; c0 += kFineChunk) {
+      vm_wait<0>();  // this chunk's keys have landed
+      u32x4 raw0[LG], raw1[LG];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t kk = kk0 + 4 * u;
-      int64_t ph = -1;
-      pg[u] = -1;
-      if (kk < k1) {
-        if (flat) {
-          pg[u] = ri.p_lo + kk;
-        } else if (kk0 == k0 + wv) {  // the pair requested up front
-          pg[u] = pg_pre[u];
-          ph = ph_pre[u];
-        } else {
-          pg[u] = pages[row * g.M + kk];
-          ph = phys[row * ldp + kk];
-        }
+      for (int v = 0; v < LG; ++v) {
+        raw0[v] = *reinterpret_cast<const u32x4*>(buf + (rd0 ^ (16 * v)));
+        raw1[v] = *reinterpret_cast<const u32x4*>(buf + (rd0 ^ (16 * v)) + 32 * RB);
       }
-      kb[u] = -1;  // key row of the page's first token
-      if (pg[u] >= ri.p_lo && pg[u] <= ri.p_hi) {
-        if (flat) ph = phys_page(g, row, pg[u]);
-        kb[u] = ph >= 0 ? ph * g.kv_page : -1;
-      }
-    }
-    const int n_items = (kk0 + 4 < k1 ? 2 : 1) * tpp;
-    // key row of lane j in `item` (row 0, not scored, outside E_t or the cache)
-    auto krow_of = [&](int item, bool& ok) -> int64_t {
-      const int u = item >= tpp, tile = item - u * tpp;
-      const int64_t page = u ? pg[1] : pg[0], kbase = u ? kb[1] : kb[0];
-      const int64_t pos = page * g.P + tile * 32 + j;
-      ok = kbase >= 0 && pos >= ri.lo && pos <= ri.hi;
-      return ok ? kbase + tile * 32 + j : 0;
-    };
-    bool ok;
-    u32x4 raw[RAWN];
-    float sc;
-    fetch(krow_of(0, ok), raw, sc);
-    for (int item = 0; item < n_items; ++item) {
-      bool nok = false;
-      u32x4 nraw[RAWN];
-      float nsc = 1.f;
-      if (item + 1 < n_items) fetch(krow_of(item + 1, nok), nraw, nsc);  // in flight while this tile is scored
-      f32x16 acc = {};
+      const float sc0 = FP8 ? lsc[wv][j] : 1.f, sc1 = FP8 ? lsc[wv][32 + j] : 1.f;
+      lds_read_wait();  // the buffer may be refilled once every read of it has returned
+      if (c0 + kFineChunk < P) issue(ph[u], c0 + kFineChunk);
+      else if (u + 1 < n_pages) issue(ph[u + 1 < kFinePagesPerWave ? u + 1 : u], 0);
+      f32x16 acc0 = {}, acc1 = {};
       if constexpr (FP8) {
 #pragma unroll
         for (int i = 0; i < D / 64; ++i) {
-          const i32x8 b = join_fp8x32(raw[2 * i], raw[2 * i + 1]);
-          acc = mfma32_fp8(qh[i], b, acc);
-          acc = mfma32_fp8(ql[i], b, acc);
+          const i32x8 b0 = join_fp8x32(raw0[2 * i], raw0[2 * i + 1]), b1 = join_fp8x32(raw1[2 * i], raw1[2 * i + 1]);
+          acc0 = mfma32_fp8(qh[i], b0, acc0);
+          acc1 = mfma32_fp8(qh[i], b1, acc1);
+          acc0 = mfma32_fp8(ql[i], b0, acc0);
+          acc1 = mfma32_fp8(ql[i], b1, acc1);
         }
       } else {
 #pragma unroll
-        for (int s = 0; s < KS; ++s) acc = mfma32(a[s], raw[s], acc);
+        for (int s = 0; s < KS; ++s) {
+          acc0 = mfma32(a[s], raw0[s], acc0);
+          acc1 = mfma32(a[s], raw1[s], acc1);
+        }
       }
-      float v = head_reduce(acc, wr);
-      if (FP8) v *= sc;
-      const int u = item >= tpp, tile = item - u * tpp;
-      if (lane < 32) fine_keys[row * ldf + (kk0 + 4 * u) * g.P + tile * 32 + j] = ok ? score_key(v) : 0u;
-      ok = nok;
-      sc = nsc;
-#pragma unroll
-      for (int e = 0; e < RAWN; ++e) raw[e] = nraw[e];
+      const float v0 = head_reduce(acc0, wr) * sc0, v1 = head_reduce(acc1, wr) * sc1;
+      // key t of the chunk (position r0 + t) is scored iff the page is mapped and lo <= t <= hi
+      const int r0 = page * P + c0;
+      const int lo = (int)ri.lo - r0, hi = ph[u] >= 0 ? (int)ri.hi - r0 : -1;
+      if (lane < 32) {
+        dst[c0 + j] = (j >= lo && j <= hi) ? score_key(v0) : 0u;
+        if (tiles_of(c0) == 2) dst[c0 + 32 + j] = (32 + j >= lo && 32 + j <= hi) ? score_key(v1) : 0u;
+      }
     }
   }
 }
@@ -1104,19 +1123,8 @@ __global__ __launch_bounds__(256) void fine_kernel(IndexGeom g, int64_t n_rows, 
 // Prefill variant (contiguous keys): one wave per (one or two rows, XCD), or several per (row, XCD).
 // Workgroup b runs on XCD b mod 8, and the wave of XCD x scores only the recalled pages p with
 // p mod 8 == x, so each XCD's L2 holds one eighth of the keys instead of streaming all of them. A page's keys are one contiguous
-// block of P rows, copied into LDS 64 rows at a time by direct loads in which the 16-byte granules
-// of one key row go to consecutive lanes (a few cache lines per load instead of one line per
-// lane); granule c of row t is stored at slot c ^ swz(t) so that the operand reads are
-// conflict-free. The two 32-key tiles of a chunk run as two independent MFMA chains.
+// block of P rows, staged as above. The two 32-key tiles of a chunk run as two independent MFMA chains.
 // Output layout as fine_kernel.
-template <int D, bool FP8>
-__device__ __forceinline__ int fine_swz(int t) {
-  constexpr int RB = FP8 ? D : 2 * D;  // key row bytes
-  constexpr int GR = RB / 16;          // 16-byte granules per row
-  return RB >= 128 ? (t & 7) : ((t >> (7 - __builtin_ctz(RB))) & (GR - 1));
-}
-
-constexpr int kFineChunk = 64;  // key rows staged in LDS at a time
 constexpr int kFineRowsPerWave = 2;  // query rows a fine-scoring wave takes in turn (long calls)
 
 template <int D, bool FP8>
@@ -2135,11 +2143,10 @@ template <int D, bool FP8>
 static hipError_t launch_fine_t(const IndexGeom& g, int64_t n_rows, const uint16_t* q, const float* w, const void* k,
                                 const float* ks, const int32_t* pages, const int32_t* phys, int64_t ldp,
                                 uint32_t* fine_keys, int64_t ldf, int64_t max_sel, hipStream_t st) {
-  constexpr int ppw = 8;  // recalled pages per workgroup (two per wave)
-  const int64_t chunks = (max_sel + ppw - 1) / ppw;
+  const int64_t chunks = (max_sel + kFinePagesPerWg - 1) / kFinePagesPerWg;
   if (chunks == 0 || n_rows == 0) return hipSuccess;
-  hipLaunchKernelGGL((fine_kernel<D, FP8>), dim3((unsigned)n_rows, (unsigned)chunks), dim3(256), 0, st, g, n_rows, q, w,
-                     k, ks, pages, phys, ldp, fine_keys, ldf, ppw);
+  hipLaunchKernelGGL((fine_kernel<D, FP8>), dim3((unsigned)n_rows, (unsigned)chunks), dim3(256), 0, st, g, q, w, k, ks, pages,
+                     phys, ldp, fine_keys, ldf);
   return hipGetLastError();
 }
 

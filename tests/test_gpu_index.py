@@ -602,6 +602,16 @@ def test_index_decode_parity(w, signed):
     P.check_runs(out["runs"], out["run_count"], out["idx"], out["count"], w.run_align)
 
 
+@pytest.mark.parametrize("page,keep_pages,fp8,head_dim", [(32, 21, True, 128), (128, 9, True, 64), (256, 3, False, 128), (96, 0, True, 128),
+                                                          (64, 13, False, 64)])
+def test_decode_page_sizes(page, keep_pages, fp8, head_dim):
+    """Paged decode with pages of one 32-key tile, of two, four and eight, and of three (a 64-key chunk and a
+    half one, flat), and counts of recalled pages that leave a wave one page or none, against the oracle."""
+    w = replace(W.SMALL_DECODE, name=f"decode_p{page}", page=page, kv_page=page, sub_block=32, keep_pages=keep_pages, fp8=fp8,
+                head_dim=head_dim, k_swa=256, batch=5)
+    test_index_decode_parity(w, False)
+
+
 def test_decode_bad_rows_are_skipped():
     """Out-of-range context lengths give count 0 (no fault, nothing selected)."""
     w = W.SMALL_DECODE
