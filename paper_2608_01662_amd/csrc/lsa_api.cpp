@@ -248,11 +248,12 @@ AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int
 }
 
 // The plan used when the workspace has room for it. Rounds of kCus whole rows, and the n_rows mod kCus
-// rows that are left cut into the number of pieces that finishes first by this count, in units of one
-// 32-entry tile (about 1 us per workgroup): rounds * (tiles per piece + 9), the 9 for a piece's fixed
-// cost (73 KB of Q, list staging, pipeline fill, 64 KB of output), plus 5 for the merge and 0.03 (fp32:
+// rows that are left cut into the number of pieces that finishes first by this count, in us: rounds * (tile *
+// tiles per piece + 9), a 32-entry tile taking about 1 beside whole rows and 1.6 in a call of few rows (their
+// lists and cache rows come from memory: one row in 73 pieces of one tile 13.6, in 37 of two 15.8, 64 rows in
+// pieces of 19 tiles 41), the 9 for a piece's fixed cost (73 KB of Q, list staging, pipeline fill, 64 KB of output), plus 5 for the merge and 0.03 (fp32:
 // 0.06) per piece for the partials it reads. Measured at 73 to 81 tiles, whole rows (and below 256 rows one piece
-// per CU whatever the rounds) before, this plan now: 4 rows 41.5 and 23.2 us, 24 rows 43.9 and 38.6 (264
+// per CU whatever the rounds) before, this plan now: 4 rows 41.5 and 22.2 us, 13 rows 38.5 and 25.2, 24 rows 43.9 and 38.6 (264
 // pieces in two rounds, 240 in one), 100 rows 72 and 62, 170 rows 110 and 92.5, 257 rows 149 and 113, 333
 // rows 150 and 136, 513 rows 224 and 195. Cut only where the count promises 5%: 400 rows took 165 us in
 // pieces and 161 whole. The error against 64 bits stays or falls (100 rows 2.50e-3 to 2.06e-3).
@@ -261,9 +262,11 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int3
   const int64_t rem = n_rows % kCus, tiles = cdiv(k_cap, 32);
   int64_t best = 1;
   if (p->latent != 0 && rem > 0) {
-    double least = 0.95 * (tiles + 9);
-    for (int64_t ns = 2; ns <= tiles && rem * ns <= kMaxPieces; ++ns) {
-      const double cost = cdiv(rem * ns, kCus) * (cdiv(tiles, ns) + 9) + 5 + (n_rows < kCus ? 0.03 : 0.06) * rem * ns;
+    const double tile = n_rows < kCus ? 1.6 : 1.0, part = n_rows < kCus ? 0.03 : 0.06;
+    double least = 0.95 * (tile * tiles + 9);
+    const int64_t most = n_rows < kCus ? kCus : kMaxPieces;  // (few rows: one round; 140 rows 84 us in two, 82 whole)
+    for (int64_t ns = 2; ns <= tiles && rem * ns <= most; ++ns) {
+      const double cost = cdiv(rem * ns, kCus) * (tile * cdiv(tiles, ns) + 9) + 5 + part * rem * ns;
       if (cost < least) {
         least = cost;
         best = ns;
