@@ -2044,11 +2044,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KPT <= 16 ? 
 template <bool FP8, bool MINMAX>
 static hipError_t launch_bk(int64_t n_items, const int64_t* rows, int64_t n_tok, int D, int B, const void* k,
                             const float* ks, uint16_t* out, hipStream_t st) {
-  if (n_items == 0) return hipSuccess;
   const int spw = rows == nullptr && B < kBlockTok ? kBlockTok / B : 1;  // sub-blocks per workgroup
-  hipLaunchKernelGGL((block_cache_kernel<FP8, MINMAX>), dim3((unsigned)((n_items + spw - 1) / spw)), dim3(256), 0, st,
-                     n_items, rows, n_tok, D, B, k, ks, out);
-  return hipGetLastError();
+  constexpr int64_t kMost = int64_t(1) << 22;  // workgroups per launch (a launch holds fewer than 2^32 threads)
+  for (int64_t i0 = 0; i0 < n_items; i0 += kMost * spw) {
+    const int64_t n = n_items - i0 < kMost * spw ? n_items - i0 : kMost * spw;
+    const bool all = rows == nullptr;  // the whole cache: sub-block i0 on; otherwise the list from i0 on
+    const uint8_t* kk = static_cast<const uint8_t*>(k) + (all ? i0 * B * D * (FP8 ? 1 : 2) : 0);
+    hipLaunchKernelGGL((block_cache_kernel<FP8, MINMAX>), dim3((unsigned)((n + spw - 1) / spw)), dim3(256), 0, st, n,
+                       all ? nullptr : rows + i0, n_tok, D, B, kk, FP8 ? ks + (all ? i0 * B : 0) : nullptr,
+                       out + (all ? i0 * D * (MINMAX ? 2 : 1) : 0));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_block_keys(int64_t n_items, const int64_t* rows, int64_t n_tok, int D, int B, bool fp8, bool minmax,

@@ -136,6 +136,21 @@ def test_block_keys_update_after_append(pooling, fp8):
             assert torch.equal(block[b].view(torch.int16), full0[b].view(torch.int16))
 
 
+def test_block_keys_update_long_list():
+    """An update list of more rows than one launch takes (2^22): the rows past it are updated too, and the whole
+    cache ends bit-identical to a recomputation."""
+    n = 4096
+    inp = synth.indexer_inputs(9, 1, n, 8, 64, True)
+    prm = lsa.IndexParams(8, 64, True, 64, 8, 16, 256, 4, 128, 64)
+    k, ks = P.to_dev(inp["k"]), P.to_dev(inp["k_scale"])
+    full = lsa.block_keys(prm, k, ks)
+    rows = torch.full((2 ** 22 + n // 8,), 3, dtype=torch.int64, device=k.device)
+    rows[2 ** 22:] = torch.arange(0, n, 8, device=k.device)   # (every sub-block, all past the first launch)
+    block = torch.zeros_like(full)
+    lsa.block_keys_update(prm, rows, k, ks, block)
+    assert torch.equal(block.view(torch.int16), full.view(torch.int16))
+
+
 def test_fp8_decode_all_codes():
     """Mean keys with B = 1 and unit scales are the decoded codes: all 256 e4m3fn codes, exactly."""
     codes = np.arange(256, dtype=np.uint32).astype(np.uint8)
