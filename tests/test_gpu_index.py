@@ -460,6 +460,31 @@ def test_mask_selection_clustered_scores(mode):
         assert stats["exact"] == stats["rows"], (q0, stats)
 
 
+@pytest.mark.parametrize("mode", ["random", "two_values"])
+def test_select_beyond_the_mask(mode):
+    """Rows with more candidate slots than the bit mask holds (262144) keep the selection that streams the
+    keys for its histogram, gather and compaction: flat indexing over 262500 tokens, scores drawn or of two
+    values (ties by position), three query rows against the oracle."""
+    n_kv, n_q = 262500, 3
+    w = replace(W.L2K_MQA, name=f"beyond_mask_{mode}", keep_pages=0, seq_len=n_kv, k_sparse=700)
+    inp = synth.indexer_inputs(31, n_q, n_kv, w.n_heads, w.head_dim, False)
+    if mode == "two_values":
+        q = np.zeros((n_q, w.n_heads, w.head_dim), np.float32)
+        q[:, :, 0] = 1.0
+        kb = np.zeros((n_kv, w.head_dim), np.uint16)
+        kb[:, 0] = 0x3F80 + (np.arange(n_kv) % 997 == 3)
+        inp = dict(q=synth.to_bf16_bits(q), w=np.ones((n_q, w.n_heads), np.float32), k=kb, k_scale=None)
+    q, wt, k, ks = P.gpu_index_inputs(inp, w)
+    q0 = n_kv - n_q
+    out = lsa.index_prefill(w.index_params(), q, wt, k, ks, None, q0, n_kv=n_kv, runs=True)
+    out = {key: v.cpu().numpy() for key, v in out.items()}
+    k_hat, qf = P.oracle_keys(inp), orc.bf16_bits_to_f64(inp["q"])
+    res = [P.oracle_index_row(q0 + i, qf[i], inp["w"][i], k_hat, None, P.oracle_params(w)) for i in range(n_q)]
+    stats = P.check_index_rows(w, [q0 + i for i in range(n_q)], out["idx"], out["count"], None, res)
+    P.check_runs(out["runs"], out["run_count"], out["idx"], out["count"], w.run_align)
+    assert mode == "random" or stats["exact"] == stats["rows"], stats
+
+
 def test_fine_scoring_orders_every_fp8_code():
     """The fine stage widens fp8 keys to bf16 on the GPU. Designed case: each eligible token carries
     one distinct e4m3fn code in component 0 (all 254 non-NaN codes, in seeded random positions),
