@@ -25,6 +25,11 @@ constexpr float kLazy = 8.0f;  // rescale when the max grows by more than this (
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// A partial of no entries (a wave without tiles, an empty piece) has the sum +0 exactly and is left out of a
+// merge; one whose sum is NaN (an infinite score; MLA: also a NaN) counts, so that the merged output is NaN as a
+// row taken whole has it. On the bits: without NaN semantics (see build.py) !(l > 0) may hold for a NaN sum.
+__device__ __forceinline__ bool no_entries(float l) { return __float_as_uint(l) == 0u; }
+
 __device__ __forceinline__ u32x4 tr16_pair(const uint8_t* pa, const uint8_t* pb) {
   const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(pa));
   const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(pb));
@@ -816,7 +821,7 @@ __global__ __launch_bounds__(64 * W) void mqa_attn_kernel(AttnGeom a) {
       f32x4 acc = {};
 #pragma unroll
       for (int x = 0; x < W; ++x) {
-        if (!(pl[x][head] > 0.f)) continue;  // (a wave without tiles)
+        if (no_entries(pl[x][head])) continue;
         const float wgt = fast_exp2(pm[x][head] - M);
         L += pl[x][head] * wgt;
         acc += wgt * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(lvs[x]) + head * kMqaOStride + d);
@@ -889,7 +894,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
   f32x4 acc = {};
 #pragma unroll
   for (int s = 0; s < kCombineRegs; ++s) {
-    if (!(ls[s] > 0.f)) continue;
+    if (no_entries(ls[s])) continue;
     // the partial is normalised by its own sum ls: weight it back by ls 2^(m_s - M)
     const float wgt = ls[s] * fast_exp2(ms[s] - M);
     L += wgt;
@@ -952,7 +957,7 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
     }
 #pragma unroll
     for (int u = 0; u < kCombineDeep; ++u) {
-      if (!(ls[u] > 0.f)) continue;  // (an empty piece of the list)
+      if (no_entries(ls[u])) continue;
       const float wgt = ls[u] * fast_exp2(ms[u] - M);
       L += wgt;
       acc[0] += wgt * pv[u][0].f32();

@@ -370,6 +370,41 @@ def test_mqa_waves_per_row(n_rows, k_cap, paged):
         P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
 
 
+@pytest.mark.parametrize("attn,n_rows,k_cap,mode", [("mqa", n, 400, "inf_score") for n in (5, 300, 600, 1030)] +
+                         [("mla", n, k, mode) for n, k in ((1, 400), (6, 400), (40, 400), (256, 400), (300, 1500))
+                          for mode in ("nan_key", "inf_score", "nan_query")])
+def test_nan_stays_visible(attn, n_rows, k_cap, mode):
+    """An infinite score, or for MLA a NaN in one listed key or in a query, makes the whole output of the
+    rows that attend to it NaN, however many waves (MQA: eight, four, two, one) or pieces (MLA: few-row calls
+    with either merge, whole rows, rows left over a round) share the row; every other row keeps its values.
+    (An MQA token whose score is NaN is skipped, whatever shares the row.)"""
+    from dataclasses import replace
+    w = replace(W.L2K_MQA if attn == "mqa" else W.SMALL_MLA, seq_len=2048)
+    n_kv, bad_key = w.seq_len, 1234
+    a = _attn_inputs(w, 0, n_rows, n_kv)
+    g = np.random.default_rng(29)
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    cnt = np.full(n_rows, k_cap - 5, np.int32)
+    others = np.setdiff1d(np.arange(n_kv), [bad_key])
+    for i in range(n_rows):
+        idx[i, :cnt[i]] = np.sort(g.choice(others, cnt[i], replace=False))
+    hit = sorted({0, n_rows // 2, n_rows - 1})
+    good, _ = _gpu_attn(w, a, list(range(n_rows)), idx, cnt)
+    if mode == "nan_query":
+        for r in hit:
+            a["q"][r, :, 7] = 0x7FC0
+    else:
+        a["kv"][bad_key, 0] = 0x7FC0 if mode == "nan_key" else 0x7F80
+        for r in hit:
+            idx[r, 200] = bad_key
+            a["q"][r, :, 0] = 0x3F80    # (1.0: the infinite key's score is +inf for every head)
+    o, _ = _gpu_attn(w, a, list(range(n_rows)), idx, cnt)
+    for r in hit:
+        assert np.all(np.isnan(o[r])), f"row {r}: {np.isnan(o[r]).mean():.3f} of the output is NaN"
+    keep = np.setdiff1d(np.arange(n_rows), hit)
+    assert np.array_equal(o[keep], good[keep])
+
+
 @pytest.mark.parametrize("n_rows", [None, 8], ids=["all_rows", "split_8_rows"])
 def test_run_form_equals_list_form(n_rows):
     """Attention over the indexer's run encoding equals attention over its index lists, bit for bit
