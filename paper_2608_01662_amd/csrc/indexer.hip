@@ -347,19 +347,38 @@ __device__ __forceinline__ void lds_dma(const void* base, uint32_t off, uint32_t
 __device__ __forceinline__ void lds_read_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // ============================================================================ Stage 1: coarse page scores
-// Sub-blocks of a page: 1 to 32 of them, consecutive block keys (a 32-bit shift where their number is a
-// power of two: n_kv < 2^31).
+// Sub-blocks of a page: n = 1 to 32 of them, consecutive block keys. A tile scores 32 consecutive block keys,
+// of which the first pages() * n are whole pages (all 32 where n is a power of two): the next tile starts
+// with the page after them, so that no page straddles two tiles.
 struct SubBlocks {
-  int n, lg;  // sub-blocks per page; log2 or -1
-  __device__ __forceinline__ explicit SubBlocks(const IndexGeom& g) : n(g.P / g.B) { lg = (n & (n - 1)) == 0 ? __ffs(n) - 1 : -1; }
-  __device__ __forceinline__ void split(uint32_t sb, int& page, int& sub) const {
-    page = lg >= 0 ? (int)(sb >> lg) : (int)(sb / (uint32_t)n);
-    sub = (int)sb - page * n;
+  int n, lg;      // sub-blocks per page; log2 or -1 (P / B = 3, 5, 6, 7, 10, ..: pages of 96, 160, 192, 224 tokens)
+  int page, sub;  // page of lane j's block key within the tile, and its sub-block in it (-1: past the whole pages)
+  __device__ __forceinline__ SubBlocks(const IndexGeom& g, int j) : n(g.P / g.B) {
+    lg = (n & (n - 1)) == 0 ? __ffs(n) - 1 : -1;
+    page = lg >= 0 ? j >> lg : j / n;
+    sub = page < pages() ? j - page * n : -1;
   }
-  // sum over a page's lanes (aligned groups of n, the butterfly over lanes ^1, ^2, .., ^16), by register
-  // exchanges: quads and the mirrors of half rows and rows, whose lanes hold equal sums by then, then
-  // the row swap. (An LDS permute per step made four dependent round trips per row and tile at n = 16.)
+  __device__ __forceinline__ int pages() const { return lg >= 0 ? 32 >> lg : 32 / n; }  // whole pages per tile
+  __device__ __forceinline__ int64_t tiles(int64_t n_pages) const {                     // tiles that hold them
+    return lg >= 0 ? (n_pages * n + 31) >> 5 : (int)((uint32_t)(n_pages + pages() - 1) / (uint32_t)pages());
+  }
+  // A page's sum over its lanes, valid in its first one (sub = 0). Powers of two: the butterfly over lanes
+  // ^1, ^2, .., ^16 by register exchanges (quads and the mirrors of half rows and rows, whose lanes hold
+  // equal sums by then, then the row swap; an LDS permute per step made four dependent round trips per row
+  // and tile at n = 16). Otherwise by the bits of n, with the sums p of 1, 2, 4, .. lanes from each lane on.
   __device__ __forceinline__ float sum(float v) const {
+    if (lg < 0) {
+      float s = 0.f, p = v;
+      int done = 0;
+      for (int b = 1; b <= n; b <<= 1) {
+        if (n & b) {
+          s += __shfl_down(p, done);
+          done += b;
+        }
+        p += __shfl_down(p, b);
+      }
+      return s;
+    }
     auto dpp = [](float x, auto ctrl) {
       return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
     };
@@ -384,8 +403,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   constexpr int DK = MINMAX ? 2 * D : D;  // width of a block key and of the dot product
   constexpr int KS = DK / 16;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, j = lane & 31;
-  const SubBlocks subs(g);
-  const int nsub = subs.n;
+  const SubBlocks subs(g, j);
+  const int nsub = subs.n, sub = subs.sub;
   // Decode: one row, chunks of 8 tiles, wave wv scoring tiles wv and wv + 4 of its chunk. The
   // page-table entries of both tiles and the query are requested before the context length is
   // known (any page below max_pages lies inside the sequence's table row), and both tiles' block
@@ -394,12 +413,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   const int64_t row = blockIdx.x, p_base = g.k_sink / g.P;  // first eligible page (k_sink only)
   const int64_t tile_beg = (int64_t)blockIdx.y * tiles_per_chunk;
   int64_t pp[2], ph[2];
-  int sub[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    int page;
-    subs.split((uint32_t)(tile_beg + wv + 4 * u) * 32 + j, page, sub[u]);  // sub-block counted from the first eligible page
-    pp[u] = p_base + page;
+    pp[u] = p_base + (tile_beg + wv + 4 * u) * subs.pages() + subs.page;
     ph[u] = phys_page(g, row, pp[u]);
   }
   u32x4 a[KS];
@@ -409,11 +425,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   load_head_weights(w, g.H, row, lane, wr);
   const RowInfo ri = row_info(g, row);
   if (!ri.valid || ri.p_hi < ri.p_lo) return;
-  const int64_t n_tiles = ((ri.p_hi - ri.p_lo + 1) * nsub + 31) / 32;
+  const int64_t n_tiles = subs.tiles(ri.p_hi - ri.p_lo + 1);
   u32x4 b[2][KS];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int64_t mrow = ph[u] >= 0 ? ph[u] * nsub + sub[u] : 0;
+    const int64_t mrow = ph[u] >= 0 && sub >= 0 ? ph[u] * nsub + sub : 0;
     const u32x4* pk = reinterpret_cast<const u32x4*>(kmean + mrow * DK + (DK / 2) * (lane >> 5));
 #pragma unroll
     for (int s = 0; s < KS; ++s) b[u][s] = pk[s];
@@ -426,7 +442,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 #pragma unroll
     for (int s = 0; s < KS; ++s) acc = mfma32(a[s], b[u][s], acc);
     const float v = subs.sum(head_reduce(acc, wr));
-    if (lane < 32 && sub[u] == 0 && pp[u] <= ri.p_hi) page_keys[row * ld + pp[u]] = ph[u] >= 0 ? score_key(v) : 0u;
+    if (lane < 32 && sub == 0 && pp[u] <= ri.p_hi) page_keys[row * ld + pp[u]] = ph[u] >= 0 ? score_key(v) : 0u;
   }
 }
 
@@ -456,7 +472,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int lane = threadIdx.x & 63, j = lane & 31;
   const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int64_t row0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * R;
-  const SubBlocks subs(g);
+  const SubBlocks subs(g, j);
 
   RowInfo ri[R];
   int64_t max_tiles = 0;
@@ -465,7 +481,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int64_t row = row0 + r;
     ri[r] = row < n_rows ? row_info(g, row) : RowInfo{0, 0, 1, 0, 0, -1};
     if (ri[r].valid && ri[r].p_hi >= ri[r].p_lo) {
-      const int64_t nt = ((ri[r].p_hi - ri[r].p_lo + 1) * subs.n + 31) / 32;
+      const int64_t nt = subs.tiles(ri[r].p_hi - ri[r].p_lo + 1);
       max_tiles = nt > max_tiles ? nt : max_tiles;
     }
   }
@@ -491,7 +507,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int tl = lane / GR, cl = lane % GR;
   const uint32_t v0 = (uint32_t)(tl * RB + 16 * (cl ^ coarse_swz<GR>(tl)));  // load 0; load m: XOR of swz(RPL m)
   auto issue = [&](int tile, int buf) {
-    const int64_t r0 = (int64_t)p_base * subs.n + (int64_t)tile * 32;
+    const int64_t r0 = ((int64_t)p_base + (int64_t)tile * subs.pages()) * subs.n;
     const uint32_t lds = lds_addr(&csm[wv][buf][0]);
     const uint8_t* base = reinterpret_cast<const uint8_t*>(kmean);
     if (r0 + 32 <= g.n_sub) {
@@ -548,10 +564,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       lds_read_wait();  // the operand reads are done before the buffer is refilled
       if (more) issue(tile + NW, 0);
     }
-    int page, sub_in_page;
-    subs.split((uint32_t)tile * 32 + j, page, sub_in_page);
-    const int p = p_base + page;
-    const bool okp = (int64_t)p * subs.n + sub_in_page < g.n_sub;
+    const int p = p_base + tile * subs.pages() + subs.page;
+    const bool okp = (int64_t)p * subs.n < g.n_sub;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       f32x16 acc = {};
@@ -568,7 +582,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
       const float v = subs.sum(head_reduce(acc, wr[WLDS ? 0 : r]));
       const int64_t row = row0 + r;
-      if (lane < 32 && sub_in_page == 0 && row < n_rows && ri[r].valid && p <= ri[r].p_hi)
+      if (lane < 32 && subs.sub == 0 && row < n_rows && ri[r].valid && p <= ri[r].p_hi)
         page_keys[row * ld + p] = okp ? score_key(v) : 0u;
     }
     if (NBUF == 2) {

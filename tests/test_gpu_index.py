@@ -652,6 +652,34 @@ def test_decode_page_sizes(page, keep_pages, fp8, head_dim):
     test_index_decode_parity(w, False)
 
 
+_ODD_SUBS = [(96, 32, "mean"), (160, 32, "minmax"), (192, 32, "mean"), (224, 32, "mean"), (160, 16, "mean"), (96, 8, "minmax"),
+             (96, 4, "mean"), (224, 8, "mean")]
+
+
+@pytest.mark.parametrize("page,sub_block,pooling", _ODD_SUBS)
+def test_prefill_sub_block_counts(page, sub_block, pooling):
+    """Pages of 3, 5, 6, 7, 10, 12, 24 and 28 sub-blocks (P / B no power of two, so pages do not fill the
+    32-key coarse tiles): page scores in rows of up to 64 coarse tiles and of more (96 / 4: one page per tile, 85
+    tiles), mean and min-max, stage-wise against the oracle; calls of few rows give the same rows."""
+    w = replace(W.SMALL_CLI, name=f"p{page}_b{sub_block}", page=page, sub_block=sub_block, pooling=pooling)
+    inp = P.prefill_inputs(w)
+    out, _ = _run_prefill(w, inp)
+    rows = _sample_rows(w.seq_len, 173, [w.k_sink + w.k_swa, w.k_sink + w.k_swa + page, w.keep_pages * page + w.k_swa])
+    res = _oracle_rows(w, inp, rows)
+    P.check_index_rows(w, rows, out["idx"][rows], out["count"][rows], out["pages"][rows], res)
+    q0 = w.seq_len - 40
+    part, _ = _run_prefill(w, inp, q_start=q0, n_q=35)
+    P.assert_same_index_outputs(part, out, slice(q0, q0 + 35))
+
+
+@pytest.mark.parametrize("page,sub_block,pooling", _ODD_SUBS)
+def test_decode_sub_block_counts(page, sub_block, pooling):
+    """Paged decode with the same pages, every sequence stage-wise against the oracle."""
+    w = replace(W.SMALL_DECODE, name=f"decode_p{page}_b{sub_block}", page=page, kv_page=page, sub_block=sub_block, pooling=pooling,
+                keep_pages=6, k_swa=256, batch=5)
+    test_index_decode_parity(w, False)
+
+
 def test_decode_bad_rows_are_skipped():
     """Out-of-range context lengths give count 0 (no fault, nothing selected)."""
     w = W.SMALL_DECODE
