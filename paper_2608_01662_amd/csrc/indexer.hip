@@ -70,7 +70,8 @@ __device__ __forceinline__ int64_t phys_page(const IndexGeom& g, int64_t seq, in
 // Sub-block holding token row r of an incremental update; -1 when r is out of range or in the
 // incomplete tail.
 __device__ __forceinline__ int64_t block_of_row(int64_t r, int64_t n_tok, int B) {
-  return (r >= 0 && r < n_tok && r / B < n_tok / B) ? r / B : -1;
+  const int lg = __ffs(B) - 1;  // (B is a power of two)
+  return (r >= 0 && r < n_tok && r >> lg < n_tok >> lg) ? r >> lg : -1;
 }
 
 // bf16 bits of x rounded to nearest, ties to even, in one step from fp64: the float rounded
@@ -93,9 +94,9 @@ __device__ __forceinline__ uint32_t bf16_rne_from_f64(double x) {
 //   Min-max extrema (Eq. 13): each dequantised key s_i * k_i is formed exactly in fp64 (24-bit scale
 //   times 4-bit code), the extrema are exact, and each is rounded once to bf16. Row: [k_max | k_min].
 // Latency bounds it: a prefix of 128K tokens is 17.6 MB, 4 us at the copy rate, and an appended token's
-// sub-block a few KB. With a thread per four dims reading its B tokens one dword after the other, a 128K
-// prefix at B = 128 took 25.7 us (min-max 36.4) and the update of 64 sequences' sub-blocks (B = 64)
-// 31.3 us; here 6.1 (11.3) and 4.0 us. At 1M tokens and B = 8 bandwidth bounds both (31.4 and 27.9 us). Same order of the sums, bit-identical results.
+// sub-block a few KB. With a thread per four dims reading its B tokens one dword after the other (the direct
+// kernel below), a 128K prefix at B = 128 takes 24.7 us (min-max 36.4) and the update of 64 sequences' sub-blocks
+// (B = 64) 9.4 to 31; here 5.6 (9.7) and 3.7. Same order of the sums, bit-identical results.
 constexpr int kBlockTok = 128;  // tokens staged at a time
 template <bool FP8, bool MINMAX>
 __global__ __launch_bounds__(256) void block_cache_kernel(int64_t n_items, const int64_t* __restrict__ rows, int64_t n_tok,
@@ -175,6 +176,62 @@ __global__ __launch_bounds__(256) void block_cache_kernel(int64_t n_items, const
         reinterpret_cast<uint32_t*>(out + sub * D)[dp] = pack_bf16x2(x0 * inv, x1 * inv);
       }
     }
+  }
+}
+
+// The same, one thread per (item, four dims) that reads its B tokens one after the other: for calls with so
+// many items that the chip is full of them (the rule stands at launch_bk). Same order, same bits.
+template <bool FP8, bool MINMAX>
+__global__ __launch_bounds__(256) void block_direct_kernel(int64_t n_items, const int64_t* __restrict__ rows, int64_t n_tok,
+                                                           int D, int B, const void* __restrict__ k,
+                                                           const float* __restrict__ ks, uint16_t* __restrict__ out) {
+  const int lg = D == 128 ? 5 : 4, groups = 1 << lg;  // groups of four dims
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t item = id >> lg;
+  const int gq = (int)id & (groups - 1);
+  if (item >= n_items) return;
+  const int64_t sub = rows == nullptr ? item : block_of_row(rows[item], n_tok, B);
+  if (sub < 0) return;
+  using acc_t = std::conditional_t<MINMAX, double, float>;
+  acc_t x[4] = {}, y[4] = {};  // sums, or maxima (x) and minima (y)
+  using piece_t = std::conditional_t<FP8, uint32_t, u32x2>;  // four dims of a key
+  const piece_t* kp = reinterpret_cast<const piece_t*>(k) + sub * B * groups + gq;
+  const float* sp = FP8 ? ks + sub * B : nullptr;
+  for (int i = 0; i < B; ++i, kp += groups) {
+    float v[4], sc = 1.f;
+    if constexpr (FP8) {
+      const uint32_t c = *kp;
+      const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(c, false);
+      const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(c, true);
+      v[0] = lo.x, v[1] = lo.y, v[2] = hi.x, v[3] = hi.y;
+      sc = *sp++;
+    } else {
+      const u32x2 c = *kp;
+      v[0] = __uint_as_float(c.x << 16), v[1] = __uint_as_float(c.x & 0xFFFF0000u);
+      v[2] = __uint_as_float(c.y << 16), v[3] = __uint_as_float(c.y & 0xFFFF0000u);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (MINMAX) {
+        const double p = FP8 ? (double)sc * (double)v[e] : (double)v[e];
+        x[e] = (i == 0 || p > x[e]) ? p : x[e];
+        y[e] = (i == 0 || p < y[e]) ? p : y[e];
+      } else if constexpr (FP8) {
+        x[e] += sc * v[e];
+      } else {
+        x[e] += v[e];
+      }
+    }
+  }
+  if constexpr (MINMAX) {
+    u32x2* row = reinterpret_cast<u32x2*>(out + sub * 2 * D);
+    row[gq] = u32x2{bf16_rne_from_f64(x[0]) | (bf16_rne_from_f64(x[1]) << 16),
+                    bf16_rne_from_f64(x[2]) | (bf16_rne_from_f64(x[3]) << 16)};
+    row[groups + gq] = u32x2{bf16_rne_from_f64(y[0]) | (bf16_rne_from_f64(y[1]) << 16),
+                             bf16_rne_from_f64(y[2]) | (bf16_rne_from_f64(y[3]) << 16)};
+  } else {
+    const float inv = 1.0f / (float)B;
+    reinterpret_cast<u32x2*>(out + sub * D)[gq] = u32x2{pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
   }
 }
 
@@ -2055,18 +2112,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KPT <= 16 ? 
 }
 
 // ============================================================================ host launchers
+// Which block-cache kernel. The direct one serves calls of so many items that its threads hide their own loads,
+// and short sub-blocks, for which the staged one spends more on staging than on the tokens (and, in fp64, leaves
+// most of a workgroup's threads without a sub-block at B >= 64). Kernel us, staged / direct, fp8 keys, d_I = 128:
+//   update of 1024, 4096, 8192 consecutive rows: B = 8 mean 3.5 / 3.2, 6.8 / 3.4, 10.9 / 3.7; B = 32 min-max 5.5 /
+//     9.3, 12.5 / 9.3, 22.9 / 15.1; B = 64 min-max 7.3 / 15.8, 19.2 / 15.7, 35.7 / 26.0; 64 rows, B = 64: 3.7 / 9.4
+//   min-max cache of 32768, 131072, 1M tokens: B = 8 6.1 / 4.5, 13.0 / 10.7, 73.1 / 62.5; B = 64 5.8 / 15.2, 9.5 / 25.3,
+//     57.0 / 52.4 (8192 sub-blocks and more: 0.91 to 1.05 of each other; B = 256 65.8 / 91.1)
+//   mean cache: B = 4 5.3 / 3.1, 8.1 / 5.4, 36.7 / 36.3; B = 8 3.9 / 3.2, 5.6 / 4.4, 28.6 / 32.0; B = 16 3.6 / 3.9, 5.0 / 4.5,
+//     24.6 / 28.9; d_I = 64, bf16: B = 16 and 32 at 1M 22.7 / 21.3 and 22.4 / 20.2, at 131072 4.1 / 4.4 and 4.1 / 9.2
+static bool block_direct(int64_t items, bool list, bool minmax, int D, int B) {
+  if (list) return items >= std::min<int64_t>(4096, std::max<int64_t>(1024, 64 * B));
+  if (minmax) return B <= 8 || (B <= 128 && items >= 8192);
+  return B <= 4 || (B == 8 && items <= 65536) || (D == 64 && B <= 32 && items >= 16384);
+}
 template <bool FP8, bool MINMAX>
 static hipError_t launch_bk(int64_t n_items, const int64_t* rows, int64_t n_tok, int D, int B, const void* k,
                             const float* ks, uint16_t* out, hipStream_t st) {
-  const int spw = rows == nullptr && B < kBlockTok ? kBlockTok / B : 1;  // sub-blocks per workgroup
-  constexpr int64_t kMost = int64_t(1) << 22;  // workgroups per launch (a launch holds fewer than 2^32 threads)
-  for (int64_t i0 = 0; i0 < n_items; i0 += kMost * spw) {
-    const int64_t n = n_items - i0 < kMost * spw ? n_items - i0 : kMost * spw;
-    const bool all = rows == nullptr;  // the whole cache: sub-block i0 on; otherwise the list from i0 on
+  const bool all = rows == nullptr;  // the whole cache, or the sub-blocks of a list
+  const bool direct = block_direct(n_items, !all, MINMAX, D, B);
+  auto kernel = direct ? block_direct_kernel<FP8, MINMAX> : block_cache_kernel<FP8, MINMAX>;
+  // items per workgroup; 2^22 workgroups per launch (a launch holds fewer than 2^32 threads)
+  const int ipw = direct ? 256 / (D / 4) : all && B < kBlockTok ? kBlockTok / B : 1;
+  const int64_t most = (int64_t(1) << 22) * (direct ? 1 : ipw);
+  for (int64_t i0 = 0; i0 < n_items; i0 += most) {
+    const int64_t n = n_items - i0 < most ? n_items - i0 : most;
     const uint8_t* kk = static_cast<const uint8_t*>(k) + (all ? i0 * B * D * (FP8 ? 1 : 2) : 0);
-    hipLaunchKernelGGL((block_cache_kernel<FP8, MINMAX>), dim3((unsigned)((n + spw - 1) / spw)), dim3(256), 0, st, n,
-                       all ? nullptr : rows + i0, n_tok, D, B, kk, FP8 ? ks + (all ? i0 * B : 0) : nullptr,
-                       out + (all ? i0 * D * (MINMAX ? 2 : 1) : 0));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + ipw - 1) / ipw)), dim3(256), 0, st, n, all ? nullptr : rows + i0, n_tok, D, B,
+                       kk, FP8 ? ks + (all ? i0 * B : 0) : nullptr, out + (all ? i0 * D * (MINMAX ? 2 : 1) : 0));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

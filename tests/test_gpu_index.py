@@ -136,6 +136,42 @@ def test_block_keys_update_after_append(pooling, fp8):
             assert torch.equal(block[b].view(torch.int16), full0[b].view(torch.int16))
 
 
+@pytest.mark.parametrize("pooling,head_dim,fp8,B,items", [
+    ("minmax", 64, False, 16, 8192), ("minmax", 128, True, 128, 8192), ("minmax", 64, True, 8, 300), ("minmax", 64, True, 256, 130),
+    ("mean", 64, True, 8, 65537), ("mean", 64, False, 32, 16384), ("mean", 128, True, 4, 1000), ("mean", 128, False, 1, 77)])
+def test_block_cache_kernels_agree(pooling, head_dim, fp8, B, items):
+    """The staged and the direct block-cache kernel on both sides of each size where the choice changes: a cache
+    of `items` sub-blocks, the one of one sub-block less, and their sub-blocks from update lists of 1023 and 4096
+    rows (staged, direct), all the same bits; the first sub-blocks against the oracle."""
+    prm = lsa.IndexParams(8, head_dim, fp8, max(32, B), B, 0, 16, 4, 256, 64, pooling)
+    n = items * B
+    if fp8:
+        k, ks = synth.device_fp8_keys(n, head_dim, 12, torch.device("cuda"))
+    else:
+        k, ks = synth.device_normal_bf16((n, head_dim), 12, synth.T_KI, torch.device("cuda"), 0.3), None
+    full = lsa.block_keys(prm, k, ks)
+    less = lsa.block_keys(prm, k[:n - B], None if ks is None else ks[:n - B])
+    assert torch.equal(less.view(torch.int16), full[:-1].view(torch.int16))
+    for n_rows in (1023, 4096):
+        rows = (torch.arange(n_rows, dtype=torch.int64, device=k.device) * 7919) % n
+        block = torch.full_like(full, 7.0)
+        lsa.block_keys_update(prm, rows, k, ks, block)
+        sub = torch.unique(rows // B)
+        assert torch.equal(block[sub].view(torch.int16), full[sub].view(torch.int16))
+        assert int((block != 7.0).any(1).sum()) <= sub.numel()
+    m = min(items, 64)
+    kk = k[:m * B].cpu() if fp8 else k[:m * B].view(torch.int16).cpu()
+    inp = dict(k=kk.numpy() if fp8 else kk.numpy().view(np.uint16), k_scale=None if ks is None else ks[:m * B].cpu().numpy())
+    k_hat = P.oracle_keys(inp)
+    got = full[:m].view(torch.int16).cpu().numpy().view(np.uint16)
+    if pooling == "minmax":
+        ref = np.concatenate([orc.f64_to_bf16_bits(x) for x in orc.sub_block_minmax_keys(k_hat, B)], axis=1)
+        assert np.array_equal(got, ref)
+    else:  # (an fp32 sum may land one bf16 ulp away next to a rounding boundary)
+        ref = orc.f64_to_bf16_bits(orc.sub_block_mean_keys(k_hat, B))
+        assert np.all(np.abs(got.astype(np.int32) - ref.astype(np.int32)) <= 1)
+
+
 def test_block_keys_update_long_list():
     """An update list of more rows than one launch takes (2^22): the rows past it are updated too, and the whole
     cache ends bit-identical to a recomputation."""
