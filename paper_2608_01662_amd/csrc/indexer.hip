@@ -405,26 +405,26 @@ __device__ __forceinline__ void lds_read_wait() { asm volatile("s_waitcnt lgkmcn
 
 // ============================================================================ Stage 1: coarse page scores
 // Sub-blocks of a page: n = 1 to 32 of them, consecutive block keys. A tile scores 32 consecutive block keys,
-// of which the first pages() * n are whole pages (all 32 where n is a power of two): the next tile starts
+// of which the first pages * n are whole pages (all 32 where n is a power of two): the next tile starts
 // with the page after them, so that no page straddles two tiles.
+// (The divisions by n are the host's: on the device they stood in front of the paged kernel's first loads.)
 struct SubBlocks {
-  int n, lg;      // sub-blocks per page; log2 or -1 (P / B = 3, 5, 6, 7, 10, ..: pages of 96, 160, 192, 224 tokens)
+  int n, pages;   // sub-blocks per page, whole pages per tile
   int page, sub;  // page of lane j's block key within the tile, and its sub-block in it (-1: past the whole pages)
-  __device__ __forceinline__ SubBlocks(const IndexGeom& g, int j) : n(g.P / g.B) {
-    lg = (n & (n - 1)) == 0 ? __ffs(n) - 1 : -1;
-    page = lg >= 0 ? j >> lg : j / n;
-    sub = page < pages() ? j - page * n : -1;
+  __device__ __forceinline__ SubBlocks(const IndexGeom& g, int j) : n(g.page_subs), pages(g.tile_pages) {
+    page = (j * g.sub_recip) >> 16;
+    sub = page < pages ? j - page * n : -1;
   }
-  __device__ __forceinline__ int pages() const { return lg >= 0 ? 32 >> lg : 32 / n; }  // whole pages per tile
-  __device__ __forceinline__ int64_t tiles(int64_t n_pages) const {                     // tiles that hold them
-    return lg >= 0 ? (n_pages * n + 31) >> 5 : (int)((uint32_t)(n_pages + pages() - 1) / (uint32_t)pages());
+  __device__ __forceinline__ int64_t tiles(int64_t n_pages) const {  // tiles that hold them (fewer than 2^26)
+    const uint32_t up = (uint32_t)n_pages + pages - 1;
+    return (pages & (pages - 1)) == 0 ? up >> (__ffs(pages) - 1) : up / (uint32_t)pages;
   }
   // A page's sum over its lanes, valid in its first one (sub = 0). Powers of two: the butterfly over lanes
   // ^1, ^2, .., ^16 by register exchanges (quads and the mirrors of half rows and rows, whose lanes hold
   // equal sums by then, then the row swap; an LDS permute per step made four dependent round trips per row
   // and tile at n = 16). Otherwise by the bits of n, with the sums p of 1, 2, 4, .. lanes from each lane on.
   __device__ __forceinline__ float sum(float v) const {
-    if (lg < 0) {
+    if ((n & (n - 1)) != 0) {
       float s = 0.f, p = v;
       int done = 0;
       for (int b = 1; b <= n; b <<= 1) {
@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   int64_t pp[2], ph[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    pp[u] = p_base + (tile_beg + wv + 4 * u) * subs.pages() + subs.page;
+    pp[u] = p_base + (tile_beg + wv + 4 * u) * subs.pages + subs.page;
     ph[u] = phys_page(g, row, pp[u]);
   }
   u32x4 a[KS];
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int tl = lane / GR, cl = lane % GR;
   const uint32_t v0 = (uint32_t)(tl * RB + 16 * (cl ^ coarse_swz<GR>(tl)));  // load 0; load m: XOR of swz(RPL m)
   auto issue = [&](int tile, int buf) {
-    const int64_t r0 = ((int64_t)p_base + (int64_t)tile * subs.pages()) * subs.n;
+    const int64_t r0 = ((int64_t)p_base + (int64_t)tile * subs.pages) * subs.n;
     const uint32_t lds = lds_addr(&csm[wv][buf][0]);
     const uint8_t* base = reinterpret_cast<const uint8_t*>(kmean);
     if (r0 + 32 <= g.n_sub) {
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       lds_read_wait();  // the operand reads are done before the buffer is refilled
       if (more) issue(tile + NW, 0);
     }
-    const int p = p_base + tile * subs.pages() + subs.page;
+    const int p = p_base + tile * subs.pages + subs.page;
     const bool okp = (int64_t)p * subs.n < g.n_sub;
 #pragma unroll
     for (int r = 0; r < R; ++r) {

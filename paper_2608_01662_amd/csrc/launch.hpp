@@ -12,6 +12,8 @@ struct IndexGeom {
   int P, B, M;                   // page, sub-block, kept pages (M <= 0: flat)
   int minmax;                    // coarse stage: min-max pooling (block keys [k_max | k_min])
   int k_sparse, k_sink, k_swa, C;
+  int page_subs, tile_pages;     // coarse stage: sub-blocks per page, whole pages in a tile of 32 block keys
+  int sub_recip;                 // ceil(2^16 / page_subs): (j * sub_recip) >> 16 = j / page_subs for j < 32
   int64_t q_start;               // prefill: position of row 0
   int64_t n_kv;                  // prefill: cached tokens
   int64_t n_sub;                 // mean keys available

@@ -151,6 +151,9 @@ lsa::IndexGeom make_geom(const lsa_index_params* p) {
   g.k_sink = p->k_sink;
   g.k_swa = p->k_swa;
   g.C = p->run_align;
+  g.page_subs = p->page / p->sub_block;
+  g.tile_pages = 32 / g.page_subs;
+  g.sub_recip = (65536 + g.page_subs - 1) / g.page_subs;
   return g;
 }
 
@@ -184,7 +187,7 @@ lsa_status run_index(const lsa_index_params* p, const lsa::IndexGeom& g, int64_t
     int32_t* pages = pages_out ? pages_out + r0 * g.M : reinterpret_cast<int32_t*>(ws + pl.off_pages);
     int32_t* phys = (g.ctx_len && g.M > 0) ? reinterpret_cast<int32_t*>(page_keys) : nullptr;
     if (g.M > 0) {
-      const int64_t max_tiles = cdiv(max_elig, 32 / (g.P / g.B));  // (a tile of 32 block keys scores whole pages)
+      const int64_t max_tiles = cdiv(max_elig, g.tile_pages);
       e = lsa::launch_coarse(gp, nr, q16, wp, static_cast<const uint16_t*>(block_keys), page_keys, pl.n_pages,
                              max_tiles, st);
       if (e != hipSuccess) return hip_fail(e, "coarse page scoring");
