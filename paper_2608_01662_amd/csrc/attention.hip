@@ -30,6 +30,10 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // row taken whole has it. On the bits: without NaN semantics (see build.py) !(l > 0) may hold for a NaN sum.
 __device__ __forceinline__ bool no_entries(float l) { return __float_as_uint(l) == 0u; }
 
+// Sum of the first piece of a row whose output that piece has written: nothing to merge.
+constexpr float kMerged = -1.f;
+__device__ __forceinline__ bool merged(float l) { return __float_as_uint(l) == 0xBF800000u; }
+
 __device__ __forceinline__ u32x4 tr16_pair(const uint8_t* pa, const uint8_t* pb) {
   const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(pa));
   const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(pb));
@@ -216,16 +220,17 @@ void mla_attn_kernel(AttnGeom a) {
   const int i16 = lane & 15, g = lane >> 4;
   const int w4 = wv & 3;  // scorer / value-wave pair
   const bool scorer = wv < 4;
-  // SPLIT: the first n_whole workgroups take whole rows, the others one piece of a row's list each
-  const bool whole = !SPLIT || blockIdx.x < a.n_whole;
+  // SPLIT: the first n_whole workgroups take the last rows whole, the others one piece each of an earlier row's list
+  // (a prompt's first rows are its shortest: as the last workgroups of the launch, they do not form its tail)
+  bool whole = !SPLIT || blockIdx.x < a.n_whole;
   int64_t row;
   int split = 0;
   if (whole) {
-    row = xcd_band(blockIdx.x, SPLIT ? a.n_whole : a.n_rows);
+    row = SPLIT ? a.n_rows - a.n_whole + xcd_band(blockIdx.x, a.n_whole) : xcd_band(blockIdx.x, a.n_rows);
   } else {
     const uint32_t pb = blockIdx.x - (uint32_t)a.n_whole, rem = (uint32_t)(a.n_rows - a.n_whole);
     split = (int)(pb / rem);
-    row = a.n_whole + xcd_band(pb % rem, rem);
+    row = xcd_band(pb % rem, rem);
   }
   __shared__ int64_t rtot[8];
   __shared__ int32_t roff[512];   // run form: list position of each thread's first run (clamped)
@@ -258,10 +263,29 @@ void mla_attn_kernel(AttnGeom a) {
     win0 = t - nwin + 1;
     cnt = cnt > 0 ? n_list + nwin : 0;  // an empty list (a skipped row) has no window either
   }
-  const int s0 = SPLIT ? split * a.split_len : 0;
-  const int s1 = !whole && cnt - s0 > a.split_len ? s0 + a.split_len : cnt;
+  // Pieces share the tiles of the row's own list, which may be far shorter than the capacity the plan is made
+  // for; a list of at most short_tiles is the first piece's alone, which writes the row's output itself.
+  int s0 = 0, s1 = cnt;
+  bool alone = false;
+  if (SPLIT && !whole) {
+    const int tiles = __builtin_amdgcn_readfirstlane((cnt + kMlaT - 1) / kMlaT);
+    const bool one = tiles <= a.short_tiles;
+    const int len = (one ? tiles : (int)((uint32_t)(tiles + a.n_split - 1) / (uint32_t)a.n_split)) * kMlaT;
+    s0 = split * len < cnt ? split * len : cnt;
+    s1 = cnt - s0 > len ? s0 + len : cnt;
+    alone = one && split == 0 && tiles > 0;
+    whole = alone;
+  }
   const int n = __builtin_amdgcn_readfirstlane(s1 > s0 ? s1 - s0 : 0);
   const int nl = n_list - s0;  // listed entries from s0 on (n of them unless windowed)
+  const int64_t p0 = SPLIT ? (row * a.n_split + split) * 64 : 0;  // this piece's partial of head 0
+  if (SPLIT && !whole && n == 0) {  // (uniform) nothing to add: the merge reads no more than the sum
+    if (threadIdx.x < 64) {
+      a.part_ml[(p0 + threadIdx.x) * 2] = kNoRef;
+      a.part_ml[(p0 + threadIdx.x) * 2 + 1] = 0.f;
+    }
+    return;
+  }
   const int32_t* slots = a.rows ? a.rows + row * a.k_cap + s0 : nullptr;  // list form (unused with runs)
   const uint8_t* kvb = reinterpret_cast<const uint8_t*>(a.kv);
   uint8_t* const pslots = lds + kMlaBufs * kMlaTile;
@@ -606,12 +630,12 @@ void mla_attn_kernel(AttnGeom a) {
     mfin[hb] = fmaxf(ma, mb);
     lt[hb] = (ma == mfin[hb] ? la : la * fast_exp2(ma - mfin[hb])) + (mb == mfin[hb] ? lb : lb * fast_exp2(mb - mfin[hb]));
   }
-  const int64_t p0 = SPLIT ? ((row - a.n_whole) * a.n_split + split) * 64 : 0;  // this piece's partial of head 0
   if (w4 == 0 && lane < 32) {
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb) {
       if (whole) {
         if (a.lse) a.lse[row * 64 + 32 * hb + oj] = lt[hb] > 0.f ? (mfin[hb] + __log2f(lt[hb])) * kLn2 : -INFINITY;
+        if (alone) a.part_ml[(p0 + 32 * hb + oj) * 2 + 1] = kMerged;
       } else {
         a.part_ml[(p0 + 32 * hb + oj) * 2] = mfin[hb];
         a.part_ml[(p0 + 32 * hb + oj) * 2 + 1] = lt[hb];
@@ -887,6 +911,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
       pv[s].load(a, pi * d_v + d);
     }
   }
+  if (merged(ls[0])) return;
   float M = -INFINITY;
 #pragma unroll
   for (int s = 0; s < kCombineRegs; ++s) M = fmaxf(M, ms[s]);
@@ -902,7 +927,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnGeom a) {
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
   const u32x2 v = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
-  const int64_t orow = (a.n_whole + row) * H + head;
+  const int64_t orow = row * H + head;
   *reinterpret_cast<u32x2*>(a.out + orow * d_v + d) = v;
   if (a.lse && threadIdx.x == 0) a.lse[orow] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
@@ -932,6 +957,7 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
     }
   };
   request(wv);
+  const float l0 = a.part_ml[p0 * 2 + 1];
   // maximum over all splits: every wave reads all of them, a lane four apart
   float m4[4], M = -INFINITY;
   for (int b = 0; b < ns; b += 256) {
@@ -942,6 +968,7 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
     }
     M = fmaxf(M, fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
   }
+  if (merged(l0)) return;  // (uniform over the workgroup)
   M = wave_max(M);
   f32x4 acc[2] = {};
   float L = 0.f;
@@ -972,7 +999,7 @@ __global__ __launch_bounds__(512) void attn_combine_deep_kernel(AttnGeom a) {
 #pragma unroll
   for (int x = 0; x < 8; ++x) L += wl[x];
   const float inv = L > 0.f ? 1.f / L : 0.f;
-  const int64_t orow = (a.n_whole + row) * H + head;
+  const int64_t orow = row * H + head;
   if (threadIdx.x < d_v / 2) {
     const int d = 2 * (int)threadIdx.x;
     f32x2 o = {};

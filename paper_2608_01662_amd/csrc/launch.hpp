@@ -75,8 +75,9 @@ struct AttnGeom {
   float* part_f32;         // the same in fp32 (then part_o is unused), or nullptr
   float* part_ml;          // [n_rows - n_whole, n_split, H, 2]
   int64_t n_rows;
-  int64_t n_whole;         // with n_split > 1: rows taken whole; the later ones are cut into pieces
-  int n_split, split_len;  // pieces per row, list entries per piece (multiple of the tile)
+  int64_t n_whole;         // with n_split > 1: the last rows, taken whole; the earlier ones are cut into pieces
+  int n_split;             // pieces per row, of whole tiles (some without any where the list is short)
+  int short_tiles;         // lists of at most that many 32-entry tiles are not cut
   float scale_log2;        // sm_scale * log2(e)
   // Windowed lists (MLA list form; k_swa < 0: plain lists): row r's list is its entries before the
   // window and then the contiguous positions [t - w + 1, t], t = q_pos0 + r, w = min(k_swa, t + 1).

@@ -208,8 +208,9 @@ lsa_status run_index(const lsa_index_params* p, const lsa::IndexGeom& g, int64_t
 
 // ---------------------------------------------------------------- attention planning
 struct AttnPlan {
-  int64_t n_whole;  // rows taken whole (with n_split > 1; the later ones are cut into n_split pieces)
-  int n_split, split_len;
+  int64_t n_whole;  // the last rows, taken whole (with n_split > 1; the earlier ones are cut into n_split pieces)
+  int n_split;
+  int short_tiles;  // lists of at most that many tiles are left in one piece
   bool f32;         // partials in fp32
   size_t off_po, off_ml, total;
 };
@@ -217,20 +218,26 @@ struct AttnPlan {
 // Workgroups the GPU runs at once: one per CU (the MLA kernel's LDS admits one per CU).
 constexpr int64_t kCus = 256;
 
-// Rows from n_whole on in `ns` pieces each, of 32-entry multiples (fewer where the list has fewer tiles).
+// Lists of at most this many tiles stay in one piece, whatever the plan: in calls of few rows while the tiles
+// (1.6 us each) cost less than writing and merging partials, beside whole rows up to half the capacity, as rows over the
+// rounds at the start of a prompt are short and find a free CU early. (us before any cutting by rounds / cut by the
+// capacity / by the list itself, lists of rows 0 .. of a prompt in a cache of 32768: 24 rows 21.0 / 27.7 / 17.1, 100 22.8 /
+// 26.0 / 18.3, 257 22.9 / 32.4 / 25.0, 333 36.1 / 45.0 / 36.6, 513 46.9 / 62.8 / 50.3: what is left is an empty merge.)
+constexpr int kShortTiles = 4;
+
+// The last n_whole rows whole, the others in `ns` pieces each, of 32-entry multiples (fewer where the list has fewer tiles).
 AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, int64_t n_whole,
                      int64_t ns, bool f32) {
   AttnPlan pl{};
   pl.n_split = 1;
-  pl.split_len = k_cap;
   const bool mla = p->latent != 0;
   if (ns > cdiv(k_cap, 32)) ns = cdiv(k_cap, 32);
   if (ns > 1) {
     const int64_t len = (int64_t)round_up((size_t)cdiv(k_cap, ns), 32);
-    pl.split_len = (int)len;
     pl.n_split = (int)cdiv(k_cap, len);
   }
   pl.n_whole = pl.n_split > 1 ? n_whole : 0;
+  pl.short_tiles = pl.n_whole > 0 ? (int)(cdiv(k_cap, 32) / 2) : kShortTiles;
   pl.f32 = f32;
   size_t off = 0;
   // (paged MQA calls bring room for a translated list, as they had to when a kernel of its own made it)
@@ -283,19 +290,27 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int3
   return f32 ? plan_pieces(p, n_rows, k_cap, paged, n_rows - rem, best, true) : pl;
 }
 
-// The plan of a call with this workspace (which covers plan_least's).
-AttnPlan plan_call(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, const void* ws,
+// The plan of a call with this workspace (which covers plan_least's). The lists' lengths are on the device; what
+// the host knows is how many positions they can name (the cache, or a sequence's page table). Where that is less
+// than the capacity, whole prompts and contexts are listed: few rows are planned for lists of that length, and from
+// kCus rows on all are taken whole, their lengths being those of a prompt's first rows. (The same rows with a cache
+// of their own length: 24 rows 21.2 / 27.7 / 13.8, 100 22.7 / 25.9 / 13.9, 257 23.2 / 32.5 / 22.1, 513 47.2 / 62.7 / 46.2.)
+AttnPlan plan_call(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int64_t positions, int32_t paged, const void* ws,
                    size_t ws_bytes) {
+  auto fits = [&](const AttnPlan& pl) { return pl.total == 0 || (ws != nullptr && aligned(ws, 256) && ws_bytes >= pl.total); };
+  if (positions < k_cap) {
+    const AttnPlan pl = n_rows < kCus ? plan_attn(p, n_rows, (int32_t)positions, paged) : plan_pieces(p, n_rows, k_cap, paged, 0, 1, false);
+    if (fits(pl)) return pl;
+  }
   const AttnPlan pl = plan_attn(p, n_rows, k_cap, paged);
-  const bool fits = pl.total == 0 || (ws != nullptr && aligned(ws, 256) && ws_bytes >= pl.total);
-  return fits ? pl : plan_least(p, n_rows, k_cap, paged);
+  return fits(pl) ? pl : plan_least(p, n_rows, k_cap, paged);
 }
 
 // The plan's pieces and, when there are several, its partials in the workspace.
 void set_plan(lsa::AttnGeom& a, const AttnPlan& pl, uint8_t* ws) {
   a.n_whole = pl.n_whole;
   a.n_split = pl.n_split;
-  a.split_len = pl.split_len;
+  a.short_tiles = pl.short_tiles;
   if (pl.n_split > 1) {
     if (pl.f32) a.part_f32 = reinterpret_cast<float*>(ws + pl.off_po);
     else a.part_o = reinterpret_cast<uint16_t*>(ws + pl.off_po);
@@ -605,7 +620,7 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
-  const AttnPlan pl = plan_call(p, n_rows, k_cap, paged, workspace, ws_bytes);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, paged ? (int64_t)max_pages * kv_page_size : n_kv_rows, paged, workspace, ws_bytes);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
@@ -690,7 +705,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
     return lsa_sparse_attn(p, n_rows, q, kv, v, n_kv_rows, idx, count, k_cap, page_table, max_pages, kv_page_size,
                            rows_per_seq, out, lse, ws + head, ws_bytes - head, stream);
   }
-  const AttnPlan pl = plan_call(p, n_rows, k_cap, 0, workspace, ws_bytes);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, n_kv_rows, 0, workspace, ws_bytes);
   lsa::AttnGeom a{};
   a.q = static_cast<const uint16_t*>(q);
   a.kv = static_cast<const uint16_t*>(kv);
@@ -749,7 +764,7 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
 
   // the lists with their windows as contiguous rows, in as many pieces as the workspace has partials
   const int32_t cap = k_cap > k_swa ? k_cap : k_swa;  // entries a row can have
-  AttnPlan pl = plan_attn(p, n_rows, cap, 0);
+  AttnPlan pl = plan_call(p, n_rows, cap, q_start + n_rows, 0, workspace, ws_bytes);
   if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 0, n_rows < kCus ? 2 : 1, false);  // (two per row always fit)
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   lsa::AttnGeom a{};

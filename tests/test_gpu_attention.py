@@ -275,10 +275,10 @@ def test_many_rows_mixed_lists():
 
 @pytest.mark.parametrize("n_rows,k_cap", [(257, 400), (333, 2308), (300, 33), (511, 700), (600, 1500)])
 def test_rows_left_over_a_round(n_rows, k_cap):
-    """Calls of 256 rows or more whose last rows do not fill the CUs cut those rows' lists into pieces: one
-    row of 13 tiles, 77 in three pieces, 44 of two tiles, 255 (kept whole) and 88 after two rounds, with an
-    empty row and a short one among them; against the oracle, and with a workspace that holds no partials
-    (every row whole, as before), within two roundings of each other."""
+    """Calls of 256 rows or more that are no whole rounds of the CUs cut the lists of the rows over the rounds, the
+    first ones, into pieces: 77 rows in three pieces and 88 beside two rounds; kept whole: one row of 13 tiles, 44
+    of two, 255 rows; with short rows and empty ones among them; against the oracle, and with a workspace that
+    holds no partials (every row whole), within two roundings of each other."""
     from dataclasses import replace
     w = replace(W.SMALL_MLA, seq_len=6000)
     n_kv = w.seq_len
@@ -288,6 +288,7 @@ def test_rows_left_over_a_round(n_rows, k_cap):
     cnt[::7] = g.integers(1, k_cap + 1, cnt[::7].size)
     if n_rows % 256 > 3:
         cnt[-2], cnt[-3] = 0, 1
+        cnt[1], cnt[2] = 0, 1
     idx = np.full((n_rows, k_cap), -1, np.int32)
     for i, c in enumerate(cnt):
         idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
@@ -297,12 +298,57 @@ def test_rows_left_over_a_round(n_rows, k_cap):
     ow, lw = lsa.sparse_attn(w.attn_params(), P.bf16_dev(a["q"][rows]), P.bf16_dev(a["kv"]), None, P.to_dev(idx), P.to_dev(cnt),
                              workspace=tiny)
     ow, lw = ow.float().cpu().numpy(), lw.cpu().numpy()
-    sel = [i for i in list(range(0, 250, 50)) + list(range(256, n_rows, 11)) + [n_rows - 1] if cnt[i] > 0]
+    sel = [i for i in list(range(0, 250, 12)) + list(range(256, n_rows, 11)) + [n_rows - 1] if cnt[i] > 0]
     for i in np.nonzero(cnt == 0)[0]:
         assert np.all(o[i] == 0) and np.all(np.isneginf(l[i]))
     _check_rows(w, a, sel, idx[sel], cnt[sel], o[sel], l[sel])
     full = cnt > 0
     assert np.max(np.abs(o[full] - ow[full])) <= 2e-2 and np.max(np.abs(l[full] - lw[full])) <= 2e-3
+
+
+@pytest.mark.parametrize("n_kv", [1500, 6000])
+@pytest.mark.parametrize("n_rows", [3, 40, 300])
+def test_lists_shorter_than_capacity(n_rows, n_kv):
+    """Calls planned in pieces whose lists are shorter than the capacity (2308): empty, one piece's alone (up to
+    four tiles in calls of few rows, up to half the capacity beside whole rows: that piece writes the output),
+    just over that, a piece short and full, in a cache of fewer positions than the capacity and of more; the
+    workspace holds NaN beforehand (what no piece wrote is not read). List and run form and, for the
+    last rows of a prompt, the split operator, against the oracle."""
+    from dataclasses import replace
+    w = replace(W.SMALL_MLA, seq_len=n_kv)
+    k_cap = 2308
+    a = _attn_inputs(w, 0, n_rows, n_kv)
+    g = np.random.default_rng(37)
+    lengths = [1, 128, 129, 0, 31, 33, 160, 640, 1153, 1152, 1184, 1185, min(n_kv, k_cap), 1472]
+    cnt = np.array([lengths[i % len(lengths)] for i in range(n_rows)], np.int32)
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    runs = np.zeros((n_rows, k_cap, 2), np.int32)
+    for i, c in enumerate(cnt):
+        idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
+        runs[i, :c, 0], runs[i, :c, 1] = idx[i, :c], 1
+    prm = w.attn_params()
+    q, kv = P.bf16_dev(a["q"]), P.bf16_dev(a["kv"])
+    ws = torch.full((lsa.attn_workspace_size(prm, n_rows, k_cap, False),), 255, dtype=torch.uint8, device="cuda")
+    o, l = lsa.sparse_attn(prm, q, kv, None, P.to_dev(idx), P.to_dev(cnt), workspace=ws)
+    o2, l2 = lsa.sparse_attn_runs(prm, q, kv, P.to_dev(runs), P.to_dev(cnt), workspace=ws.fill_(255))
+    assert torch.equal(o, o2) and torch.equal(l, l2)
+    o, l = o.float().cpu().numpy(), l.cpu().numpy()
+    rows = [i for i in range(n_rows) if i < 50 or i % 17 == 0]
+    for i in rows:
+        if cnt[i] == 0:
+            assert np.all(o[i] == 0) and np.all(np.isneginf(l[i]))
+    rows = [i for i in rows if cnt[i] > 0]
+    _check_rows(w, a, rows, idx[rows], cnt[rows], o[rows], l[rows])
+    q0 = n_kv - n_rows      # the split operator: the listed part ends before the window [t - 63, t]
+    for i in range(n_rows):
+        t, c = q0 + i, max(int(cnt[i]), 64)
+        cnt[i] = c
+        idx[i, :c - 64] = np.sort(g.choice(t - 63, c - 64, replace=False)) if c <= t - 63 else np.arange(c - 64)
+        idx[i, c - 64:c] = np.arange(t - 63, t + 1)
+    ws = torch.full((lsa.hfa_workspace_size(prm, 300),), 255, dtype=torch.uint8, device="cuda")
+    o, l = lsa.hfa_attn(prm, q, kv, P.to_dev(idx), P.to_dev(cnt), q0, 64, workspace=ws)
+    rows = rows[:30]
+    _check_rows(w, a, rows, idx[rows], cnt[rows], o.float().cpu().numpy()[rows], l.cpu().numpy()[rows])
 
 
 def test_mqa_long_lists():
