@@ -761,13 +761,13 @@ __global__ __launch_bounds__(64 * W) void mqa_attn_kernel(AttnGeom a) {
   int pr1 = cache_row(e1);           // and of the next
   if (wv < ntiles) request(pr);
   for (int it = wv; it < ntiles; it += W) {
-    __builtin_amdgcn_wave_barrier();  // (the wave's own LDS rows: written after the last tile's reads)
+    wave_lds_order();  // (the wave's own LDS rows: written after the last tile's reads)
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       *reinterpret_cast<u32x4*>(lk + (4 * k + g) * kMqaKStride + i16 * 16) = kr[k];
       *reinterpret_cast<u32x4*>(lv + (4 * k + g) * kMqaVStride + i16 * 16) = vr[k];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     const uint32_t vmask = (uint32_t)__ballot(pr >= 0);
     pr = pr1;
     if (it + W < ntiles) request(pr);

@@ -102,6 +102,11 @@ __device__ __forceinline__ void lds_done_barrier() {
 // Full workgroup barrier with LDS visibility (ordinary ds_write -> ds_read hand-off).
 __device__ __forceinline__ void block_sync() { __syncthreads(); }
 
+// LDS accesses of one wave before and after this point keep their order. The hardware runs a wave's LDS
+// instructions in order, so no instruction is needed; but the compiler reasons about one lane, for which a store and a
+// load of another lane's data are independent (a wave barrier does not tell it otherwise: it touches no memory).
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // ---------------------------------------------------------------- direct global -> LDS loads
 // LDS byte address of a pointer into __shared__ memory (the low 32 bits of its generic address).
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
