@@ -216,9 +216,9 @@ typedef struct lsa_attn_params {
   float sm_scale;  /* softmax scale applied to q . k                                           */
 } lsa_attn_params;
 
-/* Workspace bytes for lsa_sparse_attn: non-zero for paged MQA calls and for MLA calls whose rows do not
- * fill the GPU's 256 CUs evenly, where rows are cut into pieces. (A call of 256 rows or more that brings
- * less takes every row whole.) */
+/* Workspace bytes for lsa_sparse_attn: non-zero for MLA calls whose rows do not fill the GPU's 256 CUs
+ * evenly, where rows are cut into pieces. (A call of 256 rows or more that brings less takes every row
+ * whole.) */
 size_t lsa_sparse_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap,
                                       int32_t paged);
 
@@ -273,13 +273,16 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
  * lsa_sparse_attn over S_t, where only the part of S_t before its sliding window is read from the list
  * (sink and sparse positions: the first count[r] - min(k_swa, t+1) entries of the ascending list), and
  * the window [t - k_swa + 1, t] is taken as contiguous cache rows. One pass over both on the caller's
- * stream (calls of few rows: in two pieces merged by online-softmax rescaling). MLA latent cache only,
+ * stream (rows cut into pieces are merged by online-softmax rescaling). MLA latent cache only,
  * contiguous cache only.
  *   q_start    position t of row 0 (row r is the query at t = q_start + r); q_start + n_rows <=
  *              n_kv_rows
  *   k_swa      the indexer's window size: idx must end with the whole window of each row, as
  *              lsa_index_prefill writes it (rows shorter than the window hold [0, t])
- *   workspace  >= lsa_hfa_attn_workspace_size(p, n_rows) bytes, 256-byte aligned (the partials)
+ *   workspace  lsa_hfa_attn_workspace_size(p, n_rows) bytes (at most 68 MB), 256-byte aligned: the partials
+ *              of rows cut into pieces over idle CUs, as in lsa_sparse_attn. A call of fewer than 256 rows that
+ *              brings less, but 2 * 64 * (512 * 2 + 2 * 4) bytes per row, cuts each row in two; from 256 rows
+ *              on a smaller one or NULL leaves every row whole
  * Other arguments as lsa_sparse_attn.
  */
 size_t lsa_hfa_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows);

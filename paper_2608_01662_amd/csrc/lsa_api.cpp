@@ -226,7 +226,7 @@ constexpr int64_t kCus = 256;
 constexpr int kShortTiles = 4;
 
 // The last n_whole rows whole, the others in `ns` pieces each, of 32-entry multiples (fewer where the list has fewer tiles).
-AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged, int64_t n_whole,
+AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int64_t n_whole,
                      int64_t ns, bool f32) {
   AttnPlan pl{};
   pl.n_split = 1;
@@ -240,8 +240,6 @@ AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, in
   pl.short_tiles = pl.n_whole > 0 ? (int)(cdiv(k_cap, 32) / 2) : kShortTiles;
   pl.f32 = f32;
   size_t off = 0;
-  // (paged MQA calls bring room for a translated list, as they had to when a kernel of its own made it)
-  if (paged && !mla) off += round_up((size_t)n_rows * k_cap * 4, 256);
   const size_t pieces = pl.n_split > 1 ? (size_t)(n_rows - pl.n_whole) * pl.n_split : 0;
   pl.off_po = off;
   off += round_up(pieces * p->n_heads * p->d_v * (pl.f32 ? 4 : 2), 256);
@@ -252,9 +250,9 @@ AttnPlan plan_pieces(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, in
 }
 
 // The plan whose workspace every call must bring: one piece per CU for calls of fewer rows than CUs.
-AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
   const bool few = p->latent != 0 && n_rows > 0 && n_rows < kCus;
-  return plan_pieces(p, n_rows, k_cap, paged, 0, few ? cdiv(kCus, n_rows) : 1, false);
+  return plan_pieces(p, n_rows, k_cap, 0, few ? cdiv(kCus, n_rows) : 1, false);
 }
 
 // The plan used when the workspace has room for it. Rounds of kCus whole rows, and the n_rows mod kCus
@@ -268,7 +266,7 @@ AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int
 // rows 150 and 136, 513 rows 224 and 195. Cut only where the count promises 5%: 400 rows took 165 us in
 // pieces and 161 whole. The error against 64 bits stays or falls (100 rows 2.50e-3 to 2.06e-3).
 constexpr int64_t kMaxPieces = 512;  // bounds the partials (33 MB, 67 in fp32)
-AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
+AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
   const int64_t rem = n_rows % kCus, tiles = cdiv(k_cap, 32);
   int64_t best = 1;
   if (p->latent != 0 && rem > 0) {
@@ -285,9 +283,9 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int3
   }
   // Partials in bf16 (half the merge's traffic: 46 against 51 us at 64 rows) round every piece once more,
   // which averages out over a row's pieces: rows in fewer pieces than plan_least's keep fp32 ones.
-  const AttnPlan pl = plan_pieces(p, n_rows, k_cap, paged, n_rows - rem, best, false);
-  const bool f32 = pl.n_whole > 0 || pl.n_split < plan_least(p, n_rows, k_cap, paged).n_split;
-  return f32 ? plan_pieces(p, n_rows, k_cap, paged, n_rows - rem, best, true) : pl;
+  const AttnPlan pl = plan_pieces(p, n_rows, k_cap, n_rows - rem, best, false);
+  const bool f32 = pl.n_whole > 0 || pl.n_split < plan_least(p, n_rows, k_cap).n_split;
+  return f32 ? plan_pieces(p, n_rows, k_cap, n_rows - rem, best, true) : pl;
 }
 
 // The plan of a call with this workspace (which covers plan_least's). The lists' lengths are on the device; what
@@ -295,15 +293,15 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int3
 // than the capacity, whole prompts and contexts are listed: few rows are planned for lists of that length, and from
 // kCus rows on all are taken whole, their lengths being those of a prompt's first rows. (The same rows with a cache
 // of their own length: 24 rows 21.2 / 27.7 / 13.8, 100 22.7 / 25.9 / 13.9, 257 23.2 / 32.5 / 22.1, 513 47.2 / 62.7 / 46.2.)
-AttnPlan plan_call(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int64_t positions, int32_t paged, const void* ws,
+AttnPlan plan_call(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int64_t positions, const void* ws,
                    size_t ws_bytes) {
   auto fits = [&](const AttnPlan& pl) { return pl.total == 0 || (ws != nullptr && aligned(ws, 256) && ws_bytes >= pl.total); };
   if (positions < k_cap) {
-    const AttnPlan pl = n_rows < kCus ? plan_attn(p, n_rows, (int32_t)positions, paged) : plan_pieces(p, n_rows, k_cap, paged, 0, 1, false);
+    const AttnPlan pl = n_rows < kCus ? plan_attn(p, n_rows, (int32_t)positions) : plan_pieces(p, n_rows, k_cap, 0, 1, false);
     if (fits(pl)) return pl;
   }
-  const AttnPlan pl = plan_attn(p, n_rows, k_cap, paged);
-  return fits(pl) ? pl : plan_least(p, n_rows, k_cap, paged);
+  const AttnPlan pl = plan_attn(p, n_rows, k_cap);
+  return fits(pl) ? pl : plan_least(p, n_rows, k_cap);
 }
 
 // The plan's pieces and, when there are several, its partials in the workspace.
@@ -318,8 +316,8 @@ void set_plan(lsa::AttnGeom& a, const AttnPlan& pl, uint8_t* ws) {
   }
 }
 
-size_t attn_ws_bytes(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
-  const size_t a = plan_attn(p, n_rows, k_cap, paged).total, b = plan_least(p, n_rows, k_cap, paged).total;
+size_t attn_ws_bytes(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
+  const size_t a = plan_attn(p, n_rows, k_cap).total, b = plan_least(p, n_rows, k_cap).total;
   return a > b ? a : b;
 }
 
@@ -590,7 +588,7 @@ lsa_status lsa_index_decode_static(const lsa_index_params* p, int32_t batch, con
 
 size_t lsa_sparse_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || k_cap < 1) return 0;
-  return attn_ws_bytes(p, n_rows, k_cap, paged);
+  return attn_ws_bytes(p, n_rows, k_cap);
 }
 
 lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv, const void* v,
@@ -616,11 +614,11 @@ lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void*
   if (paged)
     LSA_REQUIRE(max_pages >= 1 && kv_page_size >= 1 && rows_per_seq >= 1, LSA_ERR_INVALID_ARG,
                 "paged cache needs max_pages, kv_page_size and rows_per_seq >= 1");
-  const size_t need = plan_least(p, n_rows, k_cap, paged).total;
+  const size_t need = plan_least(p, n_rows, k_cap).total;
   LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
-  const AttnPlan pl = plan_call(p, n_rows, k_cap, paged ? (int64_t)max_pages * kv_page_size : n_kv_rows, paged, workspace, ws_bytes);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, paged ? (int64_t)max_pages * kv_page_size : n_kv_rows, workspace, ws_bytes);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
@@ -660,7 +658,7 @@ static size_t runs_list_bytes(int64_t n_rows, int32_t k_cap) {
 
 size_t lsa_sparse_attn_runs_workspace_size(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap, int32_t paged) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || k_cap < 1) return 0;
-  const size_t attn = attn_ws_bytes(p, n_rows, k_cap, paged);
+  const size_t attn = attn_ws_bytes(p, n_rows, k_cap);
   return runs_fused(p, paged != 0) ? attn : runs_list_bytes(n_rows, k_cap) + attn;
 }
 
@@ -688,7 +686,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
   if (paged)
     LSA_REQUIRE(max_pages >= 1 && kv_page_size >= 1 && rows_per_seq >= 1, LSA_ERR_INVALID_ARG,
                 "paged cache needs max_pages, kv_page_size and rows_per_seq >= 1");
-  const size_t need = (runs_fused(p, paged) ? 0 : runs_list_bytes(n_rows, k_cap)) + plan_least(p, n_rows, k_cap, paged).total;
+  const size_t need = (runs_fused(p, paged) ? 0 : runs_list_bytes(n_rows, k_cap)) + plan_least(p, n_rows, k_cap).total;
   LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
@@ -705,7 +703,7 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
     return lsa_sparse_attn(p, n_rows, q, kv, v, n_kv_rows, idx, count, k_cap, page_table, max_pages, kv_page_size,
                            rows_per_seq, out, lse, ws + head, ws_bytes - head, stream);
   }
-  const AttnPlan pl = plan_call(p, n_rows, k_cap, n_kv_rows, 0, workspace, ws_bytes);
+  const AttnPlan pl = plan_call(p, n_rows, k_cap, n_kv_rows, workspace, ws_bytes);
   lsa::AttnGeom a{};
   a.q = static_cast<const uint16_t*>(q);
   a.kv = static_cast<const uint16_t*>(kv);
@@ -725,14 +723,20 @@ lsa_status lsa_sparse_attn_runs(const lsa_attn_params* p, int64_t n_rows, const 
 }
 
 // ---------------------------------------------------------------- split attention (HFA)
-// Rows that the workspace of lsa_hfa_attn covers with two partials each (bf16 values, fp32 maximum and
-// sum per head).
-constexpr int64_t kHfaRows = 16384;
+// Bytes of `pieces` partials of all heads: values, maximum and sum.
+static size_t partial_bytes(int64_t pieces, size_t value) {
+  return round_up((size_t)pieces * 64 * 512 * value, 256) + round_up((size_t)pieces * 64 * 2 * 4, 256);
+}
 
+// What a call must bring: two bf16 pieces per row in calls of few rows.
+static size_t hfa_least_bytes(int64_t n_rows) { return n_rows < kCus ? partial_bytes(2 * n_rows, 2) : 0; }
+
+// Room for the pieces of any plan_attn (fp32, whatever the lists' capacity).
 size_t lsa_hfa_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows) {
   if (check_attn_params(p) != LSA_OK || n_rows < 0 || p->latent == 0) return 0;
-  const size_t r = (size_t)(n_rows < kHfaRows ? n_rows : kHfaRows);
-  return round_up(r * 2 * 64 * 512 * 2, 256) + round_up(r * 2 * 64 * 2 * 4, 256);
+  const int64_t rem = n_rows % kCus, most = n_rows < kCus ? kCus : kMaxPieces;
+  const size_t least = hfa_least_bytes(n_rows), all = rem > 0 ? partial_bytes(most / rem * rem, 4) : 0;
+  return all > least ? all : least;
 }
 
 lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv, int64_t n_kv_rows,
@@ -757,15 +761,15 @@ lsa_status lsa_hfa_attn(const lsa_attn_params* p, int64_t n_rows, const void* q,
               "q, kv and out must be 16-byte aligned");
   LSA_REQUIRE(aligned(idx, 4) && aligned(count, 4) && aligned(lse, 4), LSA_ERR_INVALID_ARG,
               "idx, count and lse must be 4-byte aligned");
-  const size_t need = lsa_hfa_attn_workspace_size(p, n_rows);
-  LSA_REQUIRE(workspace != nullptr && aligned(workspace, 256), LSA_ERR_WORKSPACE,
+  const size_t need = hfa_least_bytes(n_rows);
+  LSA_REQUIRE(need == 0 || (workspace != nullptr && aligned(workspace, 256)), LSA_ERR_WORKSPACE,
               "workspace must be non-NULL and 256-byte aligned");
   LSA_REQUIRE(ws_bytes >= need, LSA_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", ws_bytes, need);
 
   // the lists with their windows as contiguous rows, in as many pieces as the workspace has partials
   const int32_t cap = k_cap > k_swa ? k_cap : k_swa;  // entries a row can have
-  AttnPlan pl = plan_call(p, n_rows, cap, q_start + n_rows, 0, workspace, ws_bytes);
-  if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 0, n_rows < kCus ? 2 : 1, false);  // (two per row always fit)
+  AttnPlan pl = plan_call(p, n_rows, cap, q_start + n_rows, workspace, ws_bytes);
+  if (pl.total > ws_bytes) pl = plan_pieces(p, n_rows, cap, 0, 2, false);  // (of few rows; two per row always fit)
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   lsa::AttnGeom a{};
   a.q = static_cast<const uint16_t*>(q);

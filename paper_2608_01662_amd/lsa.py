@@ -476,9 +476,7 @@ def hfa_attn(prm: AttnParams, q: torch.Tensor, kv: torch.Tensor, idx: torch.Tens
     _need("idx", idx, _I32, (n_rows, None), q.device)
     k_cap = idx.shape[1]
     _need("count", count, _I32, (n_rows,), q.device)
-    # (with the list form's workspace a call of few rows is split over the GPU as that one is)
-    ws, wsb = _workspace(max(hfa_workspace_size(prm, n_rows), attn_workspace_size(prm, n_rows, max(k_cap, k_swa), False)),
-                         q.device, workspace)
+    ws, wsb = _workspace(hfa_workspace_size(prm, n_rows), q.device, workspace)
     _check(lib().lsa_hfa_attn(_ref(prm), n_rows, _p(q), _p(kv), n_kv_rows, _p(idx), _p(count), k_cap,
                               q_start, k_swa, _p(out), _p(lse), _p(ws), wsb, _stream(q.device)), "lsa_hfa_attn")
     return out, lse

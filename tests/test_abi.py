@@ -209,6 +209,8 @@ def test_bad_run_form_attention_arguments():
     # MQA and paged caches expand the runs into a list at the head of the workspace
     need = L.lsa_sparse_attn_runs_workspace_size(ctypes.byref(mqa.c()), 8, 64, 0)
     assert need >= 8 * 64 * 4 + 8 * 4
+    assert need < 2 * (8 * 64 * 4 + 8 * 4) and need == L.lsa_sparse_attn_runs_workspace_size(ctypes.byref(mqa.c()), 8, 64, 1)
+    assert L.lsa_sparse_attn_workspace_size(ctypes.byref(mqa.c()), 8, 64, 1) == 0     # (positions translated as the list is read)
     assert att(prm=mqa, v=FAKE, wsb=need - 1) == WORKSPACE
     assert L.lsa_sparse_attn_runs_workspace_size(ctypes.byref(mla.c()), 131072, 3076, 0) == 0   # fused, no list
     assert L.lsa_sparse_attn_runs_workspace_size(ctypes.byref(mla.c()), 64, 2308, 1) > 64 * 2308 * 4
@@ -234,10 +236,18 @@ def test_bad_split_attention_arguments():
     assert hfa(ws=None) == WORKSPACE
     assert hfa(wsb=16) == WORKSPACE
     assert hfa(n_rows=0, q=None, idx=None, cnt=None, out=None, ws=None, wsb=0) == OK
-    # two partials per row and head (O normalised, in bf16, and (m, l) in fp32), for at most 16384
-    # rows per pass
-    assert L.lsa_hfa_attn_workspace_size(ctypes.byref(mla.c()), 100) == 100 * 2 * 64 * (512 * 2 + 2 * 4)
-    assert L.lsa_hfa_attn_workspace_size(ctypes.byref(mla.c()), 131072) == 16384 * 2 * 64 * (512 * 2 + 2 * 4)
+    # required: below 256 rows two partials per row and head (O normalised, in bf16, and (m, l) in fp32)
+    two = 8 * 2 * 64 * (512 * 2 + 2 * 4)
+    assert hfa(wsb=two - 1) == WORKSPACE and b"needed" in L.lsa_last_error()
+    # the size: room for fp32 partials of the most pieces a plan has, 256 in calls of fewer rows, 512 for the
+    # rows over whole rounds of 256, none in whole rounds
+    size = lambda n: L.lsa_hfa_attn_workspace_size(ctypes.byref(mla.c()), n)
+    piece = 64 * (512 * 4 + 2 * 4)
+    assert [size(n) for n in (0, 1, 100, 256, 257, 333, 131072)] == [0, 256 * piece, 200 * piece, 0, 512 * piece, 462 * piece, 0]
+    assert size(200) == 200 * 2 * 64 * (512 * 2 + 2 * 4)
+    for n in list(range(1, 700, 7)) + [1000, 8191]:    # every plan fits it
+        for k_cap in (1, 33, 100, 700, 2308, 3076, 9000, 60000):
+            assert size(n) >= L.lsa_sparse_attn_workspace_size(ctypes.byref(mla.c()), n, k_cap, 0), (n, k_cap)
 
 
 def test_workspace_sizes():

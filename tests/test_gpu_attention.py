@@ -718,8 +718,8 @@ def test_split_attention_parity(w, q0, n_q):
 
 @pytest.mark.parametrize("q0,n_q,ws_rows", [(0, 1, 1), (900, 1, 1), (0, 40, 40), (501, 5, 5), (501, 5, None), (130, 129, None), (100, 257, 257)])
 def test_split_attention_few_rows(q0, n_q, ws_rows):
-    """Split attention of few rows: whole lists and lists cut into pieces (two with the smallest workspace,
-    more with the list form's), pieces that start inside the window, rows shorter than the window, and a
+    """Split attention of few rows: whole lists and lists cut into pieces (two with the smallest workspace, more
+    with the whole one), pieces that start inside the window, rows shorter than the window, and a
     row whose count is smaller than its window (nothing is listed, the window is attended whole), every
     row against the oracle."""
     w = W.SMALL_MLA
@@ -731,7 +731,7 @@ def test_split_attention_few_rows(q0, n_q, ws_rows):
         cut[3] = 3
     ws = None
     if ws_rows is not None:
-        ws = torch.empty(lsa.hfa_workspace_size(w.attn_params(), ws_rows), dtype=torch.uint8, device="cuda")
+        ws = torch.empty(ws_rows * 2 * 64 * (512 * 2 + 2 * 4), dtype=torch.uint8, device="cuda")
     o, l = lsa.hfa_attn(w.attn_params(), P.bf16_dev(a["q"][rows]), P.bf16_dev(a["kv"]), P.to_dev(idx), P.to_dev(cut), q0,
                         w.k_swa, workspace=ws)
     o, l = o.float().cpu().numpy(), l.cpu().numpy()
