@@ -156,6 +156,36 @@ def check_attention_row(o_gpu, lse_gpu, o_ref, lse_ref, where=""):
     return mx, rel
 
 
+# ----------------------------------------------------------------------------- attention plans
+def attn_pieces(n_rows, k_cap):
+    """(rows cut into pieces, pieces per row, fp32 partials) of an MLA call over a cache of at least k_cap positions
+    with the whole workspace, as lsa_api.cpp's plan_attn has them, so that a test can choose its shapes by the
+    path they take (test_abi.py holds this against the library's workspace sizes)."""
+    cdiv = lambda a, b: -(-a // b)
+
+    def pieces(ns):    # pieces of whole 32-entry tiles
+        ns = min(ns, cdiv(k_cap, 32))
+        return cdiv(k_cap, cdiv(cdiv(k_cap, ns), 32) * 32)
+    few = n_rows < 256
+    rem, tiles = n_rows % 256, cdiv(k_cap, 32)
+    tile, part, most = (1.6, 0.03, 256) if few else (1.0, 0.06, 512)
+    best, least = 1, 0.95 * (tile * tiles + 9)
+    for ns in range(2, min(tiles, most // rem) + 1 if rem else 2):
+        cost = cdiv(rem * ns, 256) * (tile * cdiv(tiles, ns) + 9) + 5 + part * rem * ns
+        if cost < least:
+            best, least = ns, cost
+    ns = pieces(best)
+    if ns == 1:
+        return 0, 1, False
+    return rem, ns, not few or ns < pieces(cdiv(256, n_rows))
+
+
+def attn_partial_bytes(n_rows, k_cap):
+    """Workspace bytes of that plan."""
+    rows, ns, f32 = attn_pieces(n_rows, k_cap)
+    return rows * ns * 64 * (512 * (4 if f32 else 2) + 8) if ns > 1 else 0
+
+
 # ----------------------------------------------------------------------------- input plumbing
 def to_dev(a, dtype=None):
     t = torch.from_numpy(np.ascontiguousarray(a))

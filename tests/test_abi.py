@@ -261,6 +261,26 @@ def test_workspace_sizes():
     assert L.lsa_sparse_attn_workspace_size(ctypes.byref(mla.c()), 64, 2308, 1) > 64 * 2308 * 4
 
 
+def test_attention_plan_mirror():
+    """The workspace size of MLA calls is the larger of the plan's partials (tests/parity.py has the plan) and
+    of one bf16 piece per CU for calls of fewer rows than CUs, which every such call must bring."""
+    from tests import parity
+    L = lsa.lib()
+    mla = lsa.AttnParams(sm_scale=0.07, **lsa.MLA)
+    cdiv = lambda a, b: -(-a // b)
+    seen = set()
+    for n in list(range(1, 300)) + [333, 400, 511, 512, 513, 600, 700, 767, 1025, 8190]:
+        for k_cap in (1, 32, 33, 96, 160, 256, 320, 400, 700, 1500, 2308, 2564, 2600, 3076, 8192, 9000, 57344):
+            least = 0
+            if n < 256:
+                per = cdiv(cdiv(k_cap, min(cdiv(256, n), cdiv(k_cap, 32))), 32) * 32
+                least = n * cdiv(k_cap, per) * 64 * (512 * 2 + 8) if k_cap > per else 0
+            want = max(least, parity.attn_partial_bytes(n, k_cap))
+            assert L.lsa_sparse_attn_workspace_size(ctypes.byref(mla.c()), n, k_cap, 0) == want, (n, k_cap)
+            seen.add(parity.attn_pieces(n, k_cap)[1:])
+    assert {(1, False), (256, False), (8, False), (8, True), (9, True), (10, False)} <= seen
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(lsa, "LIB_PATH", str(tmp_path / "missing.so"))
     monkeypatch.setattr(lsa, "_lib", None)

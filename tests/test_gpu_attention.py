@@ -217,15 +217,18 @@ def test_long_lists_beyond_one_staging_pass():
         P.check_attention_row(o[i], l[i], oref, lref, f"row {i} ({cnt[i]} entries)")
 
 
-@pytest.mark.parametrize("n_rows,k_cap", [(1, 2308), (1, 8192), (2, 96), (3, 2600), (28, 2308), (29, 2308), (32, 2308)],
-                         ids=lambda v: str(v))
-def test_split_merge_counts(n_rows, k_cap):
-    """The merge of split lists at its edges: 73 pieces and the largest count (256, one tile each) for one
-    row, three pieces of one tile, 82 pieces, and the counts on both sides of the switch between its two
-    kernels (10, 9 and 8 pieces), with one row shorter than a piece (the others of its pieces are empty)
-    and one empty row, against the oracle."""
+@pytest.mark.parametrize("n_rows,k_cap,pieces,f32", [
+    (1, 2308, 73, False), (1, 57344, 256, False), (1, 8192, 128, True), (2, 96, 1, False), (2, 160, 5, False), (2, 256, 8, False),
+    (2, 288, 9, False), (2, 320, 10, False), (3, 2600, 41, True), (25, 2308, 10, True), (28, 2308, 9, True), (29, 2308, 8, True),
+    (32, 2308, 8, False)], ids=lambda v: str(v))
+def test_split_merge_counts(n_rows, k_cap, pieces, f32):
+    """The merge of lists cut into pieces at its edges: one row of 73 pieces and of the largest count (256, seven
+    tiles each), a list kept whole, few pieces of one tile, 41, and the counts on both sides of the switch
+    between its two kernels (10, 9 and 8 pieces), with bf16 and fp32 partials, with one row of one piece, one of more
+    pieces without entries than with, and one empty row, against the oracle."""
     from dataclasses import replace
-    w = replace(W.SMALL_MLA, seq_len=9000)
+    assert P.attn_pieces(n_rows, k_cap) == (n_rows if pieces > 1 else 0, pieces, f32)
+    w = replace(W.SMALL_MLA, seq_len=max(9000, k_cap + 1000))
     n_kv = w.seq_len
     a = _attn_inputs(w, 0, n_rows, n_kv)
     g = np.random.default_rng(13)
@@ -233,6 +236,8 @@ def test_split_merge_counts(n_rows, k_cap):
     cnt[-1] = k_cap - 7
     if n_rows > 2:
         cnt[0], cnt[1] = 5, 0
+    if n_rows > 3:
+        cnt[2] = 5 * 32 + 3
     idx = np.full((n_rows, k_cap), -1, np.int32)
     for i, c in enumerate(cnt):
         idx[i, :c] = np.sort(g.choice(n_kv, c, replace=False))
@@ -244,20 +249,22 @@ def test_split_merge_counts(n_rows, k_cap):
     _check_rows(w, a, keep, idx[keep], cnt[keep], o[keep], l[keep])
 
 
-def test_many_rows_mixed_lists():
-    """Calls of 256 rows or more run one pass over each row's whole list (no split into pieces):
-    259 rows mixing short lists, empty lists, one exact tile and lists longer than one staging pass
-    (8192 entries, so the list is staged in two passes), against the oracle."""
+@pytest.mark.parametrize("n_rows", [256, 259])
+def test_many_rows_mixed_lists(n_rows):
+    """Calls of 256 rows, each one pass over its whole list, and of 259, whose first three rows are cut into pieces
+    beside 256 whole ones: rows mixing short lists, empty lists, one exact tile and lists longer than one
+    staging pass (8192 entries, so the list is staged in two passes), against the oracle."""
     from dataclasses import replace
     w = replace(W.SMALL_MLA, seq_len=12000)
-    n_kv, n_rows, k_cap = w.seq_len, 259, 9000
+    n_kv, k_cap = w.seq_len, 9000
+    assert P.attn_pieces(n_rows, k_cap) == {256: (0, 1, False), 259: (3, 41, True)}[n_rows]
     H, dqk, dv = w.attn_dims
     a = _attn_inputs(w, 0, n_rows, n_kv)
     g = np.random.default_rng(7)
     counts = g.integers(1, 400, n_rows)
-    for i in (0, 5, 6, 11, 255, 258):
+    for i in (0, 5, 6, 11, 255, n_rows - 1):
         counts[i] = 0                       # empty lists, also first and last of a group
-    for i in (1, 4, 7, 12, 257):
+    for i in (1, 4, 7, 12, n_rows - 2):
         counts[i] = 8193 if i % 2 else 9000  # two staging passes
     counts[2] = 32                           # exactly one tile
     idx = np.full((n_rows, k_cap), -1, np.int32)
@@ -276,10 +283,11 @@ def test_many_rows_mixed_lists():
 @pytest.mark.parametrize("n_rows,k_cap", [(257, 400), (333, 2308), (300, 33), (511, 700), (600, 1500)])
 def test_rows_left_over_a_round(n_rows, k_cap):
     """Calls of 256 rows or more that are no whole rounds of the CUs cut the lists of the rows over the rounds, the
-    first ones, into pieces: 77 rows in three pieces and 88 beside two rounds; kept whole: one row of 13 tiles, 44
-    of two, 255 rows; with short rows and empty ones among them; against the oracle, and with a workspace that
-    holds no partials (every row whole), within two roundings of each other."""
+    first ones, into pieces: one row of 13 tiles, 77 in three pieces and 88 in two beside two rounds; 44 rows of two
+    tiles and 255 rows stay whole; with short rows and empty ones among them; against the oracle, and with a workspace
+    that holds no partials (every row whole), within two roundings of each other."""
     from dataclasses import replace
+    assert P.attn_pieces(n_rows, k_cap)[:2] == {257: (1, 13), 333: (77, 3), 300: (0, 1), 511: (0, 1), 600: (88, 2)}[n_rows]
     w = replace(W.SMALL_MLA, seq_len=6000)
     n_kv = w.seq_len
     a = _attn_inputs(w, 0, n_rows, n_kv)
@@ -683,14 +691,12 @@ def test_attention_determinism():
 @pytest.mark.parametrize("w,q0,n_q", [(W.SMALL_MLA, 0, 1536), (W.SMALL_CLI, 0, 1536), (W.SMALL_CLI, 777, 999)],
                          ids=["small_mla", "small_cli", "small_cli_odd_chunk"])
 def test_split_attention_parity(w, q0, n_q):
-    """Split attention (listed non-window part and contiguous window on two streams, merged by
-    log-sum-exp; the window part runs in the query-tiled kernel, two consecutive rows per
-    workgroup sharing each window tile): every seventh row of a chunk against the oracle's Eq. (3)
-    over the whole list, and every row against the fused kernel. The lists come from the oracle's
-    indexer (the window part is read from the cache, not from the list, so the lists must hold the
-    whole window: they do). Chunks: from position 0 (first rows shorter than the window), and an
-    odd count of rows from an odd position (the last row pair holds one row); one row's list is
-    emptied (count 0: no window either, o = 0 and lse = -inf as in the fused kernel)."""
+    """Split attention (the listed non-window part and then the window as contiguous rows, in one pass): every
+    seventh row of a chunk against the oracle's Eq. (3) over the whole list, and every row against the
+    fused kernel. The lists come from the oracle's indexer (the window part is read from the cache, not from
+    the list, so the lists must hold the whole window: they do). Chunks: from position 0 (first rows shorter
+    than the window), and an odd count of rows from an odd position; one row's list is emptied (count 0: no
+    window either, o = 0 and lse = -inf as in the fused kernel)."""
     n = w.seq_len
     n_q = min(n - q0, n_q)
     rows = list(range(q0, q0 + n_q))
@@ -740,6 +746,47 @@ def test_split_attention_few_rows(q0, n_q, ws_rows):
         win = np.arange(max(0, t - w.k_swa + 1), t + 1, dtype=np.int32)
         idx[3, :win.size], cnt[3] = win, win.size
     _check_rows(w, a, rows, idx, cnt, o, l)
+
+
+@pytest.mark.parametrize("n_rows", [3, 256, 259])
+def test_split_attention_long_windows(n_rows):
+    """Split attention over windows longer than one staging pass of the list (9000 positions after 500 listed
+    ones: 9500 entries, of which 8192 are staged at a time), in pieces (3 rows), whole (256) and both (259),
+    sampled rows against the oracle."""
+    from dataclasses import replace
+    w = replace(W.SMALL_MLA, seq_len=15000)
+    k_swa, k_cap, q0 = 9000, 9500, 14000
+    a = _attn_inputs(w, 0, n_rows, w.seq_len)
+    g = np.random.default_rng(41)
+    t = q0 + np.arange(n_rows)
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    for i in range(n_rows):
+        idx[i, :500] = np.sort(g.choice(t[i] - k_swa + 1, 500, replace=False))
+        idx[i, 500:] = np.arange(t[i] - k_swa + 1, t[i] + 1)
+    cnt = np.full(n_rows, k_cap, np.int32)
+    o, l = lsa.hfa_attn(w.attn_params(), P.bf16_dev(a["q"]), P.bf16_dev(a["kv"]), P.to_dev(idx), P.to_dev(cnt), q0, k_swa)
+    o, l = o.float().cpu().numpy(), l.cpu().numpy()
+    rows = sorted({0, 1, 2, n_rows // 2, n_rows - 1})
+    _check_rows(w, a, rows, idx[rows], cnt[rows], o[rows], l[rows])
+
+
+@pytest.mark.parametrize("k_swa", [1000, 2 ** 31 - 1])
+@pytest.mark.parametrize("n_rows", [40, 256, 300])
+def test_split_attention_window_beyond_capacity(n_rows, k_swa):
+    """Split attention at the start of a sequence with a window longer than the list capacity and the sequence:
+    every row attends to [0, t], whatever its list holds before that, against the oracle."""
+    from dataclasses import replace
+    w = replace(W.SMALL_MLA, seq_len=700)
+    k_cap = 64
+    a = _attn_inputs(w, 0, n_rows, w.seq_len)
+    idx = np.full((n_rows, k_cap), -1, np.int32)
+    idx[:] = np.arange(k_cap)
+    cnt = np.minimum(np.arange(n_rows) + 1, k_cap).astype(np.int32)
+    o, l = lsa.hfa_attn(w.attn_params(), P.bf16_dev(a["q"]), P.bf16_dev(a["kv"]), P.to_dev(idx), P.to_dev(cnt), 0, k_swa)
+    o, l = o.float().cpu().numpy(), l.cpu().numpy()
+    for i in list(range(0, n_rows, 9)) + [n_rows - 1]:
+        oref, lref = orc.attention_for_set(a["q"][i], a["kv"], None, np.arange(i + 1), 512, w.sm_scale)
+        P.check_attention_row(o[i], l[i], oref, lref, f"row {i}")
 
 
 def test_binding_rejects_mismatched_tensors():

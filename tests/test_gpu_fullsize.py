@@ -88,7 +88,7 @@ def _prefill_case(w, q_start, n_q, n_kv, layers, n_random, seed, split_attn=Fals
     for layer in layers:
         Q = synth.device_normal_bf16((n_q, H, dqk), w.seed, synth.T_Q + layer, DEV, rows_per_chunk=2048)
         KV = synth.device_normal_bf16((n_kv, dqk), w.seed, synth.T_KV + layer, DEV)
-        if split_attn:   # listed part and contiguous window on two streams, merged by LSE
+        if split_attn:   # listed part and contiguous window, in one pass
             o, lse = lsa.hfa_attn(w.attn_params(), Q, KV, out["idx"], out["count"], q_start, w.k_swa)
         else:
             o, lse = lsa.sparse_attn(w.attn_params(), Q, KV, None, out["idx"], out["count"])

@@ -221,11 +221,10 @@ def test_index_prefill_parity(w):
 
 
 def test_coarse_long_rows():
-    """Calls whose rows hold more than 64 coarse tiles use the four-wave coarse_kernel over four
-    query rows (keys read straight into the operand layout) instead of the staged one-wave kernel:
-    d_I = 64, 2-token sub-blocks in 64-token pages (32 per page) and L = 8192 give the last rows
-    128 tiles of 32 sub-blocks (coarse_kernel<64, 4, false, false, false>). Sampled rows against
-    the oracle, stage-wise."""
+    """Calls whose rows hold more than 64 coarse tiles use the coarse_kernel of four waves over four query rows
+    with one tile buffer per wave, instead of the one-wave kernel: d_I = 64, 2-token sub-blocks in 64-token
+    pages (32 per page) and L = 8192 give the last rows 128 tiles of 32 sub-blocks
+    (coarse_kernel<64, 4, false, 4, 1>). Sampled rows against the oracle, stage-wise."""
     from dataclasses import replace
     w = replace(W.SMALL_MLA, name="small_L8192_d64_B2", head_dim=64, sub_block=2, seq_len=8192)
     assert (w.seq_len // w.page) * (w.page // w.sub_block) // 32 > 64
@@ -320,9 +319,9 @@ def test_adaptive_dispatch():
     ids=["d128_bf16_hi", "d128_bf16_flat", "d64_fp8_hi", "d64_fp8_flat", "d64_fp8_minmax", "d64_bf16_minmax"])
 def test_index_prefill_other_key_formats(head_dim, fp8, keep_pages, pooling):
     """The kernel instances the five workloads do not reach: bf16 keys with d_I = 128 and fp8 keys
-    with d_I = 64, hierarchical (coarse_kernel<D, 4, false, false>, page select, fine_xcd_kernel)
-    and flat (flat_dense_kernel), and min-max pooling at d_I = 64 (coarse_kernel<64, 2, false,
-    true>), against the oracle on sampled rows."""
+    with d_I = 64, hierarchical (coarse_kernel<D, 3, false, 1, 2>, page select, fine_xcd_kernel)
+    and flat (flat_dense_kernel), and min-max pooling at d_I = 64 (coarse_kernel<64, 2, true, 1, 1>),
+    against the oracle on sampled rows."""
     from dataclasses import replace
     w = replace(W.SMALL_CLI, name=f"small_d{head_dim}_{'fp8' if fp8 else 'bf16'}_m{keep_pages}_{pooling}",
                 head_dim=head_dim, fp8=fp8, keep_pages=keep_pages, pooling=pooling, seq_len=4096)
@@ -651,8 +650,8 @@ _DECODE_FLAT = replace(W.SMALL_DECODE, name="small_decode_b8_flat", keep_pages=0
                                       (_DECODE_FLAT, False)],
                          ids=["mean", "minmax", "d64_fp8", "d64_bf16_minmax", "signed_w", "bf16", "flat"])
 def test_index_decode_parity(w, signed):
-    """Paged decode indexer against the oracle on every sequence. The d_I = 64 cases run the paged
-    coarse instances coarse_kernel<64, 1, true, false / true> and fine_kernel<64, fp8 / bf16>;
+    """Paged decode indexer against the oracle on every sequence. The d_I = 64 cases run
+    coarse_paged_kernel<64, mean / min-max> and fine_kernel<64, fp8 / bf16>;
     bf16 runs fine_kernel<128, bf16>; flat (keep_pages = 0) runs the fine kernel over every eligible
     page, looked up in the page table, and the selection over all of them; signed_w draws head
     weights of either sign (two of the eight sequences with all weights <= 0)."""
