@@ -1751,7 +1751,7 @@ __device__ int global_compact(const uint32_t* keys, int n, uint32_t T, int take_
 // range of its keys, which shrinks by a factor of kMaskBins each time, until they fit or are all equal; then
 // T and take_eq are set as radix_threshold's and false is returned (the caller compacts by them).
 // Bandwidth of the L2 and the LDS bounds it: a row of 131072 candidates (512 rows: 498 us before, 150 now; 64 rows 262 and 60).
-constexpr int kMaskBins = 2048, kMaskCand = 1024;
+constexpr int kMaskBins = 2048, kMaskCand = 1024;  // (a thread per gathered key, and bins for their ranks)
 constexpr int64_t kMaskKeys = 262144;
 struct MaskLds {
   uint32_t *mask, *hist, *ckey;
@@ -1762,6 +1762,7 @@ __host__ __device__ constexpr int64_t mask_words(int64_t n) { return (n + 31) / 
 
 template <int NT>
 __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s, int* wsum, uint32_t& T, int& take_eq) {
+  static_assert(kMaskCand <= NT && kMaskCand <= kMaskBins, "");
   __shared__ uint32_t range[2], wlo[NT / 64], whi[NT / 64];
   __shared__ int found[3], n_cand;  // boundary bin, keys in the bins above it; gathered keys
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1892,13 +1893,25 @@ __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s
     __syncthreads();
     const int nc = n_cand;
     if (nc <= kMaskCand) {
-      for (int x = threadIdx.x; x < nc; x += NT) {
-        const uint32_t key = s.ckey[x];
-        const int pos = s.cpos[x];
-        int rank = 0;
-        for (int y = 0; y < nc; ++y) rank += s.ckey[y] > key || (s.ckey[y] == key && s.cpos[y] < pos);
-        if (rank < rem) atomicOr(&s.mask[pos >> 5], 1u << (pos & 31));
+      // candidate x is ranked by every `step`-th thread from x on, each against its share of the others (indexers of few
+      // heads give 100 to 500 candidates: a thread per candidate: 35 rows of 4K to 7K keys 26.6 us, now 17.6)
+      int step = 64;
+      while (step < nc) step *= 2;  // (at most kMaskCand <= NT)
+      const int x = threadIdx.x & (step - 1), parts = NT / step;
+      const uint32_t key = s.ckey[x];
+      const int pos = s.cpos[x];
+      if (threadIdx.x < step) s.hist[threadIdx.x] = 0u;
+      __syncthreads();
+      const int per = (nc + parts - 1) / parts, y0 = (int)(threadIdx.x / step) * per, y1 = y0 + per < nc ? y0 + per : nc;
+      int rank = 0;
+#pragma unroll 4
+      for (int y = y0; y < y1; ++y) {
+        const uint32_t k2 = s.ckey[y];
+        rank += k2 > key || (k2 == key && s.cpos[y] < pos);
       }
+      if (x < nc) atomicAdd(&s.hist[x], (uint32_t)rank);
+      __syncthreads();
+      if (threadIdx.x < nc && s.hist[x] < (uint32_t)rem) atomicOr(&s.mask[pos >> 5], 1u << (pos & 31));
       __syncthreads();
       return true;
     }
@@ -1982,11 +1995,13 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
     bool masked = false;
     uint32_t* const area = reinterpret_cast<uint32_t*>(rstart);  // 16-byte aligned offsets are not needed
     const int nw = (slots_cap + 31) / 32;
-    if (GK && slots_cap <= kMaskKeys) {
-      const MaskLds ml = {area, area + nw, area + nw + kMaskBins, reinterpret_cast<int*>(area + nw + kMaskBins + kMaskCand)};
-      masked = mask_select<NT>(keys, n, g.k_sparse, ml, wsum, T, take);
-    } else if (GK) {
-      global_threshold<NT>(keys, n, g.k_sparse, h11, gsub, gcnt, hist, wsum, T, take);
+    if constexpr (GK) {
+      if (slots_cap <= kMaskKeys) {
+        const MaskLds ml = {area, area + nw, area + nw + kMaskBins, reinterpret_cast<int*>(area + nw + kMaskBins + kMaskCand)};
+        masked = mask_select<NT>(keys, n, g.k_sparse, ml, wsum, T, take);
+      } else {
+        global_threshold<NT>(keys, n, g.k_sparse, h11, gsub, gcnt, hist, wsum, T, take);
+      }
     } else {
       const int n_valid = block_count_nonzero(keys, n, wsum);
       if (n_valid > g.k_sparse) radix_threshold<NT>(keys, n, g.k_sparse, hist, T, take);

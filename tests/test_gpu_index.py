@@ -458,13 +458,15 @@ def test_selection_clustered_scores(mode):
     print(mode, stats)
 
 
-@pytest.mark.parametrize("mode", ["all_equal", "two_values_outliers", "dense_cluster_outliers", "few_non_zero", "last_bin"])
+@pytest.mark.parametrize("mode", ["all_equal", "two_values_outliers", "dense_cluster_outliers", "few_non_zero", "last_bin",
+                                  "distinct_cluster"])
 def test_mask_selection_clustered_scores(mode):
     """Designed scores (component 0 of the keys, as in the test above) for the bit-mask selection of rows
     that are read from global memory (flat, 45056 tokens): all equal (every key in one bin, ties by
     position), two values or 128 values of many ties beside outliers (the bin overflows, narrowed passes),
-    zero for all but 40 tokens, and more outliers above the sampled range than are selected. Rows at the end
-    of the cache and rows with few or fewer candidates than K_sparse, against the oracle."""
+    zero for all but 40 tokens, more outliers above the sampled range than are selected, and 32768 different values
+    beside outliers (10 to 300 gathered keys, ranked by several threads each). Rows at the end of the cache,
+    inside it, and rows with few or fewer candidates than K_sparse, against the oracle."""
     w = replace(W.L2K_MQA, name=f"mask_{mode}", keep_pages=0, seq_len=45056, k_sparse=1500)
     n, H, d = w.seq_len, w.n_heads, w.head_dim
     q = np.zeros((n, H, d), np.float32)
@@ -482,11 +484,17 @@ def test_mask_selection_clustered_scores(mode):
         kb[s % 61 == 5, 0] = 0x4700
     elif mode == "few_non_zero":
         kb[g.choice(n, 40, replace=False), 0] = 0x3F80
+    elif mode == "distinct_cluster":    # 1 + a / 128 + b / 4096, in seeded random order
+        v = g.permutation(n)
+        q[:, :, 1] = 1.0
+        kb[:, 0] = 0x3F80 + (v % 128)
+        kb[:, 1] = synth.to_bf16_bits(((v // 128) % 256 / 4096).astype(np.float32))
+        kb[s % 61 == 5, 0] = 0x4700
     else:
         kb[:, 0] = 0x3F80
         kb[g.choice(n, 1600, replace=False), 0] = 0x4000 + g.integers(0, 200, 1600)
     inp = dict(q=synth.to_bf16_bits(q), w=np.ones((n, H), np.float32), k=kb, k_scale=None)
-    for q0, nq in ((n - 12, 12), (150, 8), (1700, 8)):
+    for q0, nq in ((n - 12, 12), (150, 8), (1700, 8), (3000, 4), (9000, 4), (20000, 4)):
         out, _ = _run_prefill(w, inp, q_start=q0, n_q=nq, pages=False)
         rows = list(range(q0, q0 + nq))
         res = _oracle_rows(w, inp, rows)
