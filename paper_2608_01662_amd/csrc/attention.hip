@@ -15,9 +15,6 @@
 #include "device.hpp"
 #include "launch.hpp"
 
-// (The list staging unrolls loops with uniform early exits, which the unroller then reports.)
-#pragma clang diagnostic ignored "-Wpass-failed"
-
 namespace lsa {
 
 constexpr float kLn2 = 0.69314718055994530942f;
@@ -211,6 +208,9 @@ __device__ __forceinline__ int64_t block_prefix512(int64_t v, int64_t* wtot, int
 // row costs the same gathered or contiguous and one pass over them needs no partials and no merge (2048
 // rows at 32K: 680 us, against 846 for a listed and a query-tiled window kernel on two streams and
 // their merge; 37 rows at 60K: 48 against 66 us).
+// (The list staging unrolls loops with uniform early exits, which the unroller then reports.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wpass-failed"
 template <bool SPLIT, bool WINDOWED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void mla_attn_kernel(AttnGeom a) {
@@ -688,6 +688,7 @@ void mla_attn_kernel(AttnGeom a) {
     }
   }
 }
+#pragma clang diagnostic pop
 
 // ============================================================================ MQA 16 x 128
 // W waves per query row, wave w taking 32-entry tiles w, w + W, .. of its list; their maxima, sums and

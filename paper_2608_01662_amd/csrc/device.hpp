@@ -13,10 +13,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-#define LSA_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-
-constexpr int kWave = 64;
-
 // ---------------------------------------------------------------- matrix cores
 // v_mfma_f32_32x32x16_bf16. Operand layouts (checked on gfx950):
 //   A[i][k]: lane l holds i = l%32, k = 8*(l/32) + 0..7
@@ -48,24 +44,6 @@ __device__ __forceinline__ i32x8 join_fp8x32(u32x4 lo, u32x4 hi) {
 }
 
 // ---------------------------------------------------------------- number formats
-// Four OCP e4m3fn codes (one dword) -> four bf16, exactly: the hardware converter yields fp32
-// values with at most 4 significant bits, so keeping their upper halves loses nothing.
-__device__ __forceinline__ u32x2 fp8x4_to_bf16x4(uint32_t v) {
-  f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(v, false);
-  f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(v, true);
-  u32x2 r;
-  r.x = __builtin_amdgcn_perm(__float_as_uint(lo.y), __float_as_uint(lo.x), 0x07060302u);
-  r.y = __builtin_amdgcn_perm(__float_as_uint(hi.y), __float_as_uint(hi.x), 0x07060302u);
-  return r;
-}
-// 8 e4m3fn codes (two dwords) -> one bf16x8 MFMA operand.
-__device__ __forceinline__ u32x4 fp8x8_to_bf16x8(uint32_t a, uint32_t b) {
-  u32x2 x = fp8x4_to_bf16x4(a), y = fp8x4_to_bf16x4(b);
-  return u32x4{x.x, x.y, y.x, y.y};
-}
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
-
 // Two fp32 -> two bf16 (round to nearest even) packed in one dword: v_cvt_pk_bf16_f32.
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -93,14 +71,6 @@ __device__ __forceinline__ void vm_wait() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// Workgroup barrier that the compiler cannot move memory accesses across (no wait implied).
-__device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "memory"); }
-// All LDS reads of this wave have returned; then barrier (used before a buffer is refilled).
-__device__ __forceinline__ void lds_done_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-// Full workgroup barrier with LDS visibility (ordinary ds_write -> ds_read hand-off).
-__device__ __forceinline__ void block_sync() { __syncthreads(); }
 
 // LDS accesses of one wave before and after this point keep their order. The hardware runs a wave's LDS
 // instructions in order, so no instruction is needed; but the compiler reasons about one lane, for which a store and a

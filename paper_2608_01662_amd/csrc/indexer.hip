@@ -25,15 +25,6 @@
 
 namespace lsa {
 
-// 8 e4m3fn codes (two dwords) -> one bf16x8 MFMA operand with gfx950's packed converter: two
-// codes per instruction (scale 1.0, so the exact values come out as bf16).
-__device__ __forceinline__ u32x4 fp8x8_to_bf16x8_pk(uint32_t a, uint32_t b) {
-  return u32x4{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 1.0f, false)),
-               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 1.0f, true)),
-               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 1.0f, false)),
-               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 1.0f, true))};
-}
-
 // ============================================================================ row geometry
 struct RowInfo {
   int64_t t;       // query position
@@ -259,25 +250,6 @@ __device__ __forceinline__ void load_head_weights(const float* __restrict__ w, i
   for (int r = 0; r < 16; ++r) {
     const int head = 8 * (r / 4) + 4 * h + (r % 4);
     wr[r] = head < H ? w[row * H + head] : 0.f;
-  }
-}
-
-// B operand for one key row: lane half h reads dims [(D/2)*h, (D/2)*h + D/2) of key `krow`.
-template <int D, bool FP8>
-__device__ __forceinline__ void load_key_operand(const void* __restrict__ k, int64_t krow, int lane, u32x4 (&b)[D / 16]) {
-  const int h = lane >> 5;
-  if (FP8) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(k) + krow * D + (D / 2) * h);
-#pragma unroll
-    for (int v = 0; v < D / 32; ++v) {
-      const u32x4 raw = p[v];  // 16 codes = k-steps 2v, 2v+1
-      b[2 * v] = fp8x8_to_bf16x8(raw.x, raw.y);
-      b[2 * v + 1] = fp8x8_to_bf16x8(raw.z, raw.w);
-    }
-  } else {
-    const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(k) + krow * D + (D / 2) * h);
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) b[s] = p[s];
   }
 }
 
@@ -2479,8 +2451,8 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Lets the two select kernels use up to 156 KB of dynamic LDS (gfx950 has 160 KB per
-// workgroup); done once per device.
+// Lets every instance of the selection kernels use the dynamic LDS it may need (up to 156 of the 160 KB that a gfx950
+// workgroup has, less its static LDS); done once per device.
 hipError_t prepare_index_kernels() {
   static std::atomic<bool> done[64] = {};  // per device; repeated setup by racing threads is harmless
   int dev = 0;
