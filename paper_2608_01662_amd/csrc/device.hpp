@@ -56,6 +56,9 @@ __device__ __forceinline__ uint32_t score_key(float f) {
   uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+__device__ __forceinline__ float key_score(uint32_t key) {  // its inverse
+  return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
+}
 
 // ---------------------------------------------------------------- waits and barriers
 // Wait until at most N vector-memory operations of this wave are outstanding (direct-to-LDS

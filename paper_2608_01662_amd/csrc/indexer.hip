@@ -1714,15 +1714,20 @@ __device__ int global_compact(const uint32_t* keys, int n, uint32_t T, int take_
 
 // Selection of the k largest of the n keys of a row in global memory as a bit mask in LDS (rows of up to
 // kMaskKeys), in two passes over the keys where the threshold, gather and ordered compaction above take
-// four. (1) A histogram of the non-zero keys over kMaskBins bins: bin 0 below and the last one above the
-// range [lo, hi] of 4 NT sampled keys, the others splitting it evenly, so that the counts spread over the
-// bins (by their leading 11 bits the scores of a row fall into few bins, and their LDS atomics
-// serialize). (2) Keys in bins above the one that holds the k-th largest set their bit, the keys of that bin
-// are gathered with their positions, ranked against each other by (key descending, position ascending),
-// and the first ones set their bits. More than kMaskCand in the bin: both passes again over the exact
-// range of its keys, which shrinks by a factor of kMaskBins each time, until they fit or are all equal; then
-// T and take_eq are set as radix_threshold's and false is returned (the caller compacts by them).
-// Bandwidth of the L2 and the LDS bounds it: a row of 131072 candidates (512 rows: 498 us before, 150 now; 64 rows 262 and 60).
+// four. (1) A histogram of the non-zero keys over kMaskBins bins that split a sampled range [lo, hi] evenly by score (keys
+// outside it count in the first and the last bin). (2) Keys in bins above the one that holds the k-th largest
+// set their bit, the keys of that bin are gathered with their positions, ranked against each other by (key
+// descending, position ascending), and the first ones set their bits. More than kMaskCand in the bin: both passes
+// again over the exact range of its keys, split evenly by their bits, which shrinks by a factor of kMaskBins each
+// time, until they fit or are all equal; then T and take_eq are set as radix_threshold's and false is returned (the
+// caller compacts by them).
+// The range comes from 4 keys per thread, those of each wave spread over the row: the median of the waves' smallest
+// keys and the third of their largest, so that a few outliers do not stretch it, or the largest where fewer than one key in
+// 512 is selected and the third may lie below them. Split by the keys' bits, scores of both signs fall into few
+// bins, as most of their range of bits lies around zero: the boundary bin overflows, and the LDS atomics serialize.
+// Bandwidth of the L2 and the LDS bounds it. Decode index calls, us (threshold selection / mask with bins by bits /
+// by score), weights of either sign: 64 sequences of 40000 candidates 94 / 145 / 80, one of 40960 63 / 97 / 52, 3 of 65536 77 / 104 / 61,
+// 8 of 256000 (K_sparse 2048) 174 / 177 / 136; positive weights: 96 / 124 / 79, 62 / 78 / 50, 80 / 58 / 56, 182 / 126 / 131.
 constexpr int kMaskBins = 2048, kMaskCand = 1024;  // (a thread per gathered key, and bins for their ranks)
 constexpr int64_t kMaskKeys = 262144;
 struct MaskLds {
@@ -1743,7 +1748,8 @@ __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s
   for (int i = threadIdx.x; i < (n + 31) / 32; i += NT) s.mask[i] = 0u;
   uint32_t lo = ~0u, hi = 0u;
   {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(keys + (int)((int64_t)threadIdx.x * n / NT & ~3));
+    constexpr int NW = NT / 64;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(keys + (int)((int64_t)(lane * NW + wv) * n / NT & ~3));
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (v[c] != 0u) lo = lowest(lo, v[c]);
@@ -1756,12 +1762,19 @@ __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s
       whi[wv] = hi;
     }
     __syncthreads();
+    auto ranked = [&](const uint32_t* a, int at) {  // a's NW values in order: the one at `at`
+      const uint32_t mine = a[lane & (NW - 1)];
+      int rank = 0;
 #pragma unroll
-    for (int x = 0; x < NT / 64; ++x) {
-      lo = lowest(lo, wlo[x]);
-      hi = highest(hi, whi[x]);
-    }
-    if (hi == 0u) lo = hi = 1u;  // (no candidate among the samples)
+      for (int x = 0; x < NW; ++x) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, x);
+        rank += o < mine || (o == mine && x < lane);
+      }
+      return (uint32_t)__builtin_amdgcn_readlane((int)mine, __ffsll(__ballot(lane < NW && rank == at)) - 1);
+    };
+    lo = ranked(wlo, NW / 2);
+    hi = ranked(whi, (int64_t)k * 512 < n ? NW - 1 : NW - 3);
+    if (lo > hi) lo = hi = 1u;  // (hardly a candidate among the samples)
   }
   int rem = k;
   for (bool first = true;; first = false) {
@@ -1773,22 +1786,42 @@ __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s
     }
     __syncthreads();
     const uint32_t span = hi - lo;
-    constexpr uint32_t kInner = kMaskBins - 2;
-    const bool direct = span < kInner;  // one value per bin
-    const uint32_t scale = direct ? 0u : (uint32_t)floor(4294967296.0 * kInner / ((double)span + 1.0)) - 1u;
-    // bin of a key in play: every non-zero key at first, then those of the previous boundary bin
+    const bool direct = span < kMaskBins;  // one value per bin
+    const uint32_t scale = direct ? 0u : (uint32_t)floor(4294967296.0 * kMaskBins / ((double)span + 1.0)) - 1u;
+    const float vlo = key_score(lo), vspan = key_score(hi) - vlo;
+    const bool by_value = first && !direct && vspan > 1e-30f && vspan < 1e30f;  // (no infinity or NaN at either end)
+    const float vscale = by_value ? (float)kMaskBins / vspan : 0.f, voff = -vlo * vscale;
+    // keys in play: every non-zero one at first, then those of the previous boundary bin. Their bins never decrease with
+    // the key, whatever the rounding; those below lo and above hi go to the first and the last one.
     auto in_play = [&](uint32_t key) { return first ? key != 0u : key - lo <= span; };
-    auto bin_of = [&](uint32_t key) {
-      const uint32_t d = key - lo;
-      const uint32_t b = 1u + (direct ? d : __umulhi(d, scale));
-      return key < lo ? 0u : key > hi ? (uint32_t)kMaskBins - 1u : b;
+    auto bins_of = [&](const u32x4& v) {
+      u32x4 b;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) b[c] = lowest(highest(v[c], lo), hi);
+      if (by_value) {  // (uniform)
+        if (lo >= 0x80000000u) {  // (no negative score)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) b[c] ^= 0x80000000u;
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) b[c] = __float_as_uint(key_score(b[c]));
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          b[c] = lowest((uint32_t)fmaxf(fmaf(__uint_as_float(b[c]), vscale, voff), 0.f), kMaskBins - 1u);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) b[c] = direct ? b[c] - lo : __umulhi(b[c] - lo, scale);
+      }
+      return b;
     };
     int nz = 0;
     stream_row<NT>(keys, n, [&](int, const u32x4& v, bool ok) {
+      const u32x4 b = bins_of(v);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (ok && in_play(v[c])) {
-          atomicAdd(&s.hist[bin_of(v[c])], 1u);
+          atomicAdd(&s.hist[b[c]], 1u);
           ++nz;
         }
     });
@@ -1838,13 +1871,13 @@ __device__ bool mask_select(const uint32_t* keys, int n, int k, const MaskLds& s
     rem -= found[1];
     uint32_t mn = ~0u, mx = 0u;
     stream_row<NT>(keys, n, [&](int i, const u32x4& v, bool ok) {
+      const u32x4 b = bins_of(v);
       uint32_t nib = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (ok && in_play(v[c])) {
-          const uint32_t b = bin_of(v[c]);
-          nib |= (b > bstar ? 1u : 0u) << c;
-          if (b == bstar) {
+          nib |= (b[c] > bstar ? 1u : 0u) << c;
+          if (b[c] == bstar) {
             const int at = atomicAdd(&n_cand, 1);
             if (at < kMaskCand) {
               s.ckey[at] = v[c];

@@ -459,19 +459,22 @@ def test_selection_clustered_scores(mode):
 
 
 @pytest.mark.parametrize("mode", ["all_equal", "two_values_outliers", "dense_cluster_outliers", "few_non_zero", "last_bin",
-                                  "distinct_cluster"])
+                                  "distinct_cluster", "signed", "negative", "infinities", "tiny"])
 def test_mask_selection_clustered_scores(mode):
     """Designed scores (component 0 of the keys, as in the test above) for the bit-mask selection of rows
     that are read from global memory (flat, 45056 tokens): all equal (every key in one bin, ties by
     position), two values or 128 values of many ties beside outliers (the bin overflows, narrowed passes),
-    zero for all but 40 tokens, more outliers above the sampled range than are selected, and 32768 different values
-    beside outliers (10 to 300 gathered keys, ranked by several threads each). Rows at the end of the cache,
+    zero for all but 40 tokens, more outliers above the sampled range than are selected, 32768 different values
+    beside outliers (10 to 300 gathered keys, ranked by several threads each), the same values on both sides of zero
+    (heads of either weight) or below it, with infinities of both signs among them, or so small that the bins
+    follow the keys' bits instead of the scores. Rows at the end of the cache,
     inside it, and rows with few or fewer candidates than K_sparse, against the oracle."""
     w = replace(W.L2K_MQA, name=f"mask_{mode}", keep_pages=0, seq_len=45056, k_sparse=1500)
     n, H, d = w.seq_len, w.n_heads, w.head_dim
     q = np.zeros((n, H, d), np.float32)
     q[:, :, 0] = 1.0
     kb = np.zeros((n, d), np.uint16)
+    wt = np.ones((n, H), np.float32)
     s = np.arange(n)
     g = np.random.default_rng(23)
     if mode == "all_equal":
@@ -490,10 +493,24 @@ def test_mask_selection_clustered_scores(mode):
         kb[:, 0] = 0x3F80 + (v % 128)
         kb[:, 1] = synth.to_bf16_bits(((v // 128) % 256 / 4096).astype(np.float32))
         kb[s % 61 == 5, 0] = 0x4700
+    elif mode in ("signed", "negative", "infinities"):    # a / 128 + b / 16384, a in -128 .. 127, as sum of w ReLU(q k) = H / 2 (x+ - x-)
+        v = g.permutation(n)
+        q[:, :, 1] = 1.0
+        q[:, H // 2:, :2] = -1.0
+        wt[:, H // 2:] = -1.0
+        if mode == "negative":
+            wt[:, :H // 2] = 0.0
+        kb[:, 0] = synth.to_bf16_bits(((v % 256 - 128) / 128).astype(np.float32))
+        kb[:, 1] = synth.to_bf16_bits((v // 256 / 16384).astype(np.float32))
+        if mode == "infinities":
+            kb[g.choice(n, 300, replace=False), 0] = 0x7F80
+            kb[g.choice(n, 300, replace=False), 0] = 0xFF80
+    elif mode == "tiny":
+        kb[:, 0] = 0x0880 + g.integers(0, 128, n)
     else:
         kb[:, 0] = 0x3F80
         kb[g.choice(n, 1600, replace=False), 0] = 0x4000 + g.integers(0, 200, 1600)
-    inp = dict(q=synth.to_bf16_bits(q), w=np.ones((n, H), np.float32), k=kb, k_scale=None)
+    inp = dict(q=synth.to_bf16_bits(q), w=wt, k=kb, k_scale=None)
     for q0, nq in ((n - 12, 12), (150, 8), (1700, 8), (3000, 4), (9000, 4), (20000, 4)):
         out, _ = _run_prefill(w, inp, q_start=q0, n_q=nq, pages=False)
         rows = list(range(q0, q0 + nq))
