@@ -1962,9 +1962,11 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
   __shared__ uint32_t hist[256];
   __shared__ int wsum[2 * NT / 64 + 2];
   const int k_cap = g.k_sink + g.k_swa + g.k_sparse;
-  // LDS: keys [max(slots_cap, k_cap)] (not with GK), lidx [k_cap], lpages [M], and with GK the
-  // run-start scratch [k_cap] (otherwise the keys area serves for it), which rows of up to kMaskKeys share
-  // with the mask selection's areas, or the 11-bit histogram, the gathered boundary-bin keys and their counter
+  // LDS areas, in order:
+  //   without GK: the keys, later the run starts [max(slots_cap, k_cap)], lidx [k_cap], lpages [M]
+  //   with GK: lidx [k_cap], lpages [M], run starts [k_cap], and for the threshold selection the 11-bit histogram, the
+  //   gathered keys of its boundary bin and their counter; the mask selection is done with its areas
+  //   (mask_words) before the run starts are written and takes their place
   const int key_words = GK ? 0 : (slots_cap > k_cap ? slots_cap : k_cap);
   int32_t* lidx = reinterpret_cast<int32_t*>(smem + key_words);
   int32_t* lpages = lidx + k_cap;
@@ -1998,7 +2000,7 @@ __global__ __launch_bounds__(NT) void token_select_kernel(IndexGeom g, int64_t n
     uint32_t T = 0;
     int take = 0;
     bool masked = false;
-    uint32_t* const area = reinterpret_cast<uint32_t*>(rstart);  // 16-byte aligned offsets are not needed
+    uint32_t* const area = reinterpret_cast<uint32_t*>(rstart);
     const int nw = (slots_cap + 31) / 32;
     if constexpr (GK) {
       if (slots_cap <= kMaskKeys) {

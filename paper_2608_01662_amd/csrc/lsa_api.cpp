@@ -218,11 +218,12 @@ struct AttnPlan {
 // Workgroups the GPU runs at once: one per CU (the MLA kernel's LDS admits one per CU).
 constexpr int64_t kCus = 256;
 
-// Lists of at most this many tiles stay in one piece, whatever the plan: in calls of few rows while the tiles
-// (1.6 us each) cost less than writing and merging partials, beside whole rows up to half the capacity, as rows over the
-// rounds at the start of a prompt are short and find a free CU early. (us before any cutting by rounds / cut by the
-// capacity / by the list itself, lists of rows 0 .. of a prompt in a cache of 32768: 24 rows 21.0 / 27.7 / 17.1, 100 22.8 /
-// 26.0 / 18.3, 257 22.9 / 32.4 / 25.0, 333 36.1 / 45.0 / 36.6, 513 46.9 / 62.8 / 50.3: what is left is an empty merge.)
+// A list of at most this many tiles stays in one piece, whatever the plan: in a call of few rows its tiles (1.6 us
+// each) cost less than writing and merging partials. Beside whole rows the limit is half the capacity: such rows
+// are a prompt's first and shortest, and find a free CU early. us for lists of rows 0 .. of a prompt in a cache of
+// 32768 (every row whole, or one piece per CU / cut by the capacity / cut by the list itself with this limit): 24 rows 21.0 /
+// 27.7 / 17.1, 100 22.8 / 26.0 / 18.3, 257 22.9 / 32.4 / 25.0, 333 36.1 / 45.0 / 36.6, 513 46.9 / 62.8 / 50.3. What is
+// left above whole rows is the launch of a merge with nothing to do.
 constexpr int kShortTiles = 4;
 
 // The last n_whole rows whole, the others in `ns` pieces each, of 32-entry multiples (fewer where the list has fewer tiles).
@@ -255,16 +256,20 @@ AttnPlan plan_least(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
   return plan_pieces(p, n_rows, k_cap, 0, few ? cdiv(kCus, n_rows) : 1, false);
 }
 
-// The plan used when the workspace has room for it. Rounds of kCus whole rows, and the n_rows mod kCus
-// rows that are left cut into the number of pieces that finishes first by this count, in us: rounds * (tile *
-// tiles per piece + 9), a 32-entry tile taking about 1 beside whole rows and 1.6 in a call of few rows (their
-// lists and cache rows come from memory: one row in 73 pieces of one tile 13.6, in 37 of two 15.8, 64 rows in
-// pieces of 19 tiles 41), the 9 for a piece's fixed cost (73 KB of Q, list staging, pipeline fill, 64 KB of output), plus 5 for the merge and 0.03 (fp32:
-// 0.06) per piece for the partials it reads. Measured at 73 to 81 tiles, whole rows (and below 256 rows one piece
-// per CU whatever the rounds) before, this plan now: 4 rows 41.5 and 22.2 us, 13 rows 38.5 and 25.2, 24 rows 43.9 and 38.6 (264
-// pieces in two rounds, 240 in one), 100 rows 72 and 62, 170 rows 110 and 92.5, 257 rows 149 and 113, 333
-// rows 150 and 136, 513 rows 224 and 195. Cut only where the count promises 5%: 400 rows took 165 us in
-// pieces and 161 whole. The error against 64 bits stays or falls (100 rows 2.50e-3 to 2.06e-3).
+// The plan used when the workspace has room for it: rounds of kCus whole rows, and the n_rows mod kCus rows
+// over them (all rows of a call of few) in the number of pieces that finishes first by this count, in us:
+//   rounds of pieces * (9 + tiles per piece * 1, in a call of few rows * 1.6) + 5 + pieces * 0.06, in a call of few rows * 0.03
+// 9 is a piece's fixed cost (73 KB of Q, list staging, pipeline fill, 64 KB of output). A 32-entry tile takes
+// about 1 beside whole rows; in a call of few rows its list entries and cache rows come from memory (one row in 73
+// pieces of one tile 13.6, in 37 of two 15.8; 64 rows in pieces of 19 tiles 41). 5 is the merge, and the last term the
+// partials that it reads. Rows are cut only where the count promises 5%, and in calls of few rows into one round
+// at most (400 rows: 165 us in pieces, 161 whole; 140 rows: 84 in two pieces, 82 whole).
+// Partials are bf16 in calls of few rows with as many pieces as plan_least has, where the rounding of every piece
+// averages out, and otherwise fp32, so that the error against 64 bits stays or falls (100 rows 2.50e-3 to
+// 2.06e-3); fp32 costs the merge twice the traffic (64 rows 46 us with bf16, 51 with fp32).
+// Lists of 2308, us (every row whole, below kCus rows one piece per CU / this plan): 1 row 61.6 / 18.0, 3 77 / 25, 13 39.7 / 25.3, 24
+// 44.4 / 35.8, 64 37.2 / 37.4, 100 65 / 54, 170 88 / 74.6, 255 109 / 89; 257 137 / 98, 300 138 / 119, 340 144 / 134, 420 159 / 157,
+// 540 214 / 198, 800 292 / 272, 1030 366 / 334. Lists of 600 and 30 rows pay for the fp32 partials: 21.9 / 24.2.
 constexpr int64_t kMaxPieces = 512;  // bounds the partials (33 MB, 67 in fp32)
 AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
   const int64_t rem = n_rows % kCus, tiles = cdiv(k_cap, 32);
@@ -281,8 +286,6 @@ AttnPlan plan_attn(const lsa_attn_params* p, int64_t n_rows, int32_t k_cap) {
       }
     }
   }
-  // Partials in bf16 (half the merge's traffic: 46 against 51 us at 64 rows) round every piece once more,
-  // which averages out over a row's pieces: rows in fewer pieces than plan_least's keep fp32 ones.
   const AttnPlan pl = plan_pieces(p, n_rows, k_cap, n_rows - rem, best, false);
   const bool f32 = pl.n_whole > 0 || pl.n_split < plan_least(p, n_rows, k_cap).n_split;
   return f32 ? plan_pieces(p, n_rows, k_cap, n_rows - rem, best, true) : pl;
