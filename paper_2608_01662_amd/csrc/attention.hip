@@ -202,6 +202,8 @@ __device__ __forceinline__ int64_t block_prefix512(int64_t v, int64_t* wtot, int
   return base + inc - v;
 }
 
+constexpr uint32_t kSpreadPieces = 120;  // 128 KB of fp32 partials each
+
 // WINDOWED lists (a.k_swa >= 0, the split attention of Sec. 4.1.1): a row's list is the entries before
 // its window, idx[0 .. count - w), and then the window [t - w + 1, t], w = min(k_swa, t + 1), taken as
 // contiguous positions instead of read from the list; both go through the same tiles, since a 1152-byte
@@ -643,18 +645,30 @@ void mla_attn_kernel(AttnGeom a) {
     }
   }
   if (SPLIT && !whole && a.part_f32) {  // fp32 partials straight from the accumulators
+    // A store writes 32 bytes of 32 heads' rows, 2 KB apart. Calls of few pieces write other lines with the next store, which
+    // spreads them over the channels; with more pieces the lines are filled one after the other, or they leave
+    // the L2 in parts. us at 2308 entries, spread / filled: 2 rows (74 pieces) 20.7 / 21.6, 3 (111) 22.5 / 24.4, 5 (125) 25.9 /
+    // 24.9, 7 (175) 29.0 / 26.8, 20 (260) 38.6 / 33.7; 300 rows (132 pieces beside whole rows) 133 / 127.
+    float inv[2], *dst[2];
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb) {
-      const float inv = lt[hb] > 0.f ? 1.f / lt[hb] : 0.f;
-      float* dst = a.part_f32 + (p0 + 32 * hb + oj) * 512 + 128 * w4 + 4 * (lane >> 5);
+      inv[hb] = lt[hb] > 0.f ? 1.f / lt[hb] : 0.f;
+      dst[hb] = a.part_f32 + (p0 + 32 * hb + oj) * 512 + 128 * w4 + 4 * (lane >> 5);
+    }
+    auto store = [&](int hb, int c, int q) {
+      const f32x16& ob = o[4 * hb + c];
+      *reinterpret_cast<f32x4*>(dst[hb] + 32 * c + 8 * q) =
+          f32x4{ob[4 * q] * inv[hb], ob[4 * q + 1] * inv[hb], ob[4 * q + 2] * inv[hb], ob[4 * q + 3] * inv[hb]};
+    };
+    // (the products of the two orders are kept apart: computed before the branch they spill)
+    if (a.n_whole == 0 && gridDim.x <= kSpreadPieces) {
+      asm volatile("" : "+v"(inv[0]), "+v"(inv[1]));
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+      for (int u = 0; u < 32; ++u) store((u >> 2) & 1, u & 3, u >> 3);
+    } else {
+      asm volatile("" : "+v"(inv[0]), "+v"(inv[1]));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& ob = o[4 * hb + c];
-          *reinterpret_cast<f32x4*>(dst + 32 * c + 8 * q) =
-              f32x4{ob[4 * q] * inv, ob[4 * q + 1] * inv, ob[4 * q + 2] * inv, ob[4 * q + 3] * inv};
-        }
+      for (int u = 0; u < 32; ++u) store(u >> 4, (u >> 2) & 3, u & 3);
     }
     return;
   }

@@ -219,12 +219,13 @@ def test_long_lists_beyond_one_staging_pass():
 
 @pytest.mark.parametrize("n_rows,k_cap,pieces,f32", [
     (1, 2308, 73, False), (1, 57344, 256, False), (1, 8192, 128, True), (2, 96, 1, False), (2, 160, 5, False), (2, 256, 8, False),
-    (2, 288, 9, False), (2, 320, 10, False), (3, 2600, 41, True), (25, 2308, 10, True), (28, 2308, 9, True), (29, 2308, 8, True),
+    (2, 288, 9, False), (2, 320, 10, False), (3, 2308, 37, True), (3, 2600, 41, True), (25, 2308, 10, True), (28, 2308, 9, True), (29, 2308, 8, True),
     (32, 2308, 8, False)], ids=lambda v: str(v))
 def test_split_merge_counts(n_rows, k_cap, pieces, f32):
     """The merge of lists cut into pieces at its edges: one row of 73 pieces and of the largest count (256, seven
     tiles each), a list kept whole, few pieces of one tile, 41, and the counts on both sides of the switch
-    between its two kernels (10, 9 and 8 pieces), with bf16 and fp32 partials, with one row of one piece, one of more
+    between its two kernels (10, 9 and 8 pieces), with bf16 and fp32 partials (fp32 ones stored in either order: 111 and 123
+    pieces in all), with one row of one piece, one of more
     pieces without entries than with, and one empty row, against the oracle."""
     from dataclasses import replace
     assert P.attn_pieces(n_rows, k_cap) == (n_rows if pieces > 1 else 0, pieces, f32)
