@@ -239,6 +239,9 @@ size_t lsa_sparse_attn_workspace_size(const lsa_attn_params* p, int64_t n_rows, 
  *   out        [n_rows, n_heads, d_v] bf16; lse [n_rows, n_heads] fp32 or NULL
  *   workspace  >= lsa_sparse_attn_workspace_size(p, n_rows, k_cap, page_table != NULL)
  * Cross-layer indexing: call once per layer with that layer's q and kv and the same idx/count.
+ * The same call gives the same bits. How many waves or pieces share a row, and so the order in which its partial
+ * sums are merged, follows n_rows, the workspace, and the cache's (or page table's) positions where they are fewer
+ * than k_cap: the same rows in other calls agree within rounding.
  */
 lsa_status lsa_sparse_attn(const lsa_attn_params* p, int64_t n_rows, const void* q, const void* kv,
                            const void* v, int64_t n_kv_rows, const int32_t* idx,
