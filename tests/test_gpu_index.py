@@ -459,15 +459,15 @@ def test_selection_clustered_scores(mode):
 
 
 @pytest.mark.parametrize("mode", ["all_equal", "two_values_outliers", "dense_cluster_outliers", "few_non_zero", "last_bin",
-                                  "distinct_cluster", "signed", "negative", "infinities", "tiny"])
+                                  "distinct_cluster", "signed", "negative", "infinities", "tiny", "zero_ties"])
 def test_mask_selection_clustered_scores(mode):
     """Designed scores (component 0 of the keys, as in the test above) for the bit-mask selection of rows
     that are read from global memory (flat, 45056 tokens): all equal (every key in one bin, ties by
     position), two values or 128 values of many ties beside outliers (the bin overflows, narrowed passes),
     zero for all but 40 tokens, more outliers above the sampled range than are selected, 32768 different values
     beside outliers (10 to 300 gathered keys, ranked by several threads each), the same values on both sides of zero
-    (heads of either weight) or below it, with infinities of both signs among them, or so small that the bins
-    follow the keys' bits instead of the scores. Rows at the end of the cache,
+    (heads of either weight) or below it, with infinities of both signs among them, so small that the bins
+    follow the keys' bits instead of the scores, or zero as the largest score of more tokens than are selected. Rows at the end of the cache,
     inside it, and rows with few or fewer candidates than K_sparse, against the oracle."""
     w = replace(W.L2K_MQA, name=f"mask_{mode}", keep_pages=0, seq_len=45056, k_sparse=1500)
     n, H, d = w.seq_len, w.n_heads, w.head_dim
@@ -505,6 +505,11 @@ def test_mask_selection_clustered_scores(mode):
         if mode == "infinities":
             kb[g.choice(n, 300, replace=False), 0] = 0x7F80
             kb[g.choice(n, 300, replace=False), 0] = 0xFF80
+    elif mode == "zero_ties":    # negative weights: 600 zeros are the largest scores, of which the last rows select 500
+        w = replace(w, k_sparse=500)
+        wt[:] = -1.0
+        kb[:, 0] = 0x3F80 + (s % 128)
+        kb[g.choice(n, 600, replace=False), 0] = 0
     elif mode == "tiny":
         kb[:, 0] = 0x0880 + g.integers(0, 128, n)
     else:
